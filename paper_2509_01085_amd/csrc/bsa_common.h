@@ -137,8 +137,6 @@ struct AttnArgs {
   int split_S, split_n;
   float* part;
   void* fwd_ws;
-  int kv_split_S, kv_split_n;  // the same for the dK/dV launch
-  float* kv_part;
   int pack;  // backward records hold two query blocks of at most 16 retained queries each
 };
 

@@ -1,0 +1,144 @@
+// Shared by the bf16 MFMA attention kernels: work items of a launch, the walk over block lists and
+// the backward's query-block records.
+#pragma once
+
+#include <math.h>
+
+#include "bsa_mfma.h"
+
+namespace bsa {
+
+constexpr int PG = 4;     // query blocks per workgroup
+constexpr int PBK = 64;   // tokens per block on this path
+
+// ---- work items -------------------------------------------------------------------------
+// A launch covers `units` units of work (four query blocks of a head each).  Workgroups are
+// dispatched round-robin over the 8 XCDs, so XCD x is given the contiguous unit range
+// [x*q + min(x, r), ...) with q = units / 8, r = units % 8: neighbouring query blocks, whose
+// lists overlap, share that XCD's L2.  When the launch is only a few rounds long (units per
+// workgroup slot), its tail leaves most of the chip idle; then the last split_n units of every
+// XCD's range are walked in split_S segments by separate, shorter workgroups dispatched last,
+// and a combine launch merges their partial results.  The dK/dV launch (units = pairs of KV
+// blocks, one workgroup per CU) does the same for the units of its last, partly filled round.
+constexpr int kCUs = 256;  // compute units of the MI355X
+
+
+struct SplitPlan {
+  int S, n;   // segments per split unit; split units per XCD (0: no splitting)
+  int grid;   // workgroups of the main launch
+  int units;  // number of split units = workgroups of the combine launch
+};
+
+static SplitPlan plan_split(int units, int slots, bool allow) {
+  SplitPlan p{1, 0, 0, 0};
+  const int q = units / 8, r = units % 8, cmax = q + (r ? 1 : 0);
+  if (allow && q >= 5 && units < 12 * slots) {  // short launch: split the last fifth in four
+    p.S = 4;
+    p.n = (q + 4) / 5;
+  }
+  p.grid = 8 * (cmax - p.n + p.S * p.n);
+  p.units = 8 * p.n;
+  return p;
+}
+
+struct Item {
+  int unit, seg, nseg;
+  int sidx;  // ordinal of a split unit (addresses its partial results), -1 for a whole unit
+};
+
+__device__ inline bool item_of(int b, int units, int S, int n, Item& it) {
+  const int q = units >> 3, r = units & 7, x = b & 7, k = b >> 3;
+  const int start = x * q + min(x, r), cnt = q + (x < r ? 1 : 0), whole = cnt - n;
+  if (k < whole) {
+    it.unit = start + k; it.seg = 0; it.nseg = 1; it.sidx = -1;
+    return true;
+  }
+  const int kk = k - whole, si = kk / S;
+  if (si >= n) return false;
+  it.unit = start + whole + si; it.seg = kk - si * S; it.nseg = S; it.sidx = x * n + si;
+  return true;
+}
+
+// the split unit a workgroup of the combine launch finishes
+__device__ inline Item split_item_of(int b, int units, int S, int n) {
+  const int q = units >> 3, r = units & 7, x = b & 7, si = b >> 3;
+  Item it;
+  it.unit = x * q + min(x, r) + (q + (x < r ? 1 : 0) - n) + si; it.seg = 0; it.nseg = S; it.sidx = x * n + si;
+  return it;
+}
+
+// Ascending walk over the union of NL block lists kept as bit masks in LDS.  Every value
+// is wave-uniform; readfirstlane moves the words to scalar registers so the bit scanning
+// costs scalar, not vector, instructions.
+template <int NL, int NOWN>
+struct WalkN {
+  const uint32_t* masks;  // [NL][W]
+  int W, own_list, word, left;
+  uint32_t u, own, own2;  // own, own2: the wavefront's own list(s), NOWN of them, own_list and own_list + 1
+  __device__ inline WalkN(const uint32_t* m, int W_, int own_)
+      : masks(m), W(W_), own_list(own_), word(-1), left(0x7fffffff), u(0), own(0), own2(0) {}
+  __device__ inline uint32_t any(int w) const {
+    uint32_t all = masks[w];
+#pragma unroll
+    for (int k = 1; k < NL; ++k) all |= masks[k * W + w];
+    return all;
+  }
+  __device__ inline void load() {
+    u = __builtin_amdgcn_readfirstlane(any(word));
+    own = __builtin_amdgcn_readfirstlane(masks[own_list * W + word]);
+    if (NOWN == 2) own2 = __builtin_amdgcn_readfirstlane(masks[(own_list + 1) * W + word]);
+  }
+  // next tile of the union; mine: bit 0 = on the first own list, bit 1 = on the second
+  __device__ inline int next(uint32_t& mine) {
+    if (left <= 0) return -1;
+    while (u == 0) {
+      if (++word >= W) return -1;
+      load();
+    }
+    const int b = __builtin_ctz(u);
+    u &= u - 1;
+    mine = ((own >> b) & 1u) | (NOWN == 2 ? ((own2 >> b) & 1u) << 1 : 0u);
+    --left;
+    return word * 32 + b;
+  }
+  __device__ inline int next(bool& mine) {
+    uint32_t m = 0;
+    const int r = next(m);
+    mine = m != 0;
+    return r;
+  }
+  // restrict a fresh walk to segment `seg` of `nseg` equal parts of the union
+  __device__ inline void restrict_to(int seg, int nseg) {
+    int total = 0;
+    for (int w = 0; w < W; ++w) total += __builtin_popcount(__builtin_amdgcn_readfirstlane(any(w)));
+    int skip = (int)((int64_t)seg * total / nseg);
+    left = (int)((int64_t)(seg + 1) * total / nseg) - skip;
+    while (++word < W) {
+      load();
+      const int c = __builtin_popcount(u);
+      if (skip < c) break;
+      skip -= c;
+      u = 0;
+    }
+    for (; skip > 0; --skip) u &= u - 1;
+  }
+};
+
+#define BSA_FENCE() __builtin_amdgcn_sched_barrier(0)
+#define BSA_WAIT_VM(n) asm volatile("s_waitcnt vmcnt(" #n ")" ::: "memory")
+
+// Record of 32 retained query rows in the backward workspace (the image in memory is the image in
+// LDS).  A query block has one, or two when it retains more than 32 queries.
+template <int D>
+struct BwdRec {
+  static constexpr int RB = D * 2;
+  static constexpr int QC = 0;               // [32][D] bf16, swizzled rows
+  static constexpr int GC = 32 * RB;         // [32][D] bf16, swizzled rows
+  static constexpr int LS = 64 * RB;         // float lse2[32]
+  static constexpr int DL = LS + 128;        // float -delta[32]
+  static constexpr int BYTES = DL + 128;     // multiple of 256
+};
+
+int launch_bwd_dkv_pipe(const Geom& g, const AttnArgs& a, hipStream_t st);
+
+}  // namespace bsa
