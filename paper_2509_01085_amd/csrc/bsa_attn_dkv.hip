@@ -105,7 +105,7 @@ __device__ inline void static_for(F f) {
   }
 }
 
-constexpr int kListCap = 8192;  // blocks per head at most: entries of the workgroup's list in LDS
+constexpr int kListCap = 8192;  // blocks per head at most
 
 // D: channels of a record row (64 or 128), DC: channels that are multiplied (d rounded up to 32),
 // NH: 32-key halves of a KV block, PACK: a record holds two query blocks of at most 16 rows.
@@ -120,7 +120,6 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
   static_assert(8 * R::BYTES >= NT * 16 * 1024, "the record ring doubles as the reduction buffer");
   extern __shared__ __align__(16) uint8_t smem[];  // [4 wavefronts][2 records] | list
   uint16_t* list = reinterpret_cast<uint16_t*>(smem + 8 * R::BYTES);
-  __shared__ int nlist_s;
 
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int grp = lane >> 5, col = lane & 31;
@@ -135,33 +134,46 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
   const uint16_t* Vh = static_cast<const uint16_t*>(a.V) + bh * g.L * g.d;
   const uint8_t* ws = static_cast<const uint8_t*>(a.ws) + bh * nrec * (int64_t)R::BYTES;
 
-  // the block's list: entries are query blocks, packed: pairs with two bits for its members (bits 14, 15)
-  int cnt;
-  if (g.dense) {
-    cnt = g.N;
-    for (int t = tid; t < cnt; t += 256) list[t] = (uint16_t)t;
-  } else {
-    const int beg = a.k2q_ptr[unit];
-    cnt = min(max(a.k2q_ptr[unit + 1] - beg, 0), min(g.N, kListCap));
-    if (!PACK) {
-      for (int t = tid; t < cnt; t += 256) list[t] = (uint16_t)min(max(a.k2q_idx[beg + t], 0), g.N - 1);
-    } else if (wave == 0) {  // ascending block ids: an entry starts a pair unless its predecessor is in the same one
-      int base = 0;
-      for (int t0 = 0; t0 < cnt; t0 += 64) {
-        const int t = t0 + lane;
-        const int b = t < cnt ? min(max(a.k2q_idx[beg + t], 0), g.N - 1) : -4;
-        const int before = t > 0 && t < cnt ? a.k2q_idx[beg + t - 1] : -2;
-        const int after = t + 1 < cnt ? a.k2q_idx[beg + t + 1] : -2;
-        const bool first = t < cnt && (before >> 1) != (b >> 1);
-        const unsigned long long m = __ballot(first);
-        if (first) {
-          const bool both = (after >> 1) == (b >> 1);
-          list[base + __popcll(m & ((1ull << lane) - 1ull))] = (uint16_t)((b >> 1) | (both ? 0xc000 : (b & 1) ? 0x8000 : 0x4000));
-        }
-        base += __popcll(m);
-      }
-      if (lane == 0) nlist_s = base;
+  // The block's list as a set: bits in LDS, then entries in ascending order (a duplicate counts once, a
+  // block id out of range not at all).  Entries are query blocks; packed: pairs, with two bits for
+  // its members (bits 14, 15).
+  uint32_t* bits = reinterpret_cast<uint32_t*>(smem);  // one word a thread; in the record ring, not in use yet
+  int* base = reinterpret_cast<int*>(bits + kListCap / 32);  // entries ahead of a word's, then their number
+  bits[tid] = g.dense ? (tid * 32 + 32 <= g.N ? 0xffffffffu : tid * 32 < g.N ? (1u << (g.N - tid * 32)) - 1u : 0u) : 0u;
+  __syncthreads();
+  if (!g.dense) {
+    const int beg = a.k2q_ptr[unit], end = a.k2q_ptr[unit + 1];
+    for (int t = beg + tid; t < end; t += 256) {
+      const int b = a.k2q_idx[t];
+      if ((unsigned)b < (unsigned)g.N) atomicOr(&bits[b >> 5], 1u << (b & 31));
     }
+    __syncthreads();
+  }
+  auto heads = [&](uint32_t w) { return PACK ? (w | (w >> 1)) & 0x55555555u : w; };  // a bit for every entry
+  if (wave == 0) {
+    int n[4], sum = 0;
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      n[k] = sum;
+      sum += __popc(heads(bits[4 * lane + k]));
+    }
+    int upto = sum;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int v = __shfl_up(upto, off);
+      if (lane >= off) upto += v;
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) base[4 * lane + k] = upto - sum + n[k];
+    if (lane == 63) base[256] = upto;
+  }
+  __syncthreads();
+  const int cnt = base[256];
+  for (int t = tid; t < (PACK ? (g.N + 1) / 2 : g.N); t += 256) {
+    const int b = PACK ? 2 * t : t, bit = b & 31;
+    const uint32_t w = bits[b >> 5], hd = heads(w);
+    if ((hd >> bit) & 1u)
+      list[base[b >> 5] + __popc(hd & ((1u << bit) - 1u))] = (uint16_t)(PACK ? t | (((w >> bit) & 3u) << 14) : t);
   }
 
   // K and V fragments (B operands): lane (col, grp) holds channels 16 s + 8 grp .. +7 of key 32 h + col;
@@ -192,8 +204,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
     for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
       for (int r = 0; r < 16; ++r) dk[h][dt][r] = dv[h][dt][r] = 0.f;
-  __syncthreads();
-  if (PACK && !g.dense) cnt = nlist_s;
+  __syncthreads();  // the list is whole, the ring free
   const int items = __builtin_amdgcn_readfirstlane(cnt * nqt);
   const int mine = (items - wave + 3) >> 2;  // items wave, wave + 4, ...
   const float c2 = a.sm_scale * kLog2e;

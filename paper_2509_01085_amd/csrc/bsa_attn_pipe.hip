@@ -362,10 +362,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 //   dQ    the forward's walk (four query blocks per workgroup, union of their KV lists):
 //         S^T = K Q^T, dP^T = V G^T, dS^T = P^T (dP^T - delta), dQ^T += K^T dS^T, one key half
 //         at a time; K^T comes from the same K tile through transposed LDS reads.
-//   dKV   a workgroup owns two adjacent KV blocks, whose K and V tiles stay in LDS, and walks
-//         the union of their k2q lists; the query-block records stream through an LDS ring
-//         by DMA.  A wavefront owns 32 keys: S = Qc K^T, dP = Gc V^T, dV^T += Gc^T P,
-//         dK^T += Qc^T dS, accumulators in registers for the whole walk.
+//   dKV   bsa_attn_dkv.hip: a workgroup owns one KV block and streams its list's records.
 // =====================================================================================
 
 template <int D, int NQT>

@@ -18,8 +18,7 @@ constexpr int PBK = 64;   // tokens per block on this path
 // lists overlap, share that XCD's L2.  When the launch is only a few rounds long (units per
 // workgroup slot), its tail leaves most of the chip idle; then the last split_n units of every
 // XCD's range are walked in split_S segments by separate, shorter workgroups dispatched last,
-// and a combine launch merges their partial results.  The dK/dV launch (units = pairs of KV
-// blocks, one workgroup per CU) does the same for the units of its last, partly filled round.
+// and a combine launch merges their partial results.
 constexpr int kCUs = 256;  // compute units of the MI355X
 
 

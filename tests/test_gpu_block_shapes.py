@@ -1,0 +1,100 @@
+"""Attention kernels at the sizes where their tiling can go wrong, against the oracle: block sizes
+around the 16- and 64-key tiles, head dimensions around the 16- and 32-channel steps, retained
+queries around one and two 16-row tiles.  Infinities in V, and lists that are sets in any order."""
+from math import sqrt
+
+import numpy as np
+import pytest
+import torch
+
+from bsa_workloads import Workload, head_inputs
+from oracle import bsa_oracle as o
+from paper_2509_01085_amd import binding as B
+
+import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+# name: (dtype, d, grid, block, keep ratio, window)
+SHAPES = {
+    "bk1_f32_d8": ("fp32", 8, (2, 3, 4), (1, 1, 1), 1.0, (0, 0, 0)),
+    "bk15_bf16_d8": ("bf16", 8, (3, 9, 5), (1, 3, 5), 0.5, (0, 0, 0)),
+    "bk16_f32_d24": ("fp32", 24, (4, 8, 8), (1, 4, 4), 0.5, (1, 2, 2)),
+    "bk18_bf16_d72": ("bf16", 72, (4, 9, 6), (2, 3, 3), 0.9, (0, 0, 0)),       # 17 queries: a second tile of one row
+    "bk30_bf16_d80": ("bf16", 80, (6, 4, 10), (3, 2, 5), 0.5, (0, 0, 0)),
+    "bk45_bf16_d96": ("bf16", 96, (3, 6, 10), (3, 3, 5), 0.75, (0, 0, 0)),     # 34 queries, three key tiles
+    "bk60_bf16_d128": ("bf16", 128, (6, 10, 8), (3, 5, 4), 0.5, (0, 0, 0)),
+    "bk60_f32_d104": ("fp32", 104, (6, 10, 8), (3, 5, 4), 0.5, (0, 0, 0)),
+    "bk64_bf16_d48": ("bf16", 48, (4, 8, 12), (4, 4, 4), 0.5, (2, 2, 2)),
+    "bk64_bf16_d152": ("bf16", 152, (4, 8, 8), (4, 4, 4), 0.3, (0, 0, 0)),
+    "bk24_bf16_d200": ("bf16", 200, (4, 6, 12), (2, 3, 4), 0.5, (0, 0, 0)),
+    "bk70_bf16_d40": ("bf16", 40, (2, 10, 14), (2, 5, 7), 0.5, (0, 0, 0)),     # a step of 64 keys and one of six
+    "bk128_bf16_d256": ("bf16", 256, (4, 8, 16), (4, 4, 8), 0.3, (0, 0, 0)),
+    "bk256_f32_d128": ("fp32", 128, (4, 8, 16), (4, 8, 8), 0.3, (0, 0, 0)),
+}
+
+
+def _run(wl):
+    x = U.device_inputs(wl)
+    shp, _, _, lists, keep = U.run_indices(wl, x)
+    O, LSE = B.attn_fwd(shp, x["Q"], x["K"], x["V"], lists, keep)
+    return x, shp, lists, keep, O, LSE
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_block_shape(name):
+    U.progress(f"block shape {name}")
+    dtype, d, grid, block, keep_ratio, window = SHAPES[name]
+    wl = Workload("shape_" + name, 1, 2, d, dtype, grid, block, threshold=0.7, keep_ratio=keep_ratio, window=window)
+    x, shp, lists, keep, O, LSE = _run(wl)
+    dQ, dK, dV = B.attn_bwd(shp, x["Q"], x["K"], x["V"], O, LSE, x["dO"], lists, keep)
+    torch.cuda.synchronize()
+    part = U.part_of(wl)
+    for h in range(wl.H):
+        xi = head_inputs(wl, 0, h)
+        ix, rO, rL, rdQ, rdK, rdV = o.bsa_head(xi["Q"], xi["K"], xi["V"], xi["dO"], part, wl.threshold, wl.keep_ratio,
+                                               o_storage=U.o_storage_of(wl))
+        assert np.array_equal(keep[0, h].cpu().numpy(), ix.keep_idx)
+        sg = U.T.rounding_sigma(xi, part, ix, 1 / sqrt(d)) if dtype == "bf16" else None
+        U.check_tensors(name, f"h{h}", dtype, [(t, U.host_f64(got[0, h]), ref) for t, got, ref in
+                                               (("O", O, rO), ("dQ", dQ, rdQ), ("dK", dK, rdK), ("dV", dV, rdV))],
+                        sigma=sg, lse=(U.host_f64(LSE[0, h]), rL))
+
+
+@pytest.mark.parametrize("name,value", [("bk30_bf16_d80", float("inf")), ("bk60_bf16_d128", float("-inf"))])
+def test_infinity_in_v_stays_in_its_channel(name, value):
+    """Every query lists every block here and no probability underflows, so the channel of an
+    infinite V entry is infinite for every token, and nothing else is."""
+    dtype, d, grid, block, keep_ratio, window = SHAPES[name]
+    wl = Workload("inf_" + name, 1, 1, d, dtype, grid, block, threshold=1.0, keep_ratio=keep_ratio, window=window)
+    x, shp, lists, keep, O, _ = _run(wl)
+    assert torch.isfinite(O).all()
+    V = x["V"].clone()
+    V[0, 0, 7, 5] = value
+    O2, _ = B.attn_fwd(shp, x["Q"], x["K"], V, lists, keep)
+    assert (O2[..., 5].float() == value).all()
+    rest = torch.arange(d, device=O.device) != 5
+    # the finite channels: the same products, rounded to bf16 after sums in another order
+    assert ((O2 - O).float()[..., rest].abs() <= 2.0 ** -7 * O.float()[..., rest].abs() + 1e-5).all()
+
+
+@pytest.mark.parametrize("keep_ratio", [0.25, 0.5, 1.0])
+def test_transposed_lists_are_sets(keep_ratio):
+    """dK, dV of the bf16 path: order, repetition and ids out of range in a k2q list change nothing."""
+    wl = Workload("sets", 1, 2, 128, "bf16", (4, 12, 20), (4, 4, 4), threshold=0.8, keep_ratio=keep_ratio)
+    x, shp, lists, keep, O, LSE = _run(wl)
+    run = lambda li: B.attn_bwd(shp, x["Q"], x["K"], x["V"], O, LSE, x["dO"], li, keep)
+    want = run(lists)
+    host = U.lists_to_host(shp, lists)
+    rng = np.random.default_rng(3)
+    ptr, idx = [0], []
+    for r in range(shp.B * shp.H * shp.N):
+        own = host["k2q_idx"][host["k2q_ptr"][r]:host["k2q_ptr"][r + 1]]
+        row = np.concatenate([own, own[:2], [-1, shp.N, shp.N + 5]]).astype(np.int32)
+        rng.shuffle(row)
+        idx.append(row)
+        ptr.append(ptr[-1] + len(row))
+    i32 = lambda a: torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).cuda()
+    other = B.KvLists(lists.q2k_ptr, lists.q2k_idx, i32(ptr), i32(np.concatenate(idx)), lists.nnz, lists.workspace)
+    for a, b in zip(run(other), want):
+        assert torch.equal(a, b)
