@@ -35,7 +35,6 @@ typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-constexpr int KC = 64;             // keys per step: up to four 16-key tiles of one KV block
 constexpr float kLog2e = 1.4426950408889634f;
 constexpr float kLn2 = 0.6931471805599453f;
 
@@ -149,7 +148,7 @@ __device__ inline void col_frags(const T* row, int i, int d, float (&f)[DS]) {
 // Matrix cycles of 16 x 16 logits at d = 128, forward: 64 + 192 against 2,048.  Forward error against
 // fp64 (24 to 128 keys a block, d = 64 .. 200): LSE at most 1.5e-6 against 1.6e-6 before, O the bf16
 // rounding of the exact result in all but 0.03 % of the elements against 0.06 to 0.1 %.
-// 32,760-token layer of 60-token blocks at inference: 3.90 -> 1.51 ms.
+// 32,760-token layer of 60-token blocks at inference: 3.90 -> 1.53 ms.
 // Layout: A row i, B column i, k slot (g, t), t = 0..7; D as above.  A and B share the order of k.
 __device__ inline f32x4 mfma32b(u32x4 a, u32x4 b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
@@ -246,7 +245,7 @@ constexpr int NWV = 4;  // wavefronts per workgroup
 // Workgroup: 16 NQT retained queries of one block; its wavefronts take the 64-key steps of the
 // block's list in turn.  S^T = K Q^T (queries on the D column), online softmax in the exp2 domain,
 // O^T += V^T P^T.
-template <typename T, int DS, int NQT>
+template <typename T, int DS, int NQT, int NS>
 __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnArgs a) {
   constexpr int LDO = 16 * DS + 4;                  // padded row of the merge buffer
   extern __shared__ __align__(16) float osum[];     // [NQT * 16][LDO]
@@ -294,17 +293,18 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
   const float c2 = a.sm_scale * kLog2e;
   const int beg = g.dense ? 0 : a.q2k_ptr[row];
   const int cnt = g.dense ? g.N : a.q2k_ptr[row + 1] - beg;
+  constexpr int KC = 16 * NS;            // keys per step
   const int nch = (g.Bk + KC - 1) / KC;  // steps per KV block
   for (int n = wave; n < cnt * nch; n += NWV) {
     const int t = n / nch, k0 = (n - t * nch) * KC;
     const int64_t origin = block_origin_fast(g, listed_block(g, a.q2k_idx, beg, t));
-    const int nk = min(KC, g.Bk - k0), ns = (nk + 15) >> 4;  // keys and 16-key tiles of this step
-    f32x4 s[NQT][4];
+    const int nk = min(KC, g.Bk - k0), ns = kBf16 ? NS : (nk + 15) >> 4;  // keys and 16-key tiles of this step
+    f32x4 s[NQT][NS];
     float mx[NQT];
 #pragma unroll
     for (int u = 0; u < NQT; ++u) mx[u] = -INFINITY;
 #pragma unroll
-    for (int st = 0; st < 4; ++st) {
+    for (int st = 0; st < NS; ++st) {
       if (st < ns) {
         const T* krow = Kh + (origin + koff[k0 + min(16 * st + i16, nk - 1)]) * d;
         f32x4 kf[kBf16 ? 1 : DS];
@@ -332,13 +332,24 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
         }
       }
     }
+    // V words of key tiles st, st + 1 (bf16); those of the first two are requested ahead of the softmax
+    uint32_t vw[8][S];
+    auto load_v = [&](int st) {
+      if constexpr (kBf16) {
+#pragma unroll
+        for (int r = 0; r < 8; ++r)
+          if (st + (r >> 2) < NS)
+            col_words<DS>(Vh + (origin + koff[k0 + min(16 * st + 16 * (r >> 2) + 4 * gq + (r & 3), nk - 1)]) * d, i16, d, vw[r]);
+      }
+    };
+    load_v(0);
 #pragma unroll
     for (int u = 0; u < NQT; ++u) {
       const float mnew = fmaxf(m[u], quad_max(mx[u]) * c2);  // c2 > 0: the maximum commutes with the scaling
       const float alpha = __builtin_amdgcn_exp2f(m[u] - mnew);
       float sum = 0.f;
 #pragma unroll
-      for (int st = 0; st < 4; ++st)
+      for (int st = 0; st < NS; ++st)
         if (st < ns)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
@@ -355,38 +366,32 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     // rows past the block's last key are zeroed: their P is zero, and 0 * inf would not be
     if constexpr (kBf16) {
 #pragma unroll
-      for (int st = 0; st < 4; st += 2) {
-        if (st < ns) {
-          uint32_t vw[8][S];
+      for (int st = 0; st < NS; st += 2) {
+        if (st > 0) load_v(st);
+        if (st + 2 > NS || 16 * st + 32 > nk) {
 #pragma unroll
           for (int r = 0; r < 8; ++r) {
-            const int key = 16 * st + (r >= 4 ? 16 : 0) + 4 * gq + (r & 3);
-            col_words<DS>(Vh + (origin + koff[k0 + min(key, nk - 1)]) * d, i16, d, vw[r]);
+            const int key = 16 * st + 16 * (r >> 2) + 4 * gq + (r & 3);
+#pragma unroll
+            for (int k = 0; k < S; ++k) vw[r][k] = st + (r >> 2) < NS && key < nk ? vw[r][k] : 0u;
           }
-          if (16 * st + 32 > nk) {
+        }
+        u32x4 part[NQT][3];
 #pragma unroll
-            for (int r = 0; r < 8; ++r) {
-              const int key = 16 * st + (r >= 4 ? 16 : 0) + 4 * gq + (r & 3);
+        for (int u = 0; u < NQT; ++u)
+          split3<true>(s[u][st], st + 1 < NS ? s[u][st + 1 < NS ? st + 1 : st] : f32x4{0.f, 0.f, 0.f, 0.f}, part[u]);
 #pragma unroll
-              for (int k = 0; k < S; ++k) vw[r][k] = key < nk ? vw[r][k] : 0u;
-            }
-          }
-          u32x4 part[NQT][3];
+        for (int c = 0; c < DS; ++c) {
+          const u32x4 va = col_operand(vw, c);
 #pragma unroll
-          for (int u = 0; u < NQT; ++u) split3<true>(s[u][st], st + 1 < ns ? s[u][st + 1] : f32x4{0.f, 0.f, 0.f, 0.f}, part[u]);
+          for (int n = 2; n >= 0; --n)
 #pragma unroll
-          for (int c = 0; c < DS; ++c) {
-            const u32x4 va = col_operand(vw, c);
-#pragma unroll
-            for (int n = 2; n >= 0; --n)
-#pragma unroll
-              for (int u = 0; u < NQT; ++u) o[u][c] = mfma32b(va, part[u][n], o[u][c]);
-          }
+            for (int u = 0; u < NQT; ++u) o[u][c] = mfma32b(va, part[u][n], o[u][c]);
         }
       }
     } else {
 #pragma unroll
-      for (int st = 0; st < 4; ++st) {
+      for (int st = 0; st < NS; ++st) {
         if (st < ns) {
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
@@ -786,20 +791,35 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_ker
 }
 
 // ------------------------------------------------------------------------- launches
-template <typename T, int DS, int NQT>
+template <typename T, int DS, int NQT, int NS>
 static int fwd_n(const Geom& g, const AttnArgs& a, hipStream_t st) {
   const size_t lds = (size_t)NQT * 16 * (16 * DS + 4) * 4;
-  hipLaunchKernelGGL((fwd_generic_kernel<T, DS, NQT>), dim3(g.rows, (a.n_keep + 16 * NQT - 1) / (16 * NQT)), dim3(64 * NWV), lds, st, g, a);
+  hipLaunchKernelGGL((fwd_generic_kernel<T, DS, NQT, NS>), dim3(g.rows, (a.n_keep + 16 * NQT - 1) / (16 * NQT)), dim3(64 * NWV), lds, st, g, a);
   return check_launch();
 }
 
 // two query tiles a wavefront (half the K and V loads per product) where both exist and their
 // operands and accumulators (32 DS registers each way) leave two wavefronts per SIMD
+template <typename T, int DS, int NS>
+static int fwd_s(const Geom& g, const AttnArgs& a, hipStream_t st) {
+  if constexpr (DS <= 8)
+    if (a.n_keep > 16) return fwd_n<T, DS, 2, NS>(g, a, st);
+  return fwd_n<T, DS, 1, NS>(g, a, st);
+}
+
+// 16-key tiles per step.  bf16: compiled in, so that no branch stands between the loads of a step; the
+// block's tiles are spread evenly over its steps, and tiles past its end are masked.  fp32 takes up to
+// four and skips those past the end: its time is that of the products.
+// Compiled in against skipped, with the first V loads ahead of the softmax: 32,760-token layer of 60-token
+// blocks 1.53 -> 1.31 ms, training layer of 24-token blocks 0.315 -> 0.307.
 template <typename T, int DS>
 static int fwd_t(const Geom& g, const AttnArgs& a, hipStream_t st) {
-  if constexpr (DS <= 8)
-    if (a.n_keep > 16) return fwd_n<T, DS, 2>(g, a, st);
-  return fwd_n<T, DS, 1>(g, a, st);
+  if constexpr (sizeof(T) == 2) {
+    const int tiles = (g.Bk + 15) / 16, steps = (tiles + 3) / 4, ns = (tiles + steps - 1) / steps;
+    if (ns <= 2) return fwd_s<T, DS, 2>(g, a, st);
+    if (ns == 3) return fwd_s<T, DS, 3>(g, a, st);
+  }
+  return fwd_s<T, DS, 4>(g, a, st);
 }
 
 template <typename T, int DS>
