@@ -433,17 +433,27 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
   }
 }
 
-template <int D, int DC, int NH, bool PACK>
+template <int D>
+static size_t lds_bytes(const Geom& g) { return (size_t)8 * BwdRec<D>::BYTES + (size_t)g.N * 2; }
+
+template <int D, bool PACK>
 static int launch_t(const Geom& g, const AttnArgs& a, hipStream_t st) {
-  const size_t lds = (size_t)8 * BwdRec<D>::BYTES + (size_t)g.N * 2;
-  if (int rc = allow_dynamic_lds<bwd_dkv_pipe_kernel<D, DC, NH, PACK>>(lds)) return rc;
-  hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, DC, NH, PACK>), dim3((g.rows + 7) / 8 * 8), dim3(256), lds, st, g, a);
+  hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, D, 2, PACK>), dim3((g.rows + 7) / 8 * 8), dim3(256), lds_bytes<D>(g), st, g, a);
   return check_launch();
 }
 
+// the dynamic LDS of the launch below, for the caller to take ahead of every launch of the backward
+int grant_bwd_dkv_pipe(const Geom& g, const AttnArgs& a) {
+  if (g.d > 64)
+    return a.pack ? allow_dynamic_lds<bwd_dkv_pipe_kernel<128, 128, 2, true>>(lds_bytes<128>(g))
+                  : allow_dynamic_lds<bwd_dkv_pipe_kernel<128, 128, 2, false>>(lds_bytes<128>(g));
+  return a.pack ? allow_dynamic_lds<bwd_dkv_pipe_kernel<64, 64, 2, true>>(lds_bytes<64>(g))
+                : allow_dynamic_lds<bwd_dkv_pipe_kernel<64, 64, 2, false>>(lds_bytes<64>(g));
+}
+
 int launch_bwd_dkv_pipe(const Geom& g, const AttnArgs& a, hipStream_t st) {
-  if (g.d > 64) return a.pack ? launch_t<128, 128, 2, true>(g, a, st) : launch_t<128, 128, 2, false>(g, a, st);
-  return a.pack ? launch_t<64, 64, 2, true>(g, a, st) : launch_t<64, 64, 2, false>(g, a, st);
+  if (g.d > 64) return a.pack ? launch_t<128, true>(g, a, st) : launch_t<128, false>(g, a, st);
+  return a.pack ? launch_t<64, true>(g, a, st) : launch_t<64, false>(g, a, st);
 }
 
 }  // namespace bsa

@@ -794,6 +794,7 @@ static int launch_bwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
   const int nrec_head = PACK ? (g.N + 1) / 2 : g.N;
   const size_t nrec = (size_t)g.B * g.H * nrec_head * NQT;  // records in the workspace
   if (int rc = allow_dynamic_lds<bwd_dq_pipe_kernel<D, SPLITQ, false, PACK>>(lds_q)) return rc;
+  if (int rc = grant_bwd_dkv_pipe(g, a)) return rc;
   if (a.stages & BSA_BWD_PRE)  // LDS: per-row-group partial sums + per-window sums of the fill gradient
     hipLaunchKernelGGL((bwd_pre_pipe_kernel<D, NQT>), dim3(g.rows), dim3(256), (size_t)(256 / (D / 8) + g.nwin) * D * 4, st, g, a);
   if (a.stages & BSA_BWD_DQ) {

@@ -138,6 +138,7 @@ struct BwdRec {
   static constexpr int BYTES = DL + 128;     // multiple of 256
 };
 
+int grant_bwd_dkv_pipe(const Geom& g, const AttnArgs& a);  // before any launch of the call
 int launch_bwd_dkv_pipe(const Geom& g, const AttnArgs& a, hipStream_t st);
 
 }  // namespace bsa
