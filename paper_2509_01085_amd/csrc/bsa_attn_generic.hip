@@ -103,8 +103,8 @@ __device__ inline void store4(uint16_t* p, f32x4 v) {
 }
 
 // DS = number of 16-channel groups the kernel is compiled for (16 DS >= d).  Channels d .. 16 DS - 1
-// are read from a clamped address (finite data of the same row) against zero in the other operand,
-// or produce channels that are not stored.
+// are read from a clamped address; a channel contraction zeroes them in both operands (the data there
+// may be infinite, and 0 * inf is not 0), a row contraction produces channels that are not stored.
 __device__ inline int chan_or0(int ch, int d) { return ch < d ? ch : 0; }
 
 // the smallest head dimension that takes DS groups: channels below it need no check
@@ -112,13 +112,13 @@ template <int DS>
 constexpr int kMinD = DS == 2 ? 8 : DS == 4 ? 40 : DS == 5 ? 72 : DS == 6 ? 88 : DS == 8 ? 104 : DS == 12 ? 136 : 200;
 
 // A or B operand of a channel contraction: this lane's row, DS loads of four channels
-template <int DS, bool ZERO, typename T>
+template <int DS, typename T>
 __device__ inline void row_frags(const T* row, int g, int d, f32x4 (&f)[DS]) {
 #pragma unroll
   for (int s = 0; s < DS; ++s) {
     const int ch = 16 * s + 4 * g;
     f[s] = load4(row + chan_or0(ch, d));
-    if (ZERO && 16 * s + 16 > kMinD<DS> && ch >= d) f[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (16 * s + 16 > kMinD<DS> && ch >= d) f[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
 
@@ -279,7 +279,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     const int pos = min(q0 + 16 * t + i16, a.n_keep - 1);
     const T* qrow = Qh + (int64_t)(origin_q + koff[kept_id(g, a.keep_idx, row, a.n_keep, pos)]) * d;
     if constexpr (kBf16) row_frags_bf16<DS>(qrow, gq, d, qb[t]);
-    else row_frags<DS, true>(qrow, gq, d, q[t]);
+    else row_frags<DS>(qrow, gq, d, q[t]);
   }
   f32x4 o[NQT][DS];
   float m[NQT], l[NQT];
@@ -310,7 +310,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
         f32x4 kf[kBf16 ? 1 : DS];
         u32x4 kb[kBf16 ? S : 1];
         if constexpr (kBf16) row_frags_bf16<DS>(krow, gq, d, kb);
-        else row_frags<DS, true>(krow, gq, d, kf);
+        else row_frags<DS>(krow, gq, d, kf);
 #pragma unroll
         for (int u = 0; u < NQT; ++u) {
           f32x4 acc = {0.f, 0.f, 0.f, 0.f};
@@ -590,8 +590,8 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dq_generic_kern
       split3<false>(x, y, gb[c]);
     }
   } else {
-    row_frags<DS, true>(Qh + (int64_t)w.tok[e] * d, gq, d, q);
-    row_frags<DS, true>(w.g + e * d, gq, d, gr);
+    row_frags<DS>(Qh + (int64_t)w.tok[e] * d, gq, d, q);
+    row_frags<DS>(w.g + e * d, gq, d, gr);
   }
   const float lse2 = w.lse2[e], delta = w.delta[e];
 #pragma unroll
@@ -643,8 +643,8 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dq_generic_kern
     } else {
       const int64_t krow = (origin + koff[min(k0 + i16, last)]) * d;
       f32x4 kf[DS], vf[DS];
-      row_frags<DS, false>(Kh + krow, gq, d, kf);
-      row_frags<DS, false>(Vh + krow, gq, d, vf);
+      row_frags<DS>(Kh + krow, gq, d, kf);
+      row_frags<DS>(Vh + krow, gq, d, vf);
       f32x4 s = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < DS; ++c)
@@ -702,8 +702,8 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_ker
   f32x4 kf[kBf16 ? 1 : DS], vf[DS], dk[DS], dv[DS];
   u32x4 kb[kBf16 ? S : 1];
   if constexpr (kBf16) row_frags_bf16<DS>(Kh + ktok * d, gq, d, kb);
-  else row_frags<DS, true>(Kh + ktok * d, gq, d, kf);
-  row_frags<DS, true>(Vh + ktok * d, gq, d, vf);
+  else row_frags<DS>(Kh + ktok * d, gq, d, kf);
+  row_frags<DS>(Vh + ktok * d, gq, d, vf);
 #pragma unroll
   for (int c = 0; c < DS; ++c) dk[c] = dv[c] = f32x4{0.f, 0.f, 0.f, 0.f};
   const float c2 = a.sm_scale * kLog2e;
@@ -719,7 +719,7 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_ker
         u32x4 qb[S];
         f32x4 gf[DS];
         row_frags_bf16<DS>(Qh + (int64_t)w.tok[e0 + i16] * d, gq, d, qb);
-        row_frags<DS, false>(w.g + (e0 + i16) * d, gq, d, gf);
+        row_frags<DS>(w.g + (e0 + i16) * d, gq, d, gf);
 #pragma unroll
         for (int c = 0; c < S; ++c) s = mfma32b(qb[c], kb[c], s);
 #pragma unroll
@@ -728,8 +728,8 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_ker
           for (int x = 0; x < 4; ++x) dp = mfma4(gf[c][x], vf[c][x], dp);
       } else {
         f32x4 qf[DS], gf[DS];
-        row_frags<DS, false>(Qh + (int64_t)w.tok[e0 + i16] * d, gq, d, qf);
-        row_frags<DS, false>(w.g + (e0 + i16) * d, gq, d, gf);
+        row_frags<DS>(Qh + (int64_t)w.tok[e0 + i16] * d, gq, d, qf);
+        row_frags<DS>(w.g + (e0 + i16) * d, gq, d, gf);
 #pragma unroll
         for (int c = 0; c < DS; ++c)
 #pragma unroll

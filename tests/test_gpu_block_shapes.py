@@ -79,6 +79,36 @@ def test_infinity_in_v_stays_in_its_channel(name, value, token):
     assert ((O2 - O).float()[..., rest].abs() <= 2.0 ** -7 * O.float()[..., rest].abs() + 1e-5).all()
 
 
+@pytest.mark.parametrize("dtype,d", [("fp32", 72), ("fp32", 104), ("fp32", 136), ("bf16", 72)])
+def test_key_at_minus_infinity_in_the_backward(dtype, d):
+    """Channel 0 of one key is -inf and that channel of every query positive: its logits are -inf, its P and
+    dS zero.  Only 0 * inf of dQ's own channel 0 is not finite; d leaves padding channels in the last group."""
+    grid, block = (4, 6, 10), (2, 3, 5)
+    wl = Workload(f"neg_inf_{dtype}_{d}", 1, 1, d, dtype, grid, block, threshold=1.0, keep_ratio=0.5)
+    x = U.device_inputs(wl)
+    shp, _, _, lists, keep = U.run_indices(wl, x)
+    Q, K = x["Q"].clone(), x["K"].clone()
+    Q[..., 0] = Q[..., 0].abs() + 0.5
+    K[0, 0, 33, 0] = float("-inf")
+    O, LSE = B.attn_fwd(shp, Q, K, x["V"], lists, keep)
+    got = B.attn_bwd(shp, Q, K, x["V"], O, LSE, x["dO"], lists, keep)
+    torch.cuda.synchronize()
+    host = U.lists_to_host(shp, lists)
+    part, ptr, idx = U.part_of(wl), *U.head_csr(host, shp, 0, 0)
+    args = [U.host_f64(t[0, 0]) for t in (Q, K, x["V"])]
+    keep_h = keep[0, 0].cpu().numpy()
+    rO, _ = o.attn_fwd(*args, part, ptr, idx, keep_h, 1 / sqrt(d))
+    with np.errstate(invalid="ignore"):
+        ref = o.attn_bwd(*args, U.host_f64(x["dO"][0, 0]), part, ptr, idx, keep_h, 1 / sqrt(d), O_in=U.o_storage_of(wl)(rO))
+    for name, a, r in zip(("O", "dQ", "dK", "dV"), (O, *got), (rO, *ref)):
+        a = U.host_f64(a[0, 0])
+        assert np.array_equal(np.isfinite(a), np.isfinite(r)), name
+        a, r = a[np.isfinite(r)], r[np.isfinite(r)]
+        f = U.T.figures(a, r)  # (these kernels round no operand: the bf16 excess needs no sigma)
+        assert f["plain"] <= U.T.TOL_F32 if dtype == "fp32" else f["excess"] <= U.T.TOL_BF16, (name, f)
+    assert not np.isfinite(ref[0]).all() and np.isfinite(ref[0][:, 1:]).all()
+
+
 @pytest.mark.parametrize("keep_ratio", [0.25, 0.5, 1.0])
 def test_transposed_lists_are_sets(keep_ratio):
     """dK, dV of the bf16 path: order, repetition and ids out of range in a k2q list change nothing."""
