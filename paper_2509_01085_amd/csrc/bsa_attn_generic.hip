@@ -83,6 +83,10 @@ __device__ inline float quad_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
+// What the exponents of a row are taken relative to: its maximum, and 0 while every logit it has met is
+// -inf (a wavefront may begin with masked keys; relative to -inf they would be NaN)
+__device__ inline float finite_base(float m) { return m == -INFINITY ? 0.f : m; }
+
 __device__ inline f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 __device__ inline f32x4 load4(const uint16_t* p) {
   const u32x2 v = *reinterpret_cast<const u32x2*>(p);
@@ -345,7 +349,8 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     load_v(0);
 #pragma unroll
     for (int u = 0; u < NQT; ++u) {
-      const float mnew = fmaxf(m[u], quad_max(mx[u]) * c2);  // c2 > 0: the maximum commutes with the scaling
+      const float mtrue = fmaxf(m[u], quad_max(mx[u]) * c2);  // c2 > 0: the maximum commutes with the scaling
+      const float mnew = finite_base(mtrue);
       const float alpha = __builtin_amdgcn_exp2f(m[u] - mnew);
       float sum = 0.f;
 #pragma unroll
@@ -357,7 +362,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
             sum += s[u][st][r];
           }
       l[u] = l[u] * alpha + sum;  // per lane; the four lanes of a query are summed at the end
-      m[u] = mnew;
+      m[u] = mtrue;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
 #pragma unroll
         for (int c = 0; c < DS; ++c) o[u][c] *= alpha;
@@ -411,7 +416,8 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
       }
     }
   }
-  // merge the wavefronts: m = max m_w, (l, O) = sum of (l_w, O_w) 2^(m_w - m), wavefronts in order
+  // merge the wavefronts: m = max m_w, (l, O) = sum of (l_w, O_w) 2^(m_w - m), wavefronts in order (one
+  // that met no key above -inf has l_w = O_w = 0)
 #pragma unroll
   for (int u = 0; u < NQT; ++u) {
     l[u] = quad_sum(l[u]);
@@ -427,13 +433,12 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     float mt = ml[0][u][0][i16], lt = 0.f;
 #pragma unroll
     for (int w = 1; w < NWV; ++w) mt = fmaxf(mt, ml[w][u][0][i16]);
+    mt = finite_base(mt);
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) {
-      const float mw = ml[w][u][0][i16];
-      lt += mw == -INFINITY ? 0.f : ml[w][u][1][i16] * __builtin_amdgcn_exp2f(mw - mt);
-    }
+    for (int w = 0; w < NWV; ++w) lt += ml[w][u][1][i16] * __builtin_amdgcn_exp2f(ml[w][u][0][i16] - mt);
     lse[u] = lt > 0.f ? (mt + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
-    const float w = m[u] == -INFINITY || !(lt > 0.f) ? 0.f : __builtin_amdgcn_exp2f(m[u] - mt) / lt;
+    // (no mass: an empty list gives zeros, a list of nothing but -inf logits NaN)
+    const float w = lt > 0.f ? __builtin_amdgcn_exp2f(m[u] - mt) / lt : cnt > 0 ? NAN : 0.f;
 #pragma unroll
     for (int c = 0; c < DS; ++c) o[u][c] *= w;
   }

@@ -109,6 +109,30 @@ def test_key_at_minus_infinity_in_the_backward(dtype, d):
     assert not np.isfinite(ref[0]).all() and np.isfinite(ref[0][:, 1:]).all()
 
 
+@pytest.mark.parametrize("dtype,d,block", [("fp32", 64, (2, 3, 5)), ("bf16", 72, (2, 3, 5)), ("bf16", 128, (4, 6, 5)), ("fp32", 200, (1, 3, 5))])
+def test_blocks_at_minus_infinity(dtype, d, block):
+    """Whole KV blocks whose logits are -inf, at every position of a list: they weigh nothing, whichever
+    wavefront begins with them.  With every block masked the softmax has no value: O is NaN, LSE -inf."""
+    grid = tuple(2 * b for b in block)  # eight blocks, all listed
+    wl = Workload(f"masked_{dtype}_{d}", 1, 1, d, dtype, grid, block, threshold=1.0, keep_ratio=0.5)
+    x = U.device_inputs(wl)
+    shp, _, _, lists, keep = U.run_indices(wl, x)
+    part, host = U.part_of(wl), U.lists_to_host(shp, lists)
+    ptr, idx = U.head_csr(host, shp, 0, 0)
+    tok, keep_h = part.block_tokens(), keep[0, 0].cpu().numpy()
+    Q = x["Q"].clone()
+    Q[..., 0] = Q[..., 0].abs() + 0.5
+    for masked in ([1], [2, 3], [1, 3, 5, 7], [0], [0, 1, 2, 3, 4, 5, 6], list(range(8))):
+        K = x["K"].clone()
+        K[0, 0, torch.from_numpy(tok[masked].reshape(-1)).cuda(), 0] = float("-inf")
+        O, LSE = B.attn_fwd(shp, Q, K, x["V"], lists, keep)
+        if len(masked) == 8:
+            assert O.isnan().all() and (LSE == float("-inf")).all()
+            continue
+        rO, rL = o.attn_fwd(*[U.host_f64(t[0, 0]) for t in (Q, K, x["V"])], part, ptr, idx, keep_h, 1 / sqrt(d))
+        U.check_tensors(wl.name, f"blocks {masked}", dtype, [("O", U.host_f64(O[0, 0]), rO)], lse=(U.host_f64(LSE[0, 0]), rL))
+
+
 @pytest.mark.parametrize("keep_ratio", [0.25, 0.5, 1.0])
 def test_transposed_lists_are_sets(keep_ratio):
     """dK, dV of the bf16 path: order, repetition and ids out of range in a k2q list change nothing."""
