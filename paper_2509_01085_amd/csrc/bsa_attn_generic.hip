@@ -198,21 +198,23 @@ __device__ inline u32x4 col_operand(const uint32_t (&w)[8][W], int c) {
   return u32x4{halves_lo(w[0][k], w[1][k]), halves_lo(w[2][k], w[3][k]), halves_lo(w[4][k], w[5][k]), halves_lo(w[6][k], w[7][k])};
 }
 
-// x = part[0] + part[1] + part[2] for the k slots t = 0..3 (a) and 4..7 (b).  PROB: x >= 0, and a part
-// that would be zero becomes 2^-126, so that an infinity in the other operand does not turn into NaN.
-// Otherwise an infinite x leaves its other parts zero.
+// x = part[0] + part[1] + part[2] for the k slots t = 0..3 (a) and 4..7 (b).  PROB: x >= 0, and where x is
+// not zero a part that would be zero becomes 2^-126, so that an infinity in the other operand does not turn
+// into NaN (where x is zero all parts are: 2^-126 of a value at the type's limit is not small).  Otherwise
+// an infinite x leaves its other parts zero.
 template <bool PROB>
 __device__ inline void split3(f32x4 a, f32x4 b, u32x4 (&part)[3]) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     float x[2] = {k < 2 ? a[2 * k] : b[2 * k - 4], k < 2 ? a[2 * k + 1] : b[2 * k - 3]};
+    const float least[2] = {fminf(x[0], 0x1p-126f), fminf(x[1], 0x1p-126f)};
 #pragma unroll
     for (int n = 0; n < 3; ++n) {
       part[n][k] = halves_hi(__float_as_uint(x[0]), __float_as_uint(x[1]));
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const float rest = x[h] - __uint_as_float(__float_as_uint(x[h]) & 0xffff0000u);
-        x[h] = PROB ? fmaxf(rest, 0x1p-126f) : copysignf(fmaxf(fabsf(rest), 0.f), x[h]);  // (fmaxf drops a NaN)
+        x[h] = PROB ? fmaxf(rest, least[h]) : copysignf(fmaxf(fabsf(rest), 0.f), x[h]);  // (fmaxf drops a NaN)
       }
     }
   }

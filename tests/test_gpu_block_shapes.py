@@ -133,6 +133,23 @@ def test_blocks_at_minus_infinity(dtype, d, block):
         U.check_tensors(wl.name, f"blocks {masked}", dtype, [("O", U.host_f64(O[0, 0]), rO)], lse=(U.host_f64(LSE[0, 0]), rL))
 
 
+@pytest.mark.parametrize("dtype,d,block", [("bf16", 72, (2, 3, 5)), ("bf16", 128, (3, 5, 4)), ("fp32", 64, (2, 3, 5))])
+def test_zero_probability_keeps_any_finite_value_out(dtype, d, block):
+    """A key whose probability underflows to zero adds nothing, also with V at the type's lowest value."""
+    grid = tuple(2 * b for b in block)
+    wl = Workload(f"lowest_{dtype}_{d}", 1, 1, d, dtype, grid, block, threshold=1.0, keep_ratio=0.5)
+    x = U.device_inputs(wl)
+    shp, _, _, lists, keep = U.run_indices(wl, x)
+    Q, K, V = (x[n].clone() for n in ("Q", "K", "V"))
+    Q[..., 0] = Q[..., 0].abs() + 0.5
+    K[0, 0, 17, 0] = -1e5
+    V[0, 0, 17] = torch.finfo(V.dtype).min
+    O, LSE = B.attn_fwd(shp, Q, K, V, lists, keep)
+    ptr, idx = U.head_csr(U.lists_to_host(shp, lists), shp, 0, 0)
+    rO, rL = o.attn_fwd(*[U.host_f64(t[0, 0]) for t in (Q, K, V)], U.part_of(wl), ptr, idx, keep[0, 0].cpu().numpy(), 1 / sqrt(d))
+    U.check_tensors(wl.name, "O", dtype, [("O", U.host_f64(O[0, 0]), rO)], lse=(U.host_f64(LSE[0, 0]), rL))
+
+
 @pytest.mark.parametrize("keep_ratio", [0.25, 0.5, 1.0])
 def test_transposed_lists_are_sets(keep_ratio):
     """dK, dV of the bf16 path: order, repetition and ids out of range in a k2q list change nothing."""
