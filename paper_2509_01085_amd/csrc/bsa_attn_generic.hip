@@ -532,9 +532,10 @@ __global__ __launch_bounds__(256) void bwd_pre_generic_kernel(Geom g, AttnArgs a
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) part += __shfl_xor(part, o);
     if (lane == 0) {
-      const float lse = kp < a.n_keep ? Lh[tok] : -INFINITY;
       w.delta[e] = part;
-      w.lse2[e] = lse == -INFINITY ? INFINITY : lse * kLog2e;  // padding and empty lists: exp2(x - inf) = 0
+      // padding: exp2(x - inf) = 0.  A row whose softmax has no value left LSE = -inf: its P is not finite, and
+      // neither are the gradients it reaches (one with an empty list reaches none)
+      w.lse2[e] = kp < a.n_keep ? Lh[tok] * kLog2e : INFINITY;
       w.tok[e] = (int)tok;
     }
   }

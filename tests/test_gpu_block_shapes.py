@@ -150,6 +150,26 @@ def test_zero_probability_keeps_any_finite_value_out(dtype, d, block):
     U.check_tensors(wl.name, "O", dtype, [("O", U.host_f64(O[0, 0]), rO)], lse=(U.host_f64(LSE[0, 0]), rL))
 
 
+@pytest.mark.parametrize("dtype,d,block", [("fp32", 64, (2, 3, 5)), ("fp32", 136, (1, 3, 5)), ("bf16", 72, (2, 3, 5)), ("bf16", 128, (3, 5, 4))])
+def test_nan_reaches_every_gradient(dtype, d, block):
+    """One NaN in K, every block listed: no row has a softmax, and no gradient may look as if it had."""
+    grid = tuple(2 * b for b in block)
+    wl = Workload(f"nan_{dtype}_{d}", 1, 1, d, dtype, grid, block, threshold=1.0, keep_ratio=0.5)
+    x = U.device_inputs(wl)
+    shp, _, _, lists, keep = U.run_indices(wl, x)
+    K = x["K"].clone()
+    K[0, 0, 17, 3] = float("nan")
+    O, LSE = B.attn_fwd(shp, x["Q"], K, x["V"], lists, keep)
+    dQ, dK, dV = B.attn_bwd(shp, x["Q"], K, x["V"], O, LSE, x["dO"], lists, keep)
+    kept = torch.zeros(shp.L, dtype=torch.bool)
+    tok = U.part_of(wl).block_tokens()
+    for i, ids in enumerate(keep[0, 0].cpu().numpy()):
+        kept[torch.from_numpy(tok[i, ids])] = True
+    assert O.isnan().all() and not LSE.isfinite().any()
+    assert not dQ[0, 0].cpu()[kept].isfinite().any() and not dQ[0, 0].cpu()[~kept].any()
+    assert not dK.isfinite().any() and not dV.isfinite().any()
+
+
 @pytest.mark.parametrize("keep_ratio", [0.25, 0.5, 1.0])
 def test_transposed_lists_are_sets(keep_ratio):
     """dK, dV of the bf16 path: order, repetition and ids out of range in a k2q list change nothing."""
