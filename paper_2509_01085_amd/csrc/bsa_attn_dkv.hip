@@ -134,6 +134,22 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
   const uint16_t* Vh = static_cast<const uint16_t*>(a.V) + bh * g.L * g.d;
   const uint8_t* ws = static_cast<const uint8_t*>(a.ws) + bh * nrec * (int64_t)R::BYTES;
 
+  // K and V fragments (B operands): lane (col, grp) holds channels 16 s + 8 grp .. +7 of key 32 h + col;
+  // channels and keys past the end repeat earlier ones (met by zero record channels, not stored).
+  // Requested ahead of the list, whose loads they overlap.
+  bf16x8 kf[NH][DS], vf[NH][DS];
+  const int origin = block_origin(g, j);
+#pragma unroll
+  for (int h = 0; h < NH; ++h) {
+    const int64_t tok = origin + intra_offset(g, min(32 * h + col, g.Bk - 1));
+#pragma unroll
+    for (int s = 0; s < DS; ++s) {
+      const int ch = 16 * s + 8 * grp, c = ch < g.d ? ch : 0;
+      kf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Kh + tok * g.d + c));
+      vf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Vh + tok * g.d + c));
+    }
+  }
+
   // The block's list as a set: bits in LDS, then entries in ascending order (a duplicate counts once, a
   // block id out of range not at all).  Entries are query blocks; packed: pairs, with two bits for
   // its members (bits 14, 15).
@@ -176,20 +192,6 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
       list[base[b >> 5] + __popc(hd & ((1u << bit) - 1u))] = (uint16_t)(PACK ? t | (((w >> bit) & 3u) << 14) : t);
   }
 
-  // K and V fragments (B operands): lane (col, grp) holds channels 16 s + 8 grp .. +7 of key 32 h + col;
-  // channels and keys past the end repeat earlier ones (met by zero record channels, not stored)
-  bf16x8 kf[NH][DS], vf[NH][DS];
-  const int origin = block_origin(g, j);
-#pragma unroll
-  for (int h = 0; h < NH; ++h) {
-    const int64_t tok = origin + intra_offset(g, min(32 * h + col, g.Bk - 1));
-#pragma unroll
-    for (int s = 0; s < DS; ++s) {
-      const int ch = 16 * s + 8 * grp, c = ch < g.d ? ch : 0;
-      kf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Kh + tok * g.d + c));
-      vf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Vh + tok * g.d + c));
-    }
-  }
 #pragma unroll
   for (int h = 0; h < NH; ++h)
 #pragma unroll
@@ -397,39 +399,49 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
       for (int dt = 0; dt < DT; ++dt) asm volatile("" : "+a"(dk[h][dt]), "+a"(dv[h][dt]));
   }
 
-  // sum of the four wavefronts, in order, through the idle ring: dK then dV
+  // sum of the four wavefronts, in order, through the idle ring: dK then dV.  Of at most two items the last
+  // two wavefronts have none, and their zeros stay out: a 256-token layer at d = 128, where this sum is a
+  // good part of the launch, 13.8 -> 12.9 us with 16 queries a block, 14.5 -> 14.0 with 32 (with the loads
+  // above); no difference from 3,000 tokens up.
   f32x4* red = reinterpret_cast<f32x4*>(smem) + lane;  // [tile][wavefront][4][64]
 #pragma unroll
   for (int pass = 0; pass < 2; ++pass) {
     __syncthreads();
+    if (wave < 2 || items > 2) {
 #pragma unroll
-    for (int h = 0; h < NH; ++h)
+      for (int h = 0; h < NH; ++h)
 #pragma unroll
-      for (int dt = 0; dt < DT; ++dt) {
-        const f32x16& acc = pass ? dv[h][dt] : dk[h][dt];
+        for (int dt = 0; dt < DT; ++dt) {
+          const f32x16& acc = pass ? dv[h][dt] : dk[h][dt];
 #pragma unroll
-        for (int r4 = 0; r4 < 4; ++r4)
-          red[(((h * DT + dt) * 4 + wave) * 4 + r4) * 64] = f32x4{acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]};
-      }
+          for (int r4 = 0; r4 < 4; ++r4)
+            red[(((h * DT + dt) * 4 + wave) * 4 + r4) * 64] = f32x4{acc[4 * r4], acc[4 * r4 + 1], acc[4 * r4 + 2], acc[4 * r4 + 3]};
+        }
+    }
     __syncthreads();
     uint16_t* out = static_cast<uint16_t*>(pass ? a.dV : a.dK) + bh * g.L * g.d;
     const float scale = pass ? 1.f : a.sm_scale;
-    for (int t = wave * NT / 4; t < (wave + 1) * NT / 4; ++t) {
-      const int key = 32 * (t / DT) + col;
-      if (key >= g.Bk) continue;
-      const int64_t tok = origin + intra_offset(g, key);
+    auto put = [&](auto N) {
+      constexpr int n = decltype(N)::value;
+      for (int t = wave * NT / 4; t < (wave + 1) * NT / 4; ++t) {
+        const int key = 32 * (t / DT) + col;
+        if (key >= g.Bk) continue;
+        const int64_t tok = origin + intra_offset(g, key);
 #pragma unroll
-      for (int r4 = 0; r4 < 4; ++r4) {
-        f32x4 v = red[(t * 16 + r4) * 64];
+        for (int r4 = 0; r4 < 4; ++r4) {
+          f32x4 v = red[(t * 16 + r4) * 64];
 #pragma unroll
-        for (int w = 1; w < 4; ++w) v += red[(t * 16 + 4 * w + r4) * 64];
-        const int ch = 32 * (t % DT) + 8 * r4 + 4 * grp;
-        u32x2 o;
-        o.x = pack_bf16(v[0] * scale, v[1] * scale);
-        o.y = pack_bf16(v[2] * scale, v[3] * scale);
-        if (ch < g.d) *reinterpret_cast<u32x2*>(out + tok * g.d + ch) = o;
+          for (int w = 1; w < n; ++w) v += red[(t * 16 + 4 * w + r4) * 64];
+          const int ch = 32 * (t % DT) + 8 * r4 + 4 * grp;
+          u32x2 o;
+          o.x = pack_bf16(v[0] * scale, v[1] * scale);
+          o.y = pack_bf16(v[2] * scale, v[3] * scale);
+          if (ch < g.d) *reinterpret_cast<u32x2*>(out + tok * g.d + ch) = o;
+        }
       }
-    }
+    };
+    if (items > 2) put(std::integral_constant<int, 4>{});
+    else put(std::integral_constant<int, 2>{});
   }
 }
 
