@@ -28,25 +28,33 @@ PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA peak
 PEAK_HBM_GBS = 8000.0
 
 
-def measured_traffic_bytes(workload: str, kernel: str):
-    """Bytes per launch between L2 and the memory side of `kernel`, read from the table that the
-    rocprofv3 --pmc passes (FETCH_SIZE, WRITE_SIZE, scaled by a 1 GiB copy's readings) left in
-    profiles/bench_<workload>.md; None when there is no such profile.  Hardware counters cannot
-    be read from inside this process, so the committed summary is the source."""
+def kernel_instances(d: int, n_keep: int) -> dict:
+    """The template instances that the sparse attention calls of a bf16 layer launch, by kernel: main
+    launches only, as a profiler prints them.  tests/test_bench_host.py holds them to the built library."""
+    b = lambda v: "true" if v else "false"
+    split, pack = n_keep > 32, n_keep <= 16
+    return {"fwd_pipe_kernel": f"<{d}, {b(split)}, false, {b(pack)}>",
+            "bwd_dq_pipe_kernel": f"<{d}, {b(split)}, false, {b(pack)}>",
+            "bwd_dkv_pipe_kernel": f"<{d}, {d}, 2, {b(pack)}>"}
+
+
+def measured_traffic_bytes(workload: str, kernel: str, root: str = ROOT):
+    """Bytes per launch between L2 and the memory side of `kernel` (name and template arguments), read
+    from the table that the rocprofv3 --pmc passes (FETCH_SIZE, WRITE_SIZE, scaled by a 1 GiB copy's
+    readings) left in profiles/bench_<workload>.md; None when there is no such profile, or it is one of
+    another kernel.  Hardware counters cannot be read from inside this process, so the committed
+    summary is the source."""
     import re
 
-    path = os.path.join(ROOT, "profiles", f"bench_{workload}.md")
+    path = os.path.join(root, "profiles", f"bench_{workload}.md")
     try:
         text = open(path).read()
     except OSError:
         return None
     if "## Traffic" not in text:
         return None
-    best = None
-    for m in re.finditer(r"^\| `bsa::" + re.escape(kernel) + r"<[^`]*` \| ([0-9.]+) \| ([0-9.]+) \|$", text.split("## Traffic", 1)[1], re.M):
-        tot = (float(m.group(1)) + float(m.group(2))) * 1e6
-        best = tot if best is None else max(best, tot)  # the main launch, not its small combine launch
-    return best
+    m = re.search(r"^\| `bsa::" + re.escape(kernel) + r"` \| ([0-9.]+) \| ([0-9.]+) \|$", text.split("## Traffic", 1)[1], re.M)
+    return (float(m.group(1)) + float(m.group(2))) * 1e6 if m else None
 
 
 def parse():
@@ -311,6 +319,7 @@ def measure(wl, steps, warmup, torch, B, traffic=True):
     # forward 4 (QK^T, PV); dK/dV kernel 8 (S, dP, dV, dK); dQ kernel 2 (its S/dP recompute is not credited)
     kernels = {"fwd_pipe_kernel": ("attn_fwd", 4), "bwd_dkv_pipe_kernel": ("bwd_dkv", 8), "bwd_dq_pipe_kernel": ("bwd_dq", 2)}
     dominant = max(kernels, key=lambda k: parts[kernels[k][0]])
+    instances = kernel_instances(wl.d, nk)
 
     # second denominator: what a register-resident MFMA loop sustains on this GPU (two workgroups per CU)
     sink = torch.empty(512 * 256, dtype=torch.float32, device=dev)
@@ -328,7 +337,7 @@ def measure(wl, steps, warmup, torch, B, traffic=True):
         tf = mult * pair_flops / (parts[call] * 1e-3) / 1e12
         return {"kernel": kname, "bound": "mfma", "achieved": tf, "peak": PEAK_BF16_TFLOPS, "unit": "TFLOP/s",
                 "frac": tf / PEAK_BF16_TFLOPS, "frac_of_measured_mfma_loop": tf / probe_tflops,
-                "traffic": measured_traffic_bytes(wl.name, kname) if traffic else None, "avg_launch_ms": parts[call],
+                "traffic": measured_traffic_bytes(wl.name, kname + instances[kname]) if traffic else None, "avg_launch_ms": parts[call],
                 "algorithmic_flops_per_launch": mult * pair_flops}
 
     out = {
