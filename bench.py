@@ -35,7 +35,7 @@ def kernel_instances(d: int, n_keep: int) -> dict:
     split, pack = n_keep > 32, n_keep <= 16
     return {"fwd_pipe_kernel": f"<{d}, {b(split)}, false, {b(pack)}>",
             "bwd_dq_pipe_kernel": f"<{d}, {b(split)}, false, {b(pack)}>",
-            "bwd_dkv_pipe_kernel": f"<{d}, {d}, 2, {b(pack)}>"}
+            "bwd_dkv_pipe_kernel": f"<{d}, {b(pack)}>"}
 
 
 def measured_traffic_bytes(workload: str, kernel: str, root: str = ROOT):

@@ -45,21 +45,15 @@ __device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b) {
 __device__ inline void mfma_next(f32x16& d, bf16x8 a, bf16x8 b) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
 }
-template <bool GAP>
 __device__ inline void mfma_next(f32x16& d, bf16x8 a, bf16x8 b, f32x16& done) {
-  if (GAP) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0\n\ts_nop 7" : "+v"(d), "+v"(done) : "v"(a), "v"(b));
-  else asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0" : "+v"(d), "+v"(done) : "v"(a), "v"(b));
+  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0" : "+v"(d), "+v"(done) : "v"(a), "v"(b));
 }
 template <bool FRESH>  // B was written by vector instructions not long ago
 __device__ inline void mfma_acc(f32x16& d, bf16x8 a, bf16x8 b) {
   if (FRESH) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
   else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
 }
-template <bool GAP>
-__device__ inline void order_behind(f32x16& done) {
-  if (GAP) asm volatile("s_nop 7" : "+v"(done));
-  else asm volatile("" : "+v"(done));
-}
+__device__ inline void order_behind(f32x16& done) { asm volatile("" : "+v"(done)); }
 
 // the fragments of bsa_mfma.h addressed by LDS byte offsets, so that constants fold into the
 // instruction's offset field
@@ -107,15 +101,15 @@ __device__ inline void static_for(F f) {
 
 constexpr int kListCap = 8192;  // blocks per head at most
 
-// D: channels of a record row (64 or 128), DC: channels that are multiplied (d rounded up to 32),
-// NH: 32-key halves of a KV block, PACK: a record holds two query blocks of at most 16 rows.
-template <int D, int DC, int NH, bool PACK>
+// D: channels (64 or 128), PACK: a record holds two query blocks of at most 16 rows.
+template <int D, bool PACK>
 __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a) {
   using R = BwdRec<D>;
-  constexpr int RB = D * 2, DT = DC / 32, DS = DC / 16, NT = NH * DT;
+  constexpr int NH = PBK / 32;  // 32-key halves of the KV block
+  constexpr int RB = D * 2, DT = D / 32, DS = D / 16, NT = NH * DT;
   constexpr int ND = 32 * RB / 1024;        // DMA instructions of a record's Q (or G) rows
   constexpr int NF = 2 * DS + 4 * DT;       // fragments of a record in order of use
-  constexpr int RING = DT == 2 ? 2 : 4;     // fragments read ahead (64 NH / 2 cycles each)
+  constexpr int RING = DT == 2 ? 2 : 4;     // fragments read ahead (64 cycles each)
   static_assert(NF % RING == 0 && 2 * DT - RING >= 2, "the ring wraps into the next record");
   static_assert(8 * R::BYTES >= NT * 16 * 1024, "the record ring doubles as the reduction buffer");
   extern __shared__ __align__(16) uint8_t smem[];  // [4 wavefronts][2 records] | list
@@ -130,23 +124,21 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
   const int j = unit % g.N;
   const int nqt = a.n_keep > 32 ? 2 : 1;                       // records per query block
   const int nrec = PACK ? (g.N + 1) / 2 : g.N * nqt;           // records of a head
-  const uint16_t* Kh = static_cast<const uint16_t*>(a.K) + bh * g.L * g.d;
-  const uint16_t* Vh = static_cast<const uint16_t*>(a.V) + bh * g.L * g.d;
+  const uint16_t* Kh = static_cast<const uint16_t*>(a.K) + bh * g.L * D;
+  const uint16_t* Vh = static_cast<const uint16_t*>(a.V) + bh * g.L * D;
   const uint8_t* ws = static_cast<const uint8_t*>(a.ws) + bh * nrec * (int64_t)R::BYTES;
 
-  // K and V fragments (B operands): lane (col, grp) holds channels 16 s + 8 grp .. +7 of key 32 h + col;
-  // channels and keys past the end repeat earlier ones (met by zero record channels, not stored).
+  // K and V fragments (B operands): lane (col, grp) holds channels 16 s + 8 grp .. +7 of key 32 h + col.
   // Requested ahead of the list, whose loads they overlap.
   bf16x8 kf[NH][DS], vf[NH][DS];
   const int origin = block_origin(g, j);
 #pragma unroll
   for (int h = 0; h < NH; ++h) {
-    const int64_t tok = origin + intra_offset(g, min(32 * h + col, g.Bk - 1));
+    const int64_t first = (origin + intra_offset(g, 32 * h + col)) * (int64_t)D + 8 * grp;
 #pragma unroll
     for (int s = 0; s < DS; ++s) {
-      const int ch = 16 * s + 8 * grp, c = ch < g.d ? ch : 0;
-      kf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Kh + tok * g.d + c));
-      vf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Vh + tok * g.d + c));
+      kf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Kh + first + 16 * s));
+      vf[h][s] = as_frag(*reinterpret_cast<const u32x4*>(Vh + first + 16 * s));
     }
   }
 
@@ -267,7 +259,6 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
     wait_vm<ND>();  // the first record has landed
     static_for<0, RING>([&](auto F) { fr[decltype(F)::value] = frag(F); });
     BSA_FENCE();
-    constexpr bool GAP = NH == 1;  // one key half: half the distance between an MFMA and its consumers
     for (int i = 0; i < mine; ++i) {
       const int e2v = entry(i + 2);
       const uint32_t other = cur + flip;
@@ -319,7 +310,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
         }
 #pragma unroll
         for (int h = 0; h < NH; ++h) {
-          if (k == 0) mfma_next<GAP>(dp[h], fr[F % RING], vf[h][k], s[h]);
+          if (k == 0) mfma_next(dp[h], fr[F % RING], vf[h][k], s[h]);
           else mfma_next(dp[h], fr[F % RING], vf[h][k]);
 #pragma unroll
           for (int r = ra; r < rz; ++r) s[h][r] = __builtin_amdgcn_exp2f(__builtin_fmaf(s[h][r], c2, -lse[r - ra]));
@@ -338,7 +329,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
         static_for<0, NH>([&](auto HH) {
           constexpr int h = decltype(HH)::value;
           mfma_acc<h == 0 && v % DT == 0>(dv[h][dt], fr[F % RING], pf[h][v / DT]);
-          if (v == 0) order_behind<GAP>(dp[h]);
+          if (v == 0) order_behind(dp[h]);
 #pragma unroll
           for (int r = ra; r < rz; ++r) dp[h][r] = s[h][r] * dp[h][r];
         });
@@ -419,13 +410,12 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
         }
     }
     __syncthreads();
-    uint16_t* out = static_cast<uint16_t*>(pass ? a.dV : a.dK) + bh * g.L * g.d;
+    uint16_t* out = static_cast<uint16_t*>(pass ? a.dV : a.dK) + bh * g.L * D;
     const float scale = pass ? 1.f : a.sm_scale;
     auto put = [&](auto N) {
       constexpr int n = decltype(N)::value;
       for (int t = wave * NT / 4; t < (wave + 1) * NT / 4; ++t) {
         const int key = 32 * (t / DT) + col;
-        if (key >= g.Bk) continue;
         const int64_t tok = origin + intra_offset(g, key);
 #pragma unroll
         for (int r4 = 0; r4 < 4; ++r4) {
@@ -436,7 +426,7 @@ __global__ __launch_bounds__(256, 1) void bwd_dkv_pipe_kernel(Geom g, AttnArgs a
           u32x2 o;
           o.x = pack_bf16(v[0] * scale, v[1] * scale);
           o.y = pack_bf16(v[2] * scale, v[3] * scale);
-          if (ch < g.d) *reinterpret_cast<u32x2*>(out + tok * g.d + ch) = o;
+          *reinterpret_cast<u32x2*>(out + tok * D + ch) = o;
         }
       }
     };
@@ -450,21 +440,21 @@ static size_t lds_bytes(const Geom& g) { return (size_t)8 * BwdRec<D>::BYTES + (
 
 template <int D, bool PACK>
 static int launch_t(const Geom& g, const AttnArgs& a, hipStream_t st) {
-  hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, D, 2, PACK>), dim3((g.rows + 7) / 8 * 8), dim3(256), lds_bytes<D>(g), st, g, a);
+  hipLaunchKernelGGL((bwd_dkv_pipe_kernel<D, PACK>), dim3((g.rows + 7) / 8 * 8), dim3(256), lds_bytes<D>(g), st, g, a);
   return check_launch();
 }
 
 // the dynamic LDS of the launch below, for the caller to take ahead of every launch of the backward
 int grant_bwd_dkv_pipe(const Geom& g, const AttnArgs& a) {
-  if (g.d > 64)
-    return a.pack ? allow_dynamic_lds<bwd_dkv_pipe_kernel<128, 128, 2, true>>(lds_bytes<128>(g))
-                  : allow_dynamic_lds<bwd_dkv_pipe_kernel<128, 128, 2, false>>(lds_bytes<128>(g));
-  return a.pack ? allow_dynamic_lds<bwd_dkv_pipe_kernel<64, 64, 2, true>>(lds_bytes<64>(g))
-                : allow_dynamic_lds<bwd_dkv_pipe_kernel<64, 64, 2, false>>(lds_bytes<64>(g));
+  if (g.d == 128)
+    return a.pack ? allow_dynamic_lds<bwd_dkv_pipe_kernel<128, true>>(lds_bytes<128>(g))
+                  : allow_dynamic_lds<bwd_dkv_pipe_kernel<128, false>>(lds_bytes<128>(g));
+  return a.pack ? allow_dynamic_lds<bwd_dkv_pipe_kernel<64, true>>(lds_bytes<64>(g))
+                : allow_dynamic_lds<bwd_dkv_pipe_kernel<64, false>>(lds_bytes<64>(g));
 }
 
 int launch_bwd_dkv_pipe(const Geom& g, const AttnArgs& a, hipStream_t st) {
-  if (g.d > 64) return a.pack ? launch_t<128, true>(g, a, st) : launch_t<128, false>(g, a, st);
+  if (g.d == 128) return a.pack ? launch_t<128, true>(g, a, st) : launch_t<128, false>(g, a, st);
   return a.pack ? launch_t<64, true>(g, a, st) : launch_t<64, false>(g, a, st);
 }
 

@@ -140,7 +140,7 @@ struct AttnArgs {
   int pack;  // backward records hold two query blocks of at most 16 retained queries each
 };
 
-// plain-ALU fp32-accumulate kernels: any supported shape, fp32 or bf16 storage
+// matrix-core kernels at fp32 precision: any supported shape, fp32 or bf16 storage
 int launch_fwd_generic(const Geom& g, int dtype, const AttnArgs& a, hipStream_t st);
 int launch_bwd_generic(const Geom& g, int dtype, const AttnArgs& a, hipStream_t st);
 size_t bwd_workspace_generic(const Geom& g, int n_keep);

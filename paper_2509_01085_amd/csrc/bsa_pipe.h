@@ -100,12 +100,6 @@ struct WalkN {
     --left;
     return word * 32 + b;
   }
-  __device__ inline int next(bool& mine) {
-    uint32_t m = 0;
-    const int r = next(m);
-    mine = m != 0;
-    return r;
-  }
   // restrict a fresh walk to segment `seg` of `nseg` equal parts of the union
   __device__ inline void restrict_to(int seg, int nseg) {
     int total = 0;

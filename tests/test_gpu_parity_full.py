@@ -41,12 +41,11 @@ def _sample(rng, n, k, always=()):
     return sorted(picks)
 
 
-# ---- which units the launches split (the host-side launch plan of the MFMA kernels, restated) ----
+# ---- which units the forward and dQ launches split (their host-side launch plan, restated) ----
 # A launch covers `units` units; XCD x owns the contiguous range [x*q + min(x, r), ...) of q or
 # q + 1 units (q, r = divmod(units, 8)) and walks the last n of it in four segments that a
-# combine launch merges.  Forward and dQ: unit = a group of 4 query blocks (8 when n_keep <= 16),
+# combine launch merges.  A unit is a group of 4 query blocks (8 when n_keep <= 16),
 # n = ceil(q / 5) when q >= 5 and the launch is shorter than 12 rounds of the chip's slots.
-# dK/dV: unit = a pair of KV blocks, n = min(q mod 32 + 8, q / 2) when 4 <= q < 2048.
 def _split_units(units, n):
     q, r = divmod(units, 8)
     out = []
@@ -66,16 +65,6 @@ def split_query_blocks(N, BH, n_keep, h):
     if not (q >= 5 and units < 12 * slots):
         return []
     return [(u % groups) * pg for u in _split_units(units, (q + 4) // 5) if u // groups == h]
-
-
-def split_kv_blocks(N, BH, h):
-    """KV blocks of head h (B = 1) that belong to a pair whose dK/dV walk is split, or []."""
-    pairs = -(-N // 2)
-    units = pairs * BH
-    q = units // 8
-    if not (4 <= q < 64 * 32):
-        return []
-    return [(u % pairs) * 2 for u in _split_units(units, min(q % 32 + 8, q // 2)) if u // pairs == h]
 
 
 @pytest.mark.parametrize("name", list(PLAN))
@@ -125,14 +114,13 @@ def test_full_size_parity(name):
                                sigma={"dQ": sg["dQ"][sel]} if wl.dtype == "bf16" else None, lse=(gL, rL[sel]))
         U.progress(f"[{name}] head {h}: query blocks {qb}: {figs}")
         # ---- dK, dV on sampled KV blocks: the longest k2q list within the cost cap, the shortest
-        # non-empty one, and a KV block whose walk the dK/dV launch splits
+        # non-empty one, and one that the four wavefronts of a workgroup share unevenly
         klens = np.diff(ix.k2q_ptr)
         cap = MAX_LISTERS[name]
         listed = [int(j) for j in np.argsort(klens, kind="stable") if klens[j] > 0]
         order = [j for j in listed if klens[j] <= cap] or listed[:1]  # (every list beyond the cap: the shortest one)
         kb = [order[-1], order[0]][:max(n_kb, 1)]
-        split = sorted(split_kv_blocks(part.N, wl.H, h), key=lambda j: klens[j])
-        kb += [j for j in split if klens[j] > 0][:1]
+        kb += [j for j in order if klens[j] % 4][:1]
         for j in sorted(set(kb)):
             # the stored O the backward reads, for every query block that lists j
             need = [int(i) for i in ix.k2q_idx[ix.k2q_ptr[j]:ix.k2q_ptr[j + 1]]]
