@@ -28,29 +28,39 @@ SHAPES = {
     "bk64_bf16_d48": ("bf16", 48, (4, 8, 12), (4, 4, 4), 0.5, (2, 2, 2)),
     "bk64_bf16_d152": ("bf16", 152, (4, 8, 8), (4, 4, 4), 0.3, (0, 0, 0)),
     "bk24_bf16_d200": ("bf16", 200, (4, 6, 12), (2, 3, 4), 0.5, (0, 0, 0)),
-    "bk70_bf16_d40": ("bf16", 40, (2, 10, 14), (2, 5, 7), 0.5, (0, 0, 0)),     # a step of 64 keys and one of six
+    "bk70_bf16_d40": ("bf16", 40, (2, 10, 14), (2, 5, 7), 0.5, (0, 0, 0)),     # steps of 48 and 22 keys
     "bk128_bf16_d256": ("bf16", 256, (4, 8, 16), (4, 4, 8), 0.3, (0, 0, 0)),
     "bk256_f32_d128": ("fp32", 128, (4, 8, 16), (4, 8, 8), 0.3, (0, 0, 0)),
 }
 
+# Enough blocks that a dK/dV workgroup takes several 16-key tiles: name: (heads, tiles a workgroup, shape as above)
+MANY = {
+    "2_of_2_f32_d72": (64, 2, ("fp32", 72, (4, 6, 10), (2, 3, 5), 0.5, (0, 0, 0))),        # 30 keys
+    "2_of_2_bf16_d80": (64, 2, ("bf16", 80, (4, 6, 8), (2, 3, 4), 0.9, (0, 0, 0))),        # 24 keys
+    "4_of_3_f32_d64": (64, 4, ("fp32", 64, (6, 6, 10), (3, 3, 5), 0.4, (0, 0, 0))),        # 45 keys: a wavefront without a tile
+    "4_of_3_bf16_d104": (64, 4, ("bf16", 104, (6, 6, 10), (3, 3, 5), 0.4, (0, 0, 0))),
+    "4_of_5_f32_d128": (32, 4, ("fp32", 128, (4, 10, 14), (2, 5, 7), 0.5, (0, 0, 0))),     # 70 keys: forward steps of 64 and 6
+    "4_of_5_bf16_d128": (32, 4, ("bf16", 128, (4, 10, 14), (2, 5, 7), 0.3, (0, 0, 0))),
+    "2_of_3_f32_d136": (32, 2, ("fp32", 136, (6, 6, 10), (3, 3, 5), 0.5, (0, 0, 0))),
+    "2_of_5_bf16_d200": (22, 2, ("bf16", 200, (4, 10, 14), (2, 5, 7), 0.5, (0, 0, 0))),
+}
 
-def _run(wl):
-    x = U.device_inputs(wl)
+
+def _run(wl, heads=None):
+    x = U.device_inputs(wl, heads=heads)
     shp, _, _, lists, keep = U.run_indices(wl, x)
     O, LSE = B.attn_fwd(shp, x["Q"], x["K"], x["V"], lists, keep)
     return x, shp, lists, keep, O, LSE
 
 
-@pytest.mark.parametrize("name", list(SHAPES))
-def test_block_shape(name):
-    U.progress(f"block shape {name}")
-    dtype, d, grid, block, keep_ratio, window = SHAPES[name]
-    wl = Workload("shape_" + name, 1, 2, d, dtype, grid, block, threshold=0.7, keep_ratio=keep_ratio, window=window)
-    x, shp, lists, keep, O, LSE = _run(wl)
+def _check_shape(name, shape, H, heads):
+    dtype, d, grid, block, keep_ratio, window = shape
+    wl = Workload("shape_" + name, 1, H, d, dtype, grid, block, threshold=0.7, keep_ratio=keep_ratio, window=window)
+    x, shp, lists, keep, O, LSE = _run(wl, heads)
     dQ, dK, dV = B.attn_bwd(shp, x["Q"], x["K"], x["V"], O, LSE, x["dO"], lists, keep)
     torch.cuda.synchronize()
     part = U.part_of(wl)
-    for h in range(wl.H):
+    for h in heads:
         xi = head_inputs(wl, 0, h)
         ix, rO, rL, rdQ, rdK, rdV = o.bsa_head(xi["Q"], xi["K"], xi["V"], xi["dO"], part, wl.threshold, wl.keep_ratio,
                                                o_storage=U.o_storage_of(wl))
@@ -59,6 +69,22 @@ def test_block_shape(name):
         U.check_tensors(name, f"h{h}", dtype, [(t, U.host_f64(got[0, h]), ref) for t, got, ref in
                                                (("O", O, rO), ("dQ", dQ, rdQ), ("dK", dK, rdK), ("dV", dV, rdV))],
                         sigma=sg, lse=(U.host_f64(LSE[0, h]), rL))
+    return shp
+
+
+@pytest.mark.parametrize("name", list(SHAPES))
+def test_block_shape(name):
+    U.progress(f"block shape {name}")
+    _check_shape(name, SHAPES[name], 2, (0, 1))
+
+
+@pytest.mark.parametrize("name", list(MANY))
+def test_block_shape_many_blocks(name):
+    U.progress(f"many blocks {name}")
+    H, tiles, shape = MANY[name]
+    shp = _check_shape("many_" + name, shape, H, (0, H // 2, H - 1))
+    nkt = (shp.Bk + 15) // 16
+    assert shp.rows * -(-nkt // tiles) >= 512 and nkt > tiles // 2  # the rule of the launch, restated
 
 
 @pytest.mark.parametrize("name,value,token", [("bk30_bf16_d80", float("inf"), 7), ("bk60_bf16_d128", float("-inf"), 7),
@@ -190,3 +216,42 @@ def test_transposed_lists_are_sets(keep_ratio):
     other = B.KvLists(lists.q2k_ptr, lists.q2k_idx, i32(ptr), i32(np.concatenate(idx)), lists.nnz, lists.workspace)
     for a, b in zip(run(other), want):
         assert torch.equal(a, b)
+
+
+# name: (d, grid, block, keep ratio)
+ROUNDING = {
+    "24_keys_d72": (72, (6, 9, 16), (2, 3, 4), 0.5),
+    "24_keys_d200": (200, (4, 9, 12), (2, 3, 4), 0.5),
+    "30_keys_d80": (80, (6, 8, 15), (3, 2, 5), 0.5),
+    "45_keys_d96": (96, (6, 9, 15), (3, 3, 5), 0.5),
+    "60_keys_d128": (128, (6, 15, 16), (3, 5, 4), 0.5),
+    "64_keys_d152": (152, (8, 12, 12), (4, 4, 4), 0.25),
+    "128_keys_d64": (64, (8, 12, 16), (4, 4, 8), 0.5),
+}
+
+
+@pytest.mark.parametrize("name", list(ROUNDING))
+def test_only_results_are_rounded(name):
+    """bf16 tensors of other shapes: products of bf16 values are exact, and an fp32 operand is the sum of three
+    bf16 parts, so a result is the bf16 rounding of an fp32 sum.  Such a sum is within some 2^-22 RMS of the exact
+    one, and rounds differently only that close to a midpoint of two bf16 values, 2^-8 |x| apart at most: a
+    share of about 2^-13 E[RMS / |x|] of the elements, near 1e-3.  An operand rounded to bf16 moves most."""
+    d, grid, block, keep_ratio = ROUNDING[name]
+    wl = Workload("round_" + name, 1, 1, d, "bf16", grid, block, threshold=0.8, keep_ratio=keep_ratio)
+    x = U.device_inputs(wl)
+    shp, _, _, lists, keep = U.run_indices(wl, x)
+    O, LSE = B.attn_fwd(shp, x["Q"], x["K"], x["V"], lists, keep)
+    xi = head_inputs(wl, 0, 0)
+    _, rO, rL, rdQ, rdK, rdV = o.bsa_head(xi["Q"], xi["K"], xi["V"], xi["dO"], U.part_of(wl), wl.threshold, wl.keep_ratio,
+                                          o_storage=U.o_storage_of(wl))
+    # the backward of the oracle's own stored output and LSE
+    O_in = torch.from_numpy(U.o_storage_of(wl)(rO)).to(torch.bfloat16).cuda()[None, None]
+    dQ, dK, dV = B.attn_bwd(shp, x["Q"], x["K"], x["V"], O_in, torch.from_numpy(rL).float().cuda()[None, None], x["dO"], lists, keep)
+    figs = {"LSE": {"abs": float(f"{np.abs(U.host_f64(LSE[0, 0]) - rL).max():.2e}")}}
+    for n, got, ref in (("O", O, rO), ("dQ", dQ, rdQ), ("dK", dK, rdK), ("dV", dV, rdV)):
+        got = U.host_f64(got[0, 0])
+        rounded = U.host_f64(torch.from_numpy(ref).to(torch.bfloat16))
+        figs[n] = {"differ": float(f"{np.mean(got != rounded):.2e}"), **{k: float(f"{v:.3e}") for k, v in U.T.figures(got, ref).items()}}
+    U.record("round " + name, "h0", figs)
+    assert figs["LSE"]["abs"] <= 1e-5  # logits of some tens: 2^-24 of them, and the sums of up to 1e3 terms
+    assert all(figs[n]["differ"] <= 2e-3 for n in ("O", "dQ", "dK", "dV")), figs
