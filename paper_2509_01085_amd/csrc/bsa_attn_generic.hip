@@ -288,7 +288,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     else row_frags<DS>(qrow, gq, d, q[t]);
   }
   f32x4 o[NQT][DS];
-  float m[NQT], l[NQT];
+  float m[NQT], l[NQT];  // maximum logit ahead of the scaling, sum of 2^(c2 (s - m))
 #pragma unroll
   for (int t = 0; t < NQT; ++t) {
     m[t] = -INFINITY;
@@ -351,9 +351,9 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     load_v(0);
 #pragma unroll
     for (int u = 0; u < NQT; ++u) {
-      const float mtrue = fmaxf(m[u], quad_max(mx[u]) * c2);  // c2 > 0: the maximum commutes with the scaling
-      const float mnew = finite_base(mtrue);
-      const float alpha = __builtin_amdgcn_exp2f(m[u] - mnew);
+      const float mtrue = fmaxf(m[u], quad_max(mx[u]));  // (c2 > 0: the maximum commutes with the scaling)
+      const float mnew = finite_base(mtrue) * c2;
+      const float alpha = __builtin_amdgcn_exp2f(m[u] * c2 - mnew);
       float sum = 0.f;
 #pragma unroll
       for (int st = 0; st < NS; ++st)
@@ -436,11 +436,14 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
 #pragma unroll
     for (int w = 1; w < NWV; ++w) mt = fmaxf(mt, ml[w][u][0][i16]);
     mt = finite_base(mt);
+    const float base = mt * c2;
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) lt += ml[w][u][1][i16] * __builtin_amdgcn_exp2f(ml[w][u][0][i16] - mt);
-    lse[u] = lt > 0.f ? (mt + __builtin_amdgcn_logf(lt)) * kLn2 : -INFINITY;
+    for (int w = 0; w < NWV; ++w) lt += ml[w][u][1][i16] * __builtin_amdgcn_exp2f(ml[w][u][0][i16] * c2 - base);
+    // ln sum = mt sm_scale + ln 2 (log2 lt - what rounding took from base): scaling the exp2-domain sum back by
+    // ln 2 instead would leave the rounding of c2, relative to the whole, in the result
+    lse[u] = lt > 0.f ? __builtin_fmaf(mt, a.sm_scale, (__builtin_amdgcn_logf(lt) - __builtin_fmaf(mt, c2, -base)) * kLn2) : -INFINITY;
     // (no mass: an empty list gives zeros, a list of nothing but -inf logits NaN)
-    const float w = lt > 0.f ? __builtin_amdgcn_exp2f(m[u] - mt) / lt : cnt > 0 ? NAN : 0.f;
+    const float w = lt > 0.f ? __builtin_amdgcn_exp2f(m[u] * c2 - base) / lt : cnt > 0 ? NAN : 0.f;
 #pragma unroll
     for (int c = 0; c < DS; ++c) o[u][c] *= w;
   }

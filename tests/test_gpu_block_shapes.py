@@ -255,3 +255,21 @@ def test_only_results_are_rounded(name):
     U.record("round " + name, "h0", figs)
     assert figs["LSE"]["abs"] <= 1e-5  # logits of some tens: 2^-24 of them, and the sums of up to 1e3 terms
     assert all(figs[n]["differ"] <= 2e-3 for n in ("O", "dQ", "dK", "dV")), figs
+
+
+@pytest.mark.parametrize("d,grid,block", [(72, (6, 9, 16), (2, 3, 4)), (72, (8, 16, 16), (4, 4, 4)), (200, (4, 9, 12), (2, 3, 4))])
+def test_lse_is_as_good_as_its_storage(d, grid, block):
+    """LSE below 16 is stored to 2^-20, an rms error of at most 2^-20 / sqrt(12) = 2.8e-7.  The logarithm (1 ulp of
+    up to 10 in the exp2 domain) and its scaling add 1.9e-7 and 1.4e-7, the logits (products of bf16 values,
+    exact, summed in fp32) less: 3.6e-7 together.  A rounded scale would leave up to 2^-24 of the logits."""
+    wl = Workload(f"lse_d{d}", 1, 1, d, "bf16", grid, block, threshold=0.8, keep_ratio=1.0)
+    x = U.device_inputs(wl)
+    shp, _, _, lists, keep = U.run_indices(wl, x)
+    _, LSE = B.attn_fwd(shp, x["Q"], x["K"], x["V"], lists, keep)
+    ptr, idx = U.head_csr(U.lists_to_host(shp, lists), shp, 0, 0)
+    _, rL = o.attn_fwd(*[U.host_f64(x[n][0, 0]) for n in "QKV"], U.part_of(wl), ptr, idx, keep[0, 0].cpu().numpy(), 1 / sqrt(d))
+    assert 4 < np.median(rL) and rL.max() < 16
+    err = U.host_f64(LSE[0, 0]) - rL
+    figs = {"LSE": {"rms": float(f"{np.sqrt(np.mean(err * err)):.2e}"), "mean": float(f"{err.mean():.2e}")}}
+    U.record(wl.name, f"grid {grid}", figs)
+    assert figs["LSE"]["rms"] <= 4e-7, figs
