@@ -207,14 +207,14 @@ __device__ inline void split3(f32x4 a, f32x4 b, u32x4 (&part)[3]) {
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     float x[2] = {k < 2 ? a[2 * k] : b[2 * k - 4], k < 2 ? a[2 * k + 1] : b[2 * k - 3]};
-    const float least[2] = {fminf(x[0], 0x1p-126f), fminf(x[1], 0x1p-126f)};
+    const float whole[2] = {x[0], x[1]};  // (no rest is larger, so the median below is max(rest, 2^-126), 0 if x is 0)
 #pragma unroll
     for (int n = 0; n < 3; ++n) {
       part[n][k] = halves_hi(__float_as_uint(x[0]), __float_as_uint(x[1]));
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
         const float rest = x[h] - __uint_as_float(__float_as_uint(x[h]) & 0xffff0000u);
-        x[h] = PROB ? fmaxf(rest, least[h]) : copysignf(fmaxf(fabsf(rest), 0.f), x[h]);  // (fmaxf drops a NaN)
+        x[h] = PROB ? __builtin_amdgcn_fmed3f(rest, 0x1p-126f, whole[h]) : copysignf(fmaxf(fabsf(rest), 0.f), x[h]);  // (fmaxf drops a NaN)
       }
     }
   }
