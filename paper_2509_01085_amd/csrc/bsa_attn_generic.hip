@@ -83,10 +83,6 @@ __device__ inline float quad_sum(float v) {
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// What the exponents of a row are taken relative to: its maximum, and 0 while every logit it has met is
-// -inf (a wavefront may begin with masked keys; relative to -inf they would be NaN)
-__device__ inline float finite_base(float m) { return m == -INFINITY ? 0.f : m; }
-
 __device__ inline f32x4 load4(const float* p) { return *reinterpret_cast<const f32x4*>(p); }
 __device__ inline f32x4 load4(const uint16_t* p) {
   const u32x2 v = *reinterpret_cast<const u32x2*>(p);
@@ -287,16 +283,19 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     if constexpr (kBf16) row_frags_bf16<DS>(qrow, gq, d, qb[t]);
     else row_frags<DS>(qrow, gq, d, q[t]);
   }
+  const float c2 = a.sm_scale * kLog2e;
+  // Exponents are taken relative to the largest logit so far, and that starts at a finite value: a wavefront
+  // may begin with masked keys, and relative to -inf they would be NaN
+  constexpr float kLowest = -3.4e38f;
   f32x4 o[NQT][DS];
-  float m[NQT], l[NQT];  // maximum logit ahead of the scaling, sum of 2^(c2 (s - m))
+  float m[NQT], l[NQT];
 #pragma unroll
   for (int t = 0; t < NQT; ++t) {
-    m[t] = -INFINITY;
+    m[t] = kLowest;
     l[t] = 0.f;
 #pragma unroll
     for (int c = 0; c < DS; ++c) o[t][c] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
-  const float c2 = a.sm_scale * kLog2e;
   const int beg = g.dense ? 0 : a.q2k_ptr[row];
   const int cnt = g.dense ? g.N : a.q2k_ptr[row + 1] - beg;
   constexpr int KC = 16 * NS;            // keys per step
@@ -351,9 +350,8 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     load_v(0);
 #pragma unroll
     for (int u = 0; u < NQT; ++u) {
-      const float mtrue = fmaxf(m[u], quad_max(mx[u]));  // (c2 > 0: the maximum commutes with the scaling)
-      const float mnew = finite_base(mtrue) * c2;
-      const float alpha = __builtin_amdgcn_exp2f(m[u] * c2 - mnew);
+      const float mnew = fmaxf(m[u], quad_max(mx[u]) * c2);  // c2 > 0: the maximum commutes with the scaling
+      const float alpha = __builtin_amdgcn_exp2f(m[u] - mnew);
       float sum = 0.f;
 #pragma unroll
       for (int st = 0; st < NS; ++st)
@@ -364,7 +362,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
             sum += s[u][st][r];
           }
       l[u] = l[u] * alpha + sum;  // per lane; the four lanes of a query are summed at the end
-      m[u] = mtrue;
+      m[u] = mnew;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {
 #pragma unroll
         for (int c = 0; c < DS; ++c) o[u][c] *= alpha;
@@ -435,15 +433,15 @@ __global__ __launch_bounds__(64 * NWV, 2) void fwd_generic_kernel(Geom g, AttnAr
     float mt = ml[0][u][0][i16], lt = 0.f;
 #pragma unroll
     for (int w = 1; w < NWV; ++w) mt = fmaxf(mt, ml[w][u][0][i16]);
-    mt = finite_base(mt);
-    const float base = mt * c2;
 #pragma unroll
-    for (int w = 0; w < NWV; ++w) lt += ml[w][u][1][i16] * __builtin_amdgcn_exp2f(ml[w][u][0][i16] * c2 - base);
-    // ln sum = mt sm_scale + ln 2 (log2 lt - what rounding took from base): scaling the exp2-domain sum back by
-    // ln 2 instead would leave the rounding of c2, relative to the whole, in the result
-    lse[u] = lt > 0.f ? __builtin_fmaf(mt, a.sm_scale, (__builtin_amdgcn_logf(lt) - __builtin_fmaf(mt, c2, -base)) * kLn2) : -INFINITY;
+    for (int w = 0; w < NWV; ++w) lt += ml[w][u][1][i16] * __builtin_amdgcn_exp2f(ml[w][u][0][i16] - mt);
+    // ln sum = (mt + log2 lt) sm_scale / c2, sum and quotient to twice fp32: times a rounded ln 2 it would keep
+    // the rounding of c2, relative to the whole
+    const float lg = __builtin_amdgcn_logf(lt), sum = mt + lg, k = a.sm_scale / c2;
+    const float part = sum - mt, rest = ((mt - (sum - part)) + (lg - part)) * k + sum * (__builtin_fmaf(-k, c2, a.sm_scale) / c2);
+    lse[u] = lt > 0.f ? __builtin_fmaf(sum, k, rest) : -INFINITY;
     // (no mass: an empty list gives zeros, a list of nothing but -inf logits NaN)
-    const float w = lt > 0.f ? __builtin_amdgcn_exp2f(m[u] * c2 - base) / lt : cnt > 0 ? NAN : 0.f;
+    const float w = lt > 0.f ? __builtin_amdgcn_exp2f(m[u] - mt) / lt : cnt > 0 ? NAN : 0.f;
 #pragma unroll
     for (int c = 0; c < DS; ++c) o[u][c] *= w;
   }
