@@ -111,14 +111,14 @@ __device__ inline int chan_or0(int ch, int d) { return ch < d ? ch : 0; }
 template <int DS>
 constexpr int kMinD = DS == 2 ? 8 : DS == 4 ? 40 : DS == 5 ? 72 : DS == 6 ? 88 : DS == 8 ? 104 : DS == 12 ? 136 : 200;
 
-// A or B operand of a channel contraction: this lane's row, DS loads of four channels
-template <int DS, typename T>
+// A or B operand of a channel contraction: this lane's row, DS loads of four channels.  FULL: d == 16 DS
+template <int DS, bool FULL = false, typename T>
 __device__ inline void row_frags(const T* row, int g, int d, f32x4 (&f)[DS]) {
 #pragma unroll
   for (int s = 0; s < DS; ++s) {
     const int ch = 16 * s + 4 * g;
     f[s] = load4(row + chan_or0(ch, d));
-    if (16 * s + 16 > kMinD<DS> && ch >= d) f[s] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (!FULL && 16 * s + 16 > kMinD<DS> && ch >= d) f[s] = f32x4{0.f, 0.f, 0.f, 0.f};
   }
 }
 
@@ -561,7 +561,7 @@ __device__ inline void sum_in_order(const f32x4 (&acc)[DS], float* dst_row, int 
 // dQ^T += K^T dS^T.  bf16 tensors: 32 keys a step; G is split once, dS in each step.  A 3,024-token
 // training layer of 24-token blocks (all its launches): 0.444 -> 0.359 ms; dQ's elements that are
 // not the bf16 rounding of the exact result 0.06 -> 0.05 %.
-template <typename T, int DS>
+template <typename T, int DS, bool FULL>
 __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dq_generic_kernel(Geom g, AttnArgs a, GenericWs w) {
   constexpr int LDO = 16 * DS + 4;
   __shared__ __align__(16) float osum[16 * LDO];
@@ -652,8 +652,8 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dq_generic_kern
     } else {
       const int64_t krow = (origin + koff[min(k0 + i16, last)]) * d;
       f32x4 kf[DS], vf[DS];
-      row_frags<DS>(Kh + krow, gq, d, kf);
-      row_frags<DS>(Vh + krow, gq, d, vf);
+      row_frags<DS, FULL>(Kh + krow, gq, d, kf);
+      row_frags<DS, FULL>(Vh + krow, gq, d, vf);
       f32x4 s = {0.f, 0.f, 0.f, 0.f}, dp = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int c = 0; c < DS; ++c)
@@ -691,7 +691,7 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dq_generic_kern
 // 16-slot form); dP and dV have the folded fp32 gradient as an operand, whose split would cost as much
 // here as it saves, and stay on the fp32 one.  A 3,024-token training layer of 24-token blocks: 0.359 ->
 // 0.315 ms; dK's elements that are not the bf16 rounding of the exact result 0.08 -> 0.07 %.
-template <typename T, int DS, int KW>
+template <typename T, int DS, int KW, bool FULL>
 __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_kernel(Geom g, AttnArgs a, GenericWs w) {
   constexpr int LDO = 16 * DS + 4, SP = NWV / KW;
   __shared__ __align__(16) float osum[KW * 16 * LDO];
@@ -737,8 +737,8 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_ker
           for (int x = 0; x < 4; ++x) dp = mfma4(gf[c][x], vf[c][x], dp);
       } else {
         f32x4 qf[DS], gf[DS];
-        row_frags<DS>(Qh + (int64_t)w.tok[e0 + i16] * d, gq, d, qf);
-        row_frags<DS>(w.g + (e0 + i16) * d, gq, d, gf);
+        row_frags<DS, FULL>(Qh + (int64_t)w.tok[e0 + i16] * d, gq, d, qf);
+        row_frags<DS, FULL>(w.g + (e0 + i16) * d, gq, d, gf);
 #pragma unroll
         for (int c = 0; c < DS; ++c)
 #pragma unroll
@@ -831,28 +831,40 @@ static int fwd_t(const Geom& g, const AttnArgs& a, hipStream_t st) {
   return fwd_s<T, DS, 4>(g, a, st);
 }
 
-template <typename T, int DS>
-static int bwd_t(const Geom& g, const AttnArgs& a, hipStream_t st) {
+template <typename T, int DS, bool FULL>
+static int bwd_full(const Geom& g, const AttnArgs& a, hipStream_t st) {
   const GenericWs w = carve(g, a.n_keep, a.ws);
   const int nqt = w.nkp / 16, nkt = (g.Bk + 15) / 16;
   if (a.stages & BSA_BWD_PRE) hipLaunchKernelGGL((bwd_pre_generic_kernel<T>), dim3(g.rows, nqt), dim3(256), 0, st, g, a, w);
-  if (a.stages & BSA_BWD_DQ) hipLaunchKernelGGL((bwd_dq_generic_kernel<T, DS>), dim3(g.rows, nqt), dim3(64 * NWV), 0, st, g, a, w);
+  if (a.stages & BSA_BWD_DQ) hipLaunchKernelGGL((bwd_dq_generic_kernel<T, DS, FULL>), dim3(g.rows, nqt), dim3(64 * NWV), 0, st, g, a, w);
   if (a.stages & BSA_BWD_DKV) {
     // four key tiles a workgroup share the records they stream through the L1 (up to d = 128: their
     // result rows fit 64 KB of LDS); with too few workgroups to fill the chip the list of one tile
-    // is spread over the four wavefronts instead
+    // is spread over the four wavefronts instead.  Several tiles against one, d = 128, r = 0.5, us: fp32,
+    // four tiles a block, 256 rows 79 / 61, 512 rows 120 / 151, 1,024 rows 906 / 1,001 (eight times the pairs);
+    // bf16, two tiles, 256 rows 18 / 17, 512 rows 31 / 35.  The line is not right everywhere: a last group
+    // that is mostly empty (three or five tiles) costs up to a quarter (fp32, five tiles, 1,024 rows 2,163 / 1,746).
     bool four = false;
     if constexpr (DS <= 8) four = (int64_t)g.rows * ((nkt + 3) / 4) >= 512 && nkt > 2;
     if (four) {
       if constexpr (DS <= 8)
-        hipLaunchKernelGGL((bwd_dkv_generic_kernel<T, DS, 4>), dim3(g.rows, (nkt + 3) / 4), dim3(64 * NWV), 0, st, g, a, w);
+        hipLaunchKernelGGL((bwd_dkv_generic_kernel<T, DS, 4, FULL>), dim3(g.rows, (nkt + 3) / 4), dim3(64 * NWV), 0, st, g, a, w);
     }
     else if ((int64_t)g.rows * ((nkt + 1) / 2) >= 512 && nkt > 1)
-      hipLaunchKernelGGL((bwd_dkv_generic_kernel<T, DS, 2>), dim3(g.rows, (nkt + 1) / 2), dim3(64 * NWV), 0, st, g, a, w);
+      hipLaunchKernelGGL((bwd_dkv_generic_kernel<T, DS, 2, FULL>), dim3(g.rows, (nkt + 1) / 2), dim3(64 * NWV), 0, st, g, a, w);
     else
-      hipLaunchKernelGGL((bwd_dkv_generic_kernel<T, DS, 1>), dim3(g.rows, nkt), dim3(64 * NWV), 0, st, g, a, w);
+      hipLaunchKernelGGL((bwd_dkv_generic_kernel<T, DS, 1, FULL>), dim3(g.rows, nkt), dim3(64 * NWV), 0, st, g, a, w);
   }
   return check_launch();
+}
+
+// fp32 has instances without the selects that zero padding channels (dQ at d = 128: 497 -> 478 us, dK/dV at 64:
+// 374 -> 370); the bf16 operands need none in the loops but those of G, which cost nothing there
+template <typename T, int DS>
+static int bwd_t(const Geom& g, const AttnArgs& a, hipStream_t st) {
+  if constexpr (sizeof(T) == 4)
+    if (g.d == 16 * DS) return bwd_full<T, DS, true>(g, a, st);
+  return bwd_full<T, DS, false>(g, a, st);
 }
 
 // the compiled numbers of 16-channel groups; a head dimension takes the next one up
