@@ -26,11 +26,10 @@
 // MFMA operand, 2 wait states: the products whose operand was just converted start with a s_nop.
 //
 // Measured (MI355X, steady state): 33,280 tokens, 12 heads, d = 128, p = 0.9, half of the queries:
-// 3.29 -> 2.64 ms (1,130 TFLOP/s; a hipBLASLt product of random 8192^3 bf16 matrices reaches 1,330 on
-// the same card).  The clock is what gives: 1.9 GHz under this load, 2.3 GHz with the requests taken
-// out (timing only: 2.08 ms at nearly the same cycle count), so bytes moved cost power before they
-// cost cycles.  In cycles the matrix cores are 55 % busy; a lone wavefront issues an MFMA every 38
-// cycles at best, and the exponentials take the rest.
+// 3.29 -> 2.63 ms (1,138 TFLOP/s; a long run of library products of random 8192^3 bf16 matrices reaches
+// 1,410 on the same card).  The matrix cores are busy 55 % of the launch's cycles, which pass at 2.0 GHz;
+// 3.5 GB come from beyond the L2 (86 % hits).  A wavefront issues an instruction in half of its cycles,
+// a vector instruction in a third: what the MFMAs leave free, the exponentials take.
 #include <type_traits>
 
 #include "bsa_pipe.h"

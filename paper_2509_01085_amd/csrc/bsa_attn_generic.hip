@@ -21,7 +21,7 @@
 // 4 g + r), so probabilities never leave their registers.
 //
 // Measured on a 3,072-token, 12-head fp32 layer (d = 128, half of the queries retained): forward
-// 0.36 ms, dQ 0.53, dK/dV 0.75 against 2.50, 4.23 and 15.5 ms of the vector-ALU kernels before.
+// 0.36 ms, dQ 0.48, dK/dV 0.72 against 2.50, 4.23 and 15.5 ms of the vector-ALU kernels before.
 #include <math.h>
 
 #include "bsa_common.h"
@@ -36,7 +36,6 @@ typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8;
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 constexpr float kLog2e = 1.4426950408889634f;
-constexpr float kLn2 = 0.6931471805599453f;
 
 // Backward workspace, one entry per retained row, rows of a block padded to a multiple of 16
 struct GenericWs {
@@ -145,9 +144,10 @@ __device__ inline void col_frags(const T* row, int i, int d, float (&f)[DS]) {
 // of two bf16 values is exact in fp32, so K Q^T takes K and Q as they are.  An fp32 probability is the
 // exact sum of three bf16 parts (24 bits of significand, eight a part, split by truncation), so V^T P^T
 // is three products with V and rounds where the fp32 instruction rounds: in the accumulation.
-// Matrix cycles of 16 x 16 logits at d = 128, forward: 64 + 192 against 2,048.  Forward error against
-// fp64 (24 to 128 keys a block, d = 64 .. 200): LSE at most 1.5e-6 against 1.6e-6 before, O the bf16
-// rounding of the exact result in all but 0.03 % of the elements against 0.06 to 0.1 %.
+// Matrix cycles of 16 x 16 logits at d = 128, forward: 64 + 192 against 2,048.  Error against fp64
+// over seven shapes (24 to 128 keys a block, d = 64 .. 200; test_only_results_are_rounded): an element of O
+// rounds to another bf16 value only within 0.35e-6 RMS of the midpoint, 0.70e-6 on the vector ALUs; LSE has
+// an rms error of 0.32 to 0.35e-6 (0.30 to 0.37e-6).
 // 32,760-token layer of 60-token blocks at inference: 3.90 -> 1.53 ms.
 // Layout: A row i, B column i, k slot (g, t), t = 0..7; D as above.  A and B share the order of k.
 __device__ inline f32x4 mfma32b(u32x4 a, u32x4 b, f32x4 c) {
@@ -559,8 +559,8 @@ __device__ inline void sum_in_order(const f32x4 (&acc)[DS], float* dst_row, int 
 // ------------------------------------------------------------------- backward: dQ
 // As the forward, 16 queries a workgroup: S^T = K Q^T, dP^T = V G^T, dS^T = P^T (dP^T - delta),
 // dQ^T += K^T dS^T.  bf16 tensors: 32 keys a step; G is split once, dS in each step.  A 3,024-token
-// training layer of 24-token blocks (all its launches): 0.444 -> 0.359 ms; dQ's elements that are
-// not the bf16 rounding of the exact result 0.06 -> 0.05 %.
+// training layer of 24-token blocks (all its launches): 0.444 -> 0.359 ms; elements of dQ that are not
+// the bf16 rounding of the exact result 0.016 -> 0.013 % (mean of the seven shapes above).
 template <typename T, int DS, bool FULL>
 __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dq_generic_kernel(Geom g, AttnArgs a, GenericWs w) {
   constexpr int LDO = 16 * DS + 4;
@@ -690,7 +690,7 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dq_generic_kern
 // bf16 tensors: S and dK on the bf16 instruction (dS in three parts, a tile of 16 queries fills its
 // 16-slot form); dP and dV have the folded fp32 gradient as an operand, whose split would cost as much
 // here as it saves, and stay on the fp32 one.  A 3,024-token training layer of 24-token blocks: 0.359 ->
-// 0.315 ms; dK's elements that are not the bf16 rounding of the exact result 0.08 -> 0.07 %.
+// 0.315 ms; elements of dK that are not the bf16 rounding of the exact result 0.049 -> 0.046 %.
 template <typename T, int DS, int KW, bool FULL>
 __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_kernel(Geom g, AttnArgs a, GenericWs w) {
   constexpr int LDO = 16 * DS + 4, SP = NWV / KW;

@@ -1,5 +1,7 @@
 """Host-side checks of bench.py: figures that it reads from committed profiles are those of the kernels
 that the library launches now."""
+import re
+
 import pytest
 
 import bench
@@ -24,3 +26,12 @@ def test_traffic_of_another_instance_is_not_reported(tmp_path):
     assert bench.measured_traffic_bytes("x", "k<128, false>", str(tmp_path)) is None
     assert bench.measured_traffic_bytes("x", "k<9>", str(tmp_path)) is None  # listed, but not under Traffic
     assert bench.measured_traffic_bytes("absent", "k<9>", str(tmp_path)) is None
+
+
+@pytest.mark.parametrize("workload", ["wan1p3b", "hd720p"])
+def test_committed_traffic_tables_hold_no_removed_attention_kernel(workload):
+    text = open(f"{bench.ROOT}/profiles/bench_{workload}.md").read().split("## Traffic", 1)[1]
+    code = open(B._LIB_PATH, "rb").read()
+    for name, args in re.findall(r"^\| `bsa::(\w+)<([^`]*)>`", text, re.M):
+        vals = [{"true": "Lb1E", "false": "Lb0E"}.get(a, f"Li{a}E") for a in args.split(", ")]
+        assert f"{len(name)}{name}I{''.join(vals)}E".encode() in code, f"{name}<{args}>"

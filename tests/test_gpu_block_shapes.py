@@ -234,9 +234,10 @@ ROUNDING = {
 @pytest.mark.parametrize("name", list(ROUNDING))
 def test_only_results_are_rounded(name):
     """bf16 tensors of other shapes: products of bf16 values are exact, and an fp32 operand is the sum of three
-    bf16 parts, so a result is the bf16 rounding of an fp32 sum.  Such a sum is within some 2^-22 RMS of the exact
-    one, and rounds differently only that close to a midpoint of two bf16 values, 2^-8 |x| apart at most: a
-    share of about 2^-13 E[RMS / |x|] of the elements, near 1e-3.  An operand rounded to bf16 moves most."""
+    bf16 parts, so a result is the bf16 rounding of an fp32 sum.  Such a sum meets the fp32 tolerance and rounds
+    differently only that close to a midpoint of two bf16 values ("flip": the farthest such midpoint, in RMS).
+    Most sums are within 2^-20 RMS, which is a share of about 2^-11 E[RMS / |x|] of the elements, near 1e-3
+    ("differ").  An operand rounded to bf16 would move most elements, by up to 2^-9."""
     d, grid, block, keep_ratio = ROUNDING[name]
     wl = Workload("round_" + name, 1, 1, d, "bf16", grid, block, threshold=0.8, keep_ratio=keep_ratio)
     x = U.device_inputs(wl)
@@ -252,10 +253,12 @@ def test_only_results_are_rounded(name):
     for n, got, ref in (("O", O, rO), ("dQ", dQ, rdQ), ("dK", dK, rdK), ("dV", dV, rdV)):
         got = U.host_f64(got[0, 0])
         rounded = U.host_f64(torch.from_numpy(ref).to(torch.bfloat16))
-        figs[n] = {"differ": float(f"{np.mean(got != rounded):.2e}"), **{k: float(f"{v:.3e}") for k, v in U.T.figures(got, ref).items()}}
+        bad = got != rounded
+        flip = np.abs(ref - (got + rounded) / 2)[bad].max(initial=0.0) / np.sqrt(np.mean(ref ** 2))
+        figs[n] = {"differ": float(f"{bad.mean():.2e}"), "flip": float(f"{flip:.2e}"), **{k: float(f"{v:.3e}") for k, v in U.T.figures(got, ref).items()}}
     U.record("round " + name, "h0", figs)
     assert figs["LSE"]["abs"] <= 1e-5  # logits of some tens: 2^-24 of them, and the sums of up to 1e3 terms
-    assert all(figs[n]["differ"] <= 2e-3 for n in ("O", "dQ", "dK", "dV")), figs
+    assert all(figs[n]["differ"] <= 2e-3 and figs[n]["flip"] <= U.T.TOL_F32 for n in ("O", "dQ", "dK", "dV")), figs
 
 
 @pytest.mark.parametrize("d,grid,block", [(72, (6, 9, 16), (2, 3, 4)), (72, (8, 16, 16), (4, 4, 4)), (200, (4, 9, 12), (2, 3, 4))])
