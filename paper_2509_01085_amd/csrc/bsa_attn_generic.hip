@@ -728,7 +728,7 @@ __global__ __launch_bounds__(64 * NWV, DS <= 8 ? 2 : 1) void bwd_dkv_generic_ker
         u32x4 qb[S];
         f32x4 gf[DS];
         row_frags_bf16<DS>(Qh + (int64_t)w.tok[e0 + i16] * d, gq, d, qb);
-        row_frags<DS>(w.g + (e0 + i16) * d, gq, d, gf);
+        row_frags<DS, FULL>(w.g + (e0 + i16) * d, gq, d, gf);
 #pragma unroll
         for (int c = 0; c < S; ++c) s = mfma32b(qb[c], kb[c], s);
 #pragma unroll
@@ -836,7 +836,7 @@ static int bwd_full(const Geom& g, const AttnArgs& a, hipStream_t st) {
   const GenericWs w = carve(g, a.n_keep, a.ws);
   const int nqt = w.nkp / 16, nkt = (g.Bk + 15) / 16;
   if (a.stages & BSA_BWD_PRE) hipLaunchKernelGGL((bwd_pre_generic_kernel<T>), dim3(g.rows, nqt), dim3(256), 0, st, g, a, w);
-  if (a.stages & BSA_BWD_DQ) hipLaunchKernelGGL((bwd_dq_generic_kernel<T, DS, FULL>), dim3(g.rows, nqt), dim3(64 * NWV), 0, st, g, a, w);
+  if (a.stages & BSA_BWD_DQ) hipLaunchKernelGGL((bwd_dq_generic_kernel<T, DS, FULL && sizeof(T) == 4>), dim3(g.rows, nqt), dim3(64 * NWV), 0, st, g, a, w);
   if (a.stages & BSA_BWD_DKV) {
     // four key tiles a workgroup share the records they stream through the L1 (up to d = 128: their
     // result rows fit 64 KB of LDS); with too few workgroups to fill the chip the list of one tile
@@ -858,13 +858,12 @@ static int bwd_full(const Geom& g, const AttnArgs& a, hipStream_t st) {
   return check_launch();
 }
 
-// fp32 has instances without the selects that zero padding channels (dQ at d = 128: 497 -> 478 us, dK/dV at 64:
-// 374 -> 370); the bf16 operands need none in the loops but those of G, which cost nothing there
+// Where d fills its groups there are instances without the selects that zero padding channels: fp32 dQ at d = 128
+// 497 -> 478 us, dK/dV at 64 374 -> 370; bf16 dK/dV (the rows of G; its other operands need none) at d = 96, 45 keys
+// a block, 483 -> 467
 template <typename T, int DS>
 static int bwd_t(const Geom& g, const AttnArgs& a, hipStream_t st) {
-  if constexpr (sizeof(T) == 4)
-    if (g.d == 16 * DS) return bwd_full<T, DS, true>(g, a, st);
-  return bwd_full<T, DS, false>(g, a, st);
+  return g.d == 16 * DS ? bwd_full<T, DS, true>(g, a, st) : bwd_full<T, DS, false>(g, a, st);
 }
 
 // the compiled numbers of 16-channel groups; a head dimension takes the next one up

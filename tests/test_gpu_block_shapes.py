@@ -38,6 +38,7 @@ MANY = {
     "2_of_2_f32_d72": (64, 2, ("fp32", 72, (4, 6, 10), (2, 3, 5), 0.5, (0, 0, 0))),        # 30 keys
     "2_of_2_f32_d64": (64, 2, ("fp32", 64, (4, 6, 10), (2, 3, 5), 1.0, (0, 0, 0))),        # (no padding channels)
     "2_of_2_bf16_d80": (64, 2, ("bf16", 80, (4, 6, 8), (2, 3, 4), 0.9, (0, 0, 0))),        # 24 keys
+    "2_of_2_bf16_d96": (64, 2, ("bf16", 96, (4, 6, 10), (2, 3, 5), 0.5, (0, 0, 0))),       # (no padding channels)
     "4_of_3_f32_d64": (64, 4, ("fp32", 64, (6, 6, 10), (3, 3, 5), 0.4, (0, 0, 0))),        # 45 keys: a wavefront without a tile
     "4_of_3_bf16_d104": (64, 4, ("bf16", 104, (6, 6, 10), (3, 3, 5), 0.4, (0, 0, 0))),
     "4_of_5_f32_d128": (32, 4, ("fp32", 128, (4, 10, 14), (2, 5, 7), 0.5, (0, 0, 0))),     # 70 keys: forward steps of 64 and 6
