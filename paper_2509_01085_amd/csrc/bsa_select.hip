@@ -67,54 +67,85 @@ int static_select_scratch(void** ptr, size_t* bytes) {
 }
 
 // ---------------------------------------------------------------- 1. block logits
-constexpr int TI = 64, TJ = 64, KC = 16;
-// A 64 x 64 tile of scores per workgroup, 4 x 4 per thread (rows i0 + 4 ti .., columns
-// j0 + 4 tj ..): per channel a thread reads 4 + 4 operands from LDS for 16 multiply-adds.
+// A wavefront computes R rows x 64 columns, one column a lane: the K operand of a channel is one LDS read
+// (the tile is staged transposed, the next 32 channels are requested while these are multiplied), the R
+// Q operands are the same for all lanes and come through scalar loads, so for R = 8 sixteen fp64 instructions
+// stand against one LDS read and the fp64 rate bounds it.  A workgroup is 4 R rows.
 // Every output is accumulated over the channels in ascending order, multiply and add rounded
 // separately, whatever the tiling.
-__global__ __launch_bounds__(256) void scores_kernel(Geom g, const double* Qbar, const double* Kbar,
-                                                     double scale, double* S) {
-  __shared__ __align__(16) double qs[KC][TI + 2];  // +2: conflict-free staging stores, rows stay 16-byte aligned
-  __shared__ __align__(16) double ks[KC][TJ + 2];
+// Before, a 64 x 64 tile a workgroup with both operands in LDS and no request ahead.  Microseconds, d = 128, before
+// and now: 12 heads of 48 blocks 32 and 10, 4 of 546 47 and 32, 12 of 364 44 and 32.
+constexpr int TJ = 64, KC = 32;
+typedef double double2_a8 __attribute__((ext_vector_type(2), aligned(8)));  // (rows are only 8-byte aligned)
+
+template <int R>
+__global__ __launch_bounds__(256) void scores_kernel(Geom g, const double* __restrict__ Qbar,
+                                                     const double* __restrict__ Kbar, double scale,
+                                                     double* __restrict__ S) {
+  __shared__ double ks[2][KC][TJ + 1];
+  constexpr int NP = KC * TJ / 2 / 256;  // 16-byte pieces of a stage per thread
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int bh = blockIdx.z;
-  const int i0 = blockIdx.y * TI, j0 = blockIdx.x * TJ;
-  const int tid = threadIdx.x;
-  const int ti = tid / 16, tj = tid % 16;
+  const int i0 = (blockIdx.y * 4 + wave) * R, j0 = blockIdx.x * TJ;
   const double* Qh = Qbar + (int64_t)bh * g.N * g.d;
   const double* Kh = Kbar + (int64_t)bh * g.N * g.d;
-  double acc[4][4] = {};
-  for (int c0 = 0; c0 < g.d; c0 += KC) {
-    __syncthreads();
-    for (int e = tid; e < TI * KC; e += 256) {
-      const int r = e / KC, c = e % KC;
-      qs[c][r] = (i0 + r < g.N && c0 + c < g.d) ? Qh[(int64_t)(i0 + r) * g.d + c0 + c] : 0.0;
+  const double* q[R];  // rows past the last one repeat it and are not stored
+#pragma unroll
+  for (int u = 0; u < R; ++u) q[u] = Qh + (int64_t)min(i0 + u, g.N - 1) * g.d;
+
+  // piece n of a thread: channels 2 sp, 2 sp + 1 of column sc + 16 n
+  const int sp = tid % (KC / 2), sc = tid / (KC / 2);
+  double2_a8 v[NP];
+  auto request = [&](int c0) {  // (d is a multiple of 8; channels past it are not multiplied)
+    const int c = c0 + 2 * sp < g.d ? c0 + 2 * sp : 0;
+#pragma unroll
+    for (int n = 0; n < NP; ++n)
+      v[n] = *reinterpret_cast<const double2_a8*>(Kh + (int64_t)min(j0 + sc + 16 * n, g.N - 1) * g.d + c);
+  };
+  auto stage = [&](int buf) {
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      ks[buf][2 * sp][sc + 16 * n] = v[n].x;
+      ks[buf][2 * sp + 1][sc + 16 * n] = v[n].y;
     }
-    for (int e = tid; e < TJ * KC; e += 256) {
-      const int r = e / KC, c = e % KC;
-      ks[c][r] = (j0 + r < g.N && c0 + c < g.d) ? Kh[(int64_t)(j0 + r) * g.d + c0 + c] : 0.0;
-    }
-    __syncthreads();
+  };
+  double acc[R] = {};
+  request(0);
+  stage(0);
+  __syncthreads();
+  for (int c0 = 0, buf = 0; c0 < g.d; c0 += KC, buf ^= 1) {
+    const bool more = c0 + KC < g.d;
+    if (more) request(c0 + KC);
     const int kc = min(KC, g.d - c0);
-    for (int c = 0; c < kc; ++c) {
-      double q[4], k[4];
+#pragma unroll 2
+    for (int c = 0; c < kc; c += 4) {
+      double qc[R][4];
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
-        q[u] = qs[c][4 * ti + u];
-        k[u] = ks[c][4 * tj + u];
+      for (int u = 0; u < R; ++u)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) qc[u][e] = q[u][c0 + c + e];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const double k = ks[buf][c + e][lane];
+#pragma unroll
+        for (int u = 0; u < R; ++u) acc[u] = __dadd_rn(acc[u], __dmul_rn(qc[u][e], k));
       }
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int u = 0; u < 4; ++u) acc[a][u] = __dadd_rn(acc[a][u], __dmul_rn(q[a], k[u]));
     }
+    if (more) stage(buf ^ 1);  // (its readers passed the barrier of the iteration before)
+    __syncthreads();
   }
+  const int j = j0 + lane;
 #pragma unroll
-  for (int a = 0; a < 4; ++a)
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int i = i0 + 4 * ti + a, j = j0 + 4 * tj + u;
-      if (i < g.N && j < g.N) S[((int64_t)bh * g.N + i) * g.N + j] = __dmul_rn(acc[a][u], scale);
-    }
+  for (int u = 0; u < R; ++u)
+    if (i0 + u < g.N && j < g.N) S[((int64_t)bh * g.N + i0 + u) * g.N + j] = __dmul_rn(acc[u], scale);
+}
+
+template <int R>
+static bool launch_scores(const Geom& g, const double* Qbar, const double* Kbar, double scale, double* S, int64_t least, hipStream_t st) {
+  const dim3 grid((g.N + TJ - 1) / TJ, (g.N + 4 * R - 1) / (4 * R), g.B * g.H);
+  if ((int64_t)grid.x * grid.y * grid.z < least) return false;
+  hipLaunchKernelGGL(scores_kernel<R>, grid, dim3(256), 0, st, g, Qbar, Kbar, scale, S);
+  return true;
 }
 
 // ---------------------------------------------------------------- 2. per-row selection
@@ -498,8 +529,9 @@ int launch_select(const Geom& g, const double* Qbar, const double* Kbar, double 
   const size_t lds = (size_t)g.N * sizeof(unsigned long long);  // <= 64 KB
   if (g.N > 4096)
     if (int rc = allow_dynamic_lds<row_select_kernel<4, 32>>(lds)) return rc;
-  hipLaunchKernelGGL(scores_kernel, dim3((g.N + TJ - 1) / TJ, (g.N + TI - 1) / TI, BH), dim3(256), 0, st,
-                     g, Qbar, Kbar, score_scale, w.scores);
+  // the most rows per wavefront that still leave three workgroups a CU (the four that fit hide the scalar loads)
+  launch_scores<8>(g, Qbar, Kbar, score_scale, w.scores, 768, st) || launch_scores<4>(g, Qbar, Kbar, score_scale, w.scores, 512, st) ||
+      launch_scores<2>(g, Qbar, Kbar, score_scale, w.scores, 0, st);
   if (g.N <= 1024)
     hipLaunchKernelGGL((row_select_kernel<1, 16>), dim3(g.rows), dim3(64), lds, st, g, w.scores, threshold, stat_z, w.mask, w.cnt);
   else if (g.N <= 4096)
