@@ -152,10 +152,13 @@ static bool launch_scores(const Geom& g, const double* Qbar, const double* Kbar,
 // Eq. 4 without a sort.  In the order (score descending, block id ascending) the selected set
 // is a prefix, so it is fixed by the key of its last element.  Scores map to 64-bit integers
 // that order the same way; with G(t) = sum of e_j over keys >= t (non-increasing in t) the
-// last selected key is the largest t with G(t) >= p*Z.  It is found by bisection over the
-// bits of t, keeping the bracket [lo, hi) with G(lo) >= p*Z > G(hi) and the number of keys
-// inside it; the search stops as soon as one key is left (about log2 N steps past the keys'
-// common prefix).  More than one key left after the last bit means equal scores: those are
+// last selected key is the largest t with G(t) >= p*Z.  It is found by bisection, keeping a
+// bracket [lo, hi] with G(lo) >= p*Z > G(hi + 1) and the number of keys inside it, until one key is
+// left.  The first kValueSteps pivots halve the bracket's range of scores, which are spread like the keys
+// of a row are, about log2 N + 2 steps; bits would be bisected through sign and exponent first, which took
+// about twice as many.  After that, and wherever the middle of two scores is no key inside the bracket
+// (infinities), the pivot is the middle key, so the search ends whatever the scores are.
+// More than one key left in a bracket of one value means equal scores: those are
 // taken in ascending block id while the mass is short.  Sums run in a fixed order (per lane
 // ascending, butterfly across lanes, wavefronts in order), so the result is reproducible;
 // it equals the sequential-prefix definition whenever no comparison is within rounding of a
@@ -166,12 +169,60 @@ __device__ inline unsigned long long order_key(double s) {
   return (u >> 63) ? ~u : (u | 0x8000000000000000ull);
 }
 
-__device__ inline double wave_sum(double v) {
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) v = __dadd_rn(v, __shfl_xor(v, m));
-  return v;
+__device__ inline double key_score(unsigned long long key) {  // the score of a key
+  return __longlong_as_double((long long)((key >> 63) ? key ^ 0x8000000000000000ull : ~key));
 }
 
+// The value of lane ^ M where all lanes that differ from this one in higher bits below 64 only hold the same
+// value, that is in a butterfly from 32 down to 1 (a rotation within 16 lanes then reaches the same value as
+// the exchange).  Register exchanges instead of the LDS crossbar: a bisection step is one chain of them.
+template <int M>
+__device__ inline uint32_t butterfly(uint32_t v) {
+  if constexpr (M == 32) {
+    const auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+    return (threadIdx.x & 32) ? r[0] : r[1];
+  } else if constexpr (M == 16) {
+    const auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);
+    return (threadIdx.x & 16) ? r[0] : r[1];
+  } else {  // row_ror:8, row_ror:4, quad_perm [2,3,0,1], quad_perm [1,0,3,2]
+    constexpr int ctrl = M == 8 ? 0x128 : M == 4 ? 0x124 : M == 2 ? 0x4e : 0xb1;
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, ctrl, 0xf, 0xf, true);
+  }
+}
+template <int M>
+__device__ inline unsigned long long butterfly(unsigned long long v) {
+  return ((unsigned long long)butterfly<M>((uint32_t)(v >> 32)) << 32) | butterfly<M>((uint32_t)v);
+}
+template <int M>
+__device__ inline double butterfly(double v) {
+  return __longlong_as_double((long long)butterfly<M>((unsigned long long)__double_as_longlong(v)));
+}
+// the reduction of op over a wavefront in every lane, pairs in the order 32, 16, .., 1
+template <typename T, typename Op>
+__device__ inline T wave_reduce(T v, Op op) {
+  v = op(v, butterfly<32>(v));
+  v = op(v, butterfly<16>(v));
+  v = op(v, butterfly<8>(v));
+  v = op(v, butterfly<4>(v));
+  v = op(v, butterfly<2>(v));
+  return op(v, butterfly<1>(v));
+}
+__device__ inline double wave_sum(double v) {
+  return wave_reduce(v, [](double a, double b) { return __dadd_rn(a, b); });
+}
+__device__ inline double wave_max(double v) {
+  return wave_reduce(v, [](double a, double b) { return fmax(a, b); });
+}
+__device__ inline unsigned long long wave_max_key(unsigned long long v) {
+  return wave_reduce(v, [](unsigned long long a, unsigned long long b) { return a > b ? a : b; });
+}
+
+// A chain of bisection steps bounds it (few rows) or the compares and masked additions of a step (many).
+// Microseconds with bits for pivots, the LDS crossbar, up to 16 elements skipped by branches and four
+// wavefronts a row above 1,024 blocks, and now: 576 rows of 48 blocks 16 and 8, 4,368 of 364 41 and 22,
+// 44,000 of 1,100 1,271 and 276.
+// MAXE: elements per thread, the next of the compiled numbers (elements past the row have the key 0 and no mass).
+constexpr int kValueSteps = 24;
 template <int NW, int MAXE>
 __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const double* S, double p, double zq,
                                                             uint32_t* mask, int32_t* cnt) {
@@ -184,7 +235,6 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
   __shared__ uint32_t bits[256];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const double* s = S + (int64_t)row * g.N;
-  const int ept = (g.N + NT - 1) / NT;  // elements per thread actually used (<= MAXE): j = e*NT + tid
   const int W = (g.N + 31) / 32;
 
   auto block_sum = [&](double v) -> double {  // the same value in every thread
@@ -223,8 +273,7 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
     cs = tc;
   };
   auto block_max = [&](double v) -> double {
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) v = fmax(v, __shfl_xor(v, m));
+    v = wave_max(v);
     if (NW == 1) return v;
     __syncthreads();
     if (lane == 0) red[wave] = v;
@@ -245,14 +294,16 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
   };
 
   double sv[MAXE];
-  double smax = -INFINITY;
+  double smin = INFINITY, smax = -INFINITY;
 #pragma unroll
   for (int e = 0; e < MAXE; ++e) {
     const int j = e * NT + tid;
-    sv[e] = (e < ept && j < g.N) ? s[j] : -INFINITY;
+    sv[e] = j < g.N ? s[j] : -INFINITY;  // element e of a thread: j = e * NT + tid
     smax = fmax(smax, sv[e]);
+    if (j < g.N) smin = fmin(smin, sv[e]);
   }
   smax = block_max(smax);
+  smin = -block_max(-smin);
   for (int k = tid; k < 256; k += NT) bits[k] = 0u;
 
   unsigned long long key[MAXE];
@@ -262,7 +313,7 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
 #pragma unroll
   for (int e = 0; e < MAXE; ++e) {
     const int j = e * NT + tid;
-    const bool live = e < ept && j < g.N;
+    const bool live = j < g.N;
     key[e] = live ? order_key(sv[e]) : 0ull;  // padding: below every real key, no mass
     ev[e] = live ? exp(sv[e] - smax) : 0.0;
     zl = __dadd_rn(zl, ev[e]);
@@ -274,12 +325,8 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
   }
   const double Z = block_sum(zl);
   // smallest and largest key of the row
-#pragma unroll
-  for (int m = 32; m > 0; m >>= 1) {
-    const unsigned long long a = __shfl_xor(kmin, m), b = __shfl_xor(kmax, m);
-    kmin = a < kmin ? a : kmin;
-    kmax = b > kmax ? b : kmax;
-  }
+  kmin = ~wave_max_key(~kmin);
+  kmax = wave_max_key(kmax);
   if (NW > 1) {
     __syncthreads();
     if (lane == 0) { rk[0][wave] = kmin; rk[1][wave] = kmax; }
@@ -294,7 +341,7 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
     int cl = 0;
 #pragma unroll
     for (int e = 0; e < MAXE; ++e)
-      if (e < ept) cl += __popcll(__ballot(equal_only ? key[e] == lo_incl : key[e] >= lo_incl));
+      cl += __popcll(__ballot(equal_only ? key[e] == lo_incl : key[e] >= lo_incl));
     return block_count(cl);
   };
 
@@ -306,43 +353,45 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
   if (p < 1.0) {
     all = false;
     const double target = __dmul_rn(p, Z);
-    const unsigned long long diff = kmin ^ kmax;
-    int b = diff ? 63 - __builtin_clzll(diff) : -1;  // highest bit in which two keys differ
-    unsigned long long lo = b >= 0 ? (kmin >> b >> 1 << 1 << b) : kmin;  // keys' common prefix, lower bits zero
-    int cnt_lo = g.N, cnt_hi = 0;  // keys >= lo; keys >= hi, hi = lo + 2^(b+1)
-    for (; b >= 0 && cnt_lo - cnt_hi > 1; --b) {
-      const unsigned long long cand = lo | (1ull << b);
+    unsigned long long lo = kmin, hi = kmax;
+    double vlo = smin, vhi = smax;  // scores between which the bracket's keys lie
+    int cnt_lo = g.N, cnt_hi = 0;   // keys >= lo; keys > hi
+    for (int step = 0; cnt_lo - cnt_hi > 1 && lo < hi; ++step) {
+      const double mid = 0.5 * vlo + 0.5 * vhi;
+      unsigned long long cand = order_key(mid);
+      if (step >= kValueSteps || !(cand > lo && cand <= hi)) {
+        cand = lo + ((hi - lo) >> 1) + ((hi - lo) & 1ull);
+        step = kValueSteps;  // (the scores no longer say where the bracket is)
+      }
       double gl = 0.0;
       int cl = 0;
 #pragma unroll
       for (int e = 0; e < MAXE; ++e) {
-        if (e < ept) {
-          const bool ge = key[e] >= cand;
-          gl = __dadd_rn(gl, ge ? ev[e] : 0.0);
-          cl += __popcll(__ballot(ge));
-        }
+        const bool ge = key[e] >= cand;
+        gl = __dadd_rn(gl, ge ? ev[e] : 0.0);
+        cl += __popcll(__ballot(ge));
       }
       double G;
       int c;
       block_sum_count(gl, cl, G, c);
       if (G >= target) {
         lo = cand;
+        vlo = mid;
         cnt_lo = c;
       } else {
+        hi = cand - 1;
+        vhi = mid;
         cnt_hi = c;
       }
     }
-    // the keys still inside the bracket [lo, lo + span) are all equal (one key, unless scores tie exactly)
-    const unsigned long long span = b >= 0 ? (1ull << b << 1) : 1ull;  // 0 stands for 2^64
+    // the keys still inside the bracket [lo, hi] are all equal (one key, unless scores tie exactly)
     tie = cnt_lo - cnt_hi > 1;
     if (tie) {  // equal scores: add them one at a time, as the sorted prefix would
       double gl = 0.0, el = 0.0;
 #pragma unroll
       for (int e = 0; e < MAXE; ++e) {
-        if (e < ept) {
-          gl = __dadd_rn(gl, key[e] > lo ? ev[e] : 0.0);
-          if (key[e] == lo) el = ev[e];
-        }
+        gl = __dadd_rn(gl, key[e] > lo ? ev[e] : 0.0);
+        if (key[e] == lo) el = ev[e];
       }
       double c = block_sum(gl);
       el = block_max(el);  // the mass of one tied element (identical in all of them)
@@ -358,12 +407,8 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
     unsigned long long lk = 0ull;
 #pragma unroll
     for (int e = 0; e < MAXE; ++e)
-      if (e < ept && key[e] >= lo && (span == 0ull || key[e] - lo < span) && key[e] > lk) lk = key[e];
-#pragma unroll
-    for (int m = 32; m > 0; m >>= 1) {
-      const unsigned long long o = __shfl_xor(lk, m);
-      lk = o > lk ? o : lk;
-    }
+      if (key[e] >= lo && key[e] <= hi && key[e] > lk) lk = key[e];
+    lk = wave_max_key(lk);
     if (NW > 1) {
       __syncthreads();
       if (lane == 0) rk[0][wave] = lk;
@@ -381,13 +426,13 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
     double sl = 0.0;
 #pragma unroll
     for (int e = 0; e < MAXE; ++e)
-      if (e < ept && e * NT + tid < g.N) sl = __dadd_rn(sl, sv[e]);
+      if (e * NT + tid < g.N) sl = __dadd_rn(sl, key_score(key[e]));
     const double mean = __ddiv_rn(block_sum(sl), (double)g.N);
     double dl = 0.0;
 #pragma unroll
     for (int e = 0; e < MAXE; ++e)
-      if (e < ept && e * NT + tid < g.N) {
-        const double dvn = __dadd_rn(sv[e], -mean);
+      if (e * NT + tid < g.N) {
+        const double dvn = __dadd_rn(key_score(key[e]), -mean);
         dl = __dadd_rn(dl, __dmul_rn(dvn, dvn));
       }
     const double var = g.N > 1 ? __ddiv_rn(block_sum(dl), (double)(g.N - 1)) : 0.0;
@@ -415,7 +460,7 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
 #pragma unroll
     for (int e = 0; e < MAXE; ++e) {
       const int j = e * NT + tid;
-      if (e < ept && j < g.N && (key[e] > last || (!tie && key[e] == last))) atomicOr(&bits[j >> 5], 1u << (j & 31));
+      if (j < g.N && (key[e] > last || (!tie && key[e] == last))) atomicOr(&bits[j >> 5], 1u << (j & 31));
     }
     if (tie && tid == 0) {  // equal scores: ascending block id, one thread (rare)
       int left = need;
@@ -521,6 +566,18 @@ __global__ __launch_bounds__(256) void transpose_kernel(Geom g, const uint32_t* 
   if (!FILL && lane < 32 && col < g.N) kcnt[(int64_t)bh * g.N + col] = acc;
 }
 
+// One wavefront per row up to 1,536 blocks, four (and two barriers a bisection step) above
+template <int NW, int MAXE, int... MORE>
+static void launch_row_select_of(const Geom& g, double p, double zq, const SelectWs& w, hipStream_t st) {
+  if constexpr (sizeof...(MORE) > 0)
+    if (g.N > 64 * NW * MAXE) return launch_row_select_of<NW, MORE...>(g, p, zq, w, st);
+  hipLaunchKernelGGL((row_select_kernel<NW, MAXE>), dim3(g.rows), dim3(64 * NW), g.N * sizeof(unsigned long long), st, g, w.scores, p, zq, w.mask, w.cnt);
+}
+static void launch_row_select(const Geom& g, double p, double zq, const SelectWs& w, hipStream_t st) {
+  if (g.N <= 1536) launch_row_select_of<1, 1, 2, 4, 6, 8, 12, 16, 20, 24>(g, p, zq, w, st);
+  else launch_row_select_of<4, 8, 12, 16, 32>(g, p, zq, w, st);
+}
+
 int launch_select(const Geom& g, const double* Qbar, const double* Kbar, double threshold, double stat_z,
                   double score_scale, int32_t* q2k_ptr, int32_t* q2k_idx, int32_t* k2q_ptr,
                   int32_t* k2q_idx, int64_t* nnz_dev, void* ws, hipStream_t st) {
@@ -532,12 +589,7 @@ int launch_select(const Geom& g, const double* Qbar, const double* Kbar, double 
   // the most rows per wavefront that still leave three workgroups a CU (the four that fit hide the scalar loads)
   launch_scores<8>(g, Qbar, Kbar, score_scale, w.scores, 768, st) || launch_scores<4>(g, Qbar, Kbar, score_scale, w.scores, 512, st) ||
       launch_scores<2>(g, Qbar, Kbar, score_scale, w.scores, 0, st);
-  if (g.N <= 1024)
-    hipLaunchKernelGGL((row_select_kernel<1, 16>), dim3(g.rows), dim3(64), lds, st, g, w.scores, threshold, stat_z, w.mask, w.cnt);
-  else if (g.N <= 4096)
-    hipLaunchKernelGGL((row_select_kernel<4, 16>), dim3(g.rows), dim3(256), lds, st, g, w.scores, threshold, stat_z, w.mask, w.cnt);
-  else
-    hipLaunchKernelGGL((row_select_kernel<4, 32>), dim3(g.rows), dim3(256), lds, st, g, w.scores, threshold, stat_z, w.mask, w.cnt);
+  launch_row_select(g, threshold, stat_z, w, st);
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, w.cnt, g.rows, q2k_ptr, nnz_dev);
   hipLaunchKernelGGL(expand_kernel, dim3((g.rows + 3) / 4), dim3(256), 0, st, g, w.mask, q2k_ptr, q2k_idx);
   if (k2q_ptr) {
