@@ -481,29 +481,55 @@ __global__ __launch_bounds__(64 * NW) void row_select_kernel(Geom g, const doubl
 }
 
 // ---------------------------------------------------------------- 3. exclusive scan
+// One workgroup, 4,096 counts a step: four a thread, a scan of the wavefront by lane shifts, one barrier for
+// the sixteen totals (two sets in turn), the next counts requested ahead.  Bound by the latency of a step.
+// 44,000 counts 72 -> 13 us, 4,368 in one step 5.2 -> 5.0 (each thread summed and wrote a run of its own before).
+typedef int int4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 __global__ __launch_bounds__(1024) void scan_kernel(const int32_t* cnt, int n, int32_t* ptr, int64_t* total) {
-  __shared__ int part[1024];
-  const int tid = threadIdx.x;
-  const int seg = (n + 1023) / 1024;
-  const int a = min(n, tid * seg), b = min(n, a + seg);
-  int s = 0;
-  for (int k = a; k < b; ++k) s += cnt[k];
-  part[tid] = s;
-  __syncthreads();
-  for (int o = 1; o < 1024; o <<= 1) {  // inclusive Hillis-Steele over the 1024 partials
-    const int v = tid >= o ? part[tid - o] : 0;
+  __shared__ int part[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  auto counts = [&](int k) {
+    int4_a4 v = {0, 0, 0, 0};
+    if (k + 4 <= n) return *reinterpret_cast<const int4_a4*>(cnt + k);
+#pragma unroll
+    for (int e = 0; e < 3; ++e)
+      if (k + e < n) v[e] = cnt[k + e];
+    return v;
+  };
+  int carry = 0;
+  int4_a4 next = counts(4 * tid);
+  for (int base = 0, buf = 0; base < n; base += 4096, buf ^= 1) {
+    const int k = base + 4 * tid;
+    const int4_a4 v = next;
+    next = counts(k + 4096);
+    const int own = v.x + v.y + v.z + v.w;
+    int incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if (lane >= o) incl += u;
+    }
+    if (lane == 63) part[buf][wave] = incl;
     __syncthreads();
-    part[tid] += v;
-    __syncthreads();
+    int run = carry + incl - own;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      const int t = part[buf][w];
+      if (w < wave) run += t;
+      carry += t;
+    }
+    const int4_a4 out = {run, run + v.x, run + v.x + v.y, run + v.x + v.y + v.z};
+    if (k + 4 <= n) {
+      *reinterpret_cast<int4_a4*>(ptr + k) = out;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 3; ++e)
+        if (k + e < n) ptr[k + e] = out[e];
+    }
   }
-  int run = part[tid] - s;
-  for (int k = a; k < b; ++k) {
-    ptr[k] = run;
-    run += cnt[k];
-  }
-  if (tid == 1023) {
-    ptr[n] = part[1023];
-    if (total) *total = part[1023];
+  if (tid == 0) {
+    ptr[n] = carry;
+    if (total) *total = carry;
   }
 }
 
@@ -535,35 +561,47 @@ __global__ __launch_bounds__(256) void expand_kernel(Geom g, const uint32_t* mas
 }
 
 // ---------------------------------------------------------------- 5-7. transpose
-// One wavefront per (head, group of 32 KV blocks).  FILL=false counts the listing query
-// blocks of each column; FILL=true writes them, ascending, at k2q_ptr[column].
+// One wavefront per (head, kCols KV blocks).  FILL=false counts the listing query
+// blocks of each column; FILL=true writes them, ascending, at k2q_ptr[column].  A wavefront is one chain over
+// the head's rows, so a few columns each (whole words cost 32 steps a chain and left most SIMDs idle), counts
+// and cursors in scalar registers.
+// A word of 32 columns a wavefront and now, microseconds: 12 heads of 364 blocks count 9.2 and 5.4, fill 17 and 5.5.
+constexpr int kCols = 8;
 template <bool FILL>
 __global__ __launch_bounds__(256) void transpose_kernel(Geom g, const uint32_t* mask, int32_t* kcnt,
                                                         const int32_t* kptr, int32_t* kidx) {
   const int lane = threadIdx.x & 63;
-  const int W = (g.N + 31) / 32;
-  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (unit >= g.B * g.H * W) return;
-  const int bh = unit / W, w = unit % W;
-  const int col = w * 32 + (lane & 31);
-  int acc = 0;  // lane b < 32: running count (or write cursor) of column w*32 + b
-  if (FILL && lane < 32 && col < g.N) acc = kptr[(int64_t)bh * g.N + col];
+  const int W = (g.N + 31) / 32, G = (g.N + kCols - 1) / kCols;  // words of a row, groups of columns
+  const int unit = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (unit >= g.B * g.H * G) return;
+  const int bh = unit / G, c0 = (unit % G) * kCols;
+  const uint32_t* word = mask + (int64_t)bh * g.N * W + c0 / 32;
+  const int shift = c0 % 32;
+  int acc[kCols];  // running count (or write cursor) of column c0 + b, the same in every lane
+#pragma unroll
+  for (int b = 0; b < kCols; ++b) acc[b] = FILL ? kptr[(int64_t)bh * g.N + min(c0 + b, g.N - 1)] : 0;
   const unsigned long long lt = (1ull << lane) - 1ull;
-  for (int i0 = 0; i0 < g.N; i0 += 64) {
+  auto bits = [&](int i0) -> uint32_t {
     const int i = i0 + lane;
-    const uint32_t word = i < g.N ? mask[((int64_t)bh * g.N + i) * W + w] : 0u;
-#pragma unroll 4
-    for (int b = 0; b < 32; ++b) {
-      const bool set = (word >> b) & 1u;
+    return i < g.N ? word[(int64_t)i * W] >> shift : 0u;
+  };
+  uint32_t next = bits(0);
+  for (int i0 = 0; i0 < g.N; i0 += 64) {
+    const uint32_t now = next;
+    next = bits(i0 + 64);
+#pragma unroll
+    for (int b = 0; b < kCols; ++b) {
+      const bool set = (now >> b) & 1u;  // (bits past the last column are zero)
       const unsigned long long m = __ballot(set);
-      if (FILL) {
-        const int cursor = __shfl(acc, b);
-        if (set) kidx[cursor + __popcll(m & lt)] = i;
-      }
-      if (lane == b) acc += __popcll(m);
+      if (FILL && set) kidx[acc[b] + __popcll(m & lt)] = i0 + lane;
+      acc[b] += __popcll(m);
     }
   }
-  if (!FILL && lane < 32 && col < g.N) kcnt[(int64_t)bh * g.N + col] = acc;
+  if (!FILL && lane == 0) {
+#pragma unroll
+    for (int b = 0; b < kCols; ++b)
+      if (c0 + b < g.N) kcnt[(int64_t)bh * g.N + c0 + b] = acc[b];
+  }
 }
 
 // One wavefront per row up to 1,536 blocks, four (and two barriers a bisection step) above
@@ -593,8 +631,7 @@ int launch_select(const Geom& g, const double* Qbar, const double* Kbar, double 
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, w.cnt, g.rows, q2k_ptr, nnz_dev);
   hipLaunchKernelGGL(expand_kernel, dim3((g.rows + 3) / 4), dim3(256), 0, st, g, w.mask, q2k_ptr, q2k_idx);
   if (k2q_ptr) {
-    const int W = (g.N + 31) / 32;
-    const int units = BH * W;
+    const int units = BH * ((g.N + kCols - 1) / kCols);
     hipLaunchKernelGGL(transpose_kernel<false>, dim3((units + 3) / 4), dim3(256), 0, st, g, w.mask, w.kcnt,
                        (const int32_t*)nullptr, (int32_t*)nullptr);
     hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, w.kcnt, g.rows, k2q_ptr, (int64_t*)nullptr);

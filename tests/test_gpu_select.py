@@ -1,6 +1,6 @@
 """GPU parity of bsa_select_kv alone on hand-made pooled inputs: exactly equal scores (the
 tie rule of the minimal prefix: ascending block id), duplicated KV blocks, and block counts
-that exercise every workgroup shape of the selection kernel (one wavefront up to 1024
+that exercise every workgroup shape of the selection kernel (one wavefront up to 1536
 blocks, four wavefronts beyond, up to the 8192-block limit).  CSR and transposed CSR are
 compared bit for bit with the CPU oracle's Eq. 4."""
 from math import sqrt
@@ -88,6 +88,36 @@ def test_block_counts(N, H):
     shp = select_shape(N, H, d)
     Qbar = rng.standard_normal((H, N, d)) * 1.5
     Kbar = rng.standard_normal((H, N, d)) * 1.5
+    host = run(shp, Qbar, Kbar, 0.9)
+    check(shp, host, Qbar, Kbar, 0.9, allow_marginal=True)
+
+
+@pytest.mark.parametrize("N,H,d", [(64, 2, 8), (72, 25, 24), (128, 1, 40), (136, 3, 32), (256, 40, 16), (264, 1, 72), (384, 12, 200),
+                                   (392, 2, 64), (512, 1, 104), (776, 1, 96), (1280, 2, 8), (1288, 1, 16), (1536, 1, 8), (1544, 1, 8),
+                                   (2048, 2, 8), (2056, 2, 8), (3080, 1, 8)])
+def test_edges_of_tiles_and_element_counts(N, H, d):
+    """The last block of a compiled element count and the first of the next, channel counts that leave a
+    remainder of a stage, every number of rows a wavefront computes, and more rows than one scan step takes.
+    Integer vectors: the scores are exact, many of them tie."""
+    U.progress(f"select edges N={N} H={H} d={d}")
+    rng = np.random.default_rng(N + d)
+    shp = select_shape(N, H, d)
+    Qbar, Kbar = rng.integers(-2, 3, (H, N, d)) * 1.0, rng.integers(-2, 3, (H, N, d)) * 0.5
+    host = run(shp, Qbar, Kbar, 0.8)
+    check(shp, host, Qbar, Kbar, 0.8, allow_marginal=True)
+
+
+@pytest.mark.parametrize("N", [8, 200, 1600])
+@pytest.mark.parametrize("big", [1e6, 1e150, 1e300])
+def test_scores_of_very_different_size(N, big):
+    """A few scores far from all others: the middle of two scores separates nothing, then the middle key does."""
+    U.progress(f"select outliers N={N} big={big}")
+    H, d = 2, 8
+    rng = np.random.default_rng(N)
+    shp = select_shape(N, H, d)
+    Qbar, Kbar = np.abs(rng.standard_normal((H, N, d))), rng.standard_normal((H, N, d))
+    Kbar[:, N // 2] = -big
+    Kbar[:, 1] = -big * 1e-3
     host = run(shp, Qbar, Kbar, 0.9)
     check(shp, host, Qbar, Kbar, 0.9, allow_marginal=True)
 
