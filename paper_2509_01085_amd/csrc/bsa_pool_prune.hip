@@ -10,6 +10,8 @@
 // inputs are fp32 or bf16, so every product of two inputs is exact in fp64 and a fused
 // multiply-add rounds exactly like multiply-then-add; cos = dot / sqrt(|a|^2 * |c|^2) uses
 // IEEE fp64 multiply, sqrt and divide.
+#include <math.h>
+
 #include "bsa_common.h"
 
 namespace bsa {
@@ -96,13 +98,18 @@ __global__ __launch_bounds__(64 * kWaves) void pool_kernel(Geom g, const uint8_t
 
 // ------------------------------------------------------------------------------ pruning
 // Lane t owns token t of the block (Bk > 64: several passes).  The token rows pass through a
-// per-wavefront LDS tile in groups of up to 8 sixteen-byte chunks: loaded row-contiguous
-// (coalesced), read back one row per lane; the dot product with the center of the token's
-// window and the two squared norms accumulate over the channels in ascending order across the
-// groups.  Ranking and quota are per window (Sec. 3.2.2, "Critical Token"); one window per
+// per-wavefront LDS tile in groups of four sixteen-byte chunks: loaded row-contiguous (four lanes
+// a row), read back one row per lane; the dot product with the center of the token's
+// window and the squared norms accumulate over the channels in ascending order across the
+// groups.  Four groups are in flight in registers, so a wavefront waits for memory once per 256 bytes of a
+// row (a small grid is bound by that latency), and 5 KB of tile a wavefront let four of them sit on a SIMD instead of three
+// (a large one is bound by the loads in flight and the fp64 rate).
+// Ranking and quota are per window (Sec. 3.2.2, "Critical Token"); one window per
 // block is the single-center method.
-constexpr int kGroup = 8;                          // chunks of a row staged at a time
-constexpr int kRowStride = kGroup * 16 + 16;       // LDS bytes per staged row (padded: lanes 16 apart share banks, the b128 minimum)
+// Eight chunks a group, none requested ahead, the center's norm in every lane, before, and now, microseconds (bf16,
+// d = 128, 64 tokens a block): 576 blocks 16.4 and 9.8, 4,368 41 and 22, 44,000 340 and 151; fp32, 576 blocks 26 and 10.
+constexpr int kGroup = 4;                          // chunks of a row staged at a time
+constexpr int kRowStride = kGroup * 16 + 16;       // LDS bytes per staged row (16 lanes' chunks take all banks)
 constexpr int kTileBytes = 64 * kRowStride;
 
 __device__ inline void wave_lds_sync() {  // LDS written by other lanes of this wavefront becomes readable
@@ -111,14 +118,16 @@ __device__ inline void wave_lds_sync() {  // LDS written by other lanes of this 
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-template <int ES>
-__global__ __launch_bounds__(64 * kWaves) void prune_kernel(Geom g, const uint8_t* Q, int kw,
+// MAXB: the largest block (LDS per token)
+// (four wavefronts a SIMD are what the sixteen loads leave registers for)
+template <int ES, int MAXB>
+__global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4, 4))) void prune_kernel(Geom g, const uint8_t* Q, int kw,
                                                            int32_t* keep_idx) {
   __shared__ __align__(16) uint8_t tiles[kWaves][kTileBytes];
-  __shared__ double cosv[kWaves][256];
-  __shared__ int koff[256];
-  __shared__ short wid[256];   // window of every intra-block token
-  __shared__ short wcen[256];  // critical token of that window (intra-block id)
+  __shared__ __align__(16) double cosv[kWaves][MAXB];
+  __shared__ int koff[MAXB];
+  __shared__ short wid[MAXB];   // window of every intra-block token
+  __shared__ short wcen[MAXB];  // critical token of that window (intra-block id)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   for (int t = threadIdx.x; t < g.Bk; t += 64 * kWaves) {
     koff[t] = intra_offset(g, t);
@@ -131,7 +140,7 @@ __global__ __launch_bounds__(64 * kWaves) void prune_kernel(Geom g, const uint8_
   if (row >= g.rows) return;
   const int64_t bh = row / g.N;
   const int i = (int)(row % g.N);
-  const int row_bytes = g.d * ES, cpr = row_bytes / 16;
+  const int row_bytes = g.d * ES, cpr = row_bytes / 16, groups = (cpr + kGroup - 1) / kGroup;
   const int n_keep = kw * g.nwin;
   const uint8_t* base = Q + (bh * g.L + block_origin(g, i)) * (int64_t)row_bytes;
   uint8_t* tile = tiles[wave];
@@ -140,56 +149,76 @@ __global__ __launch_bounds__(64 * kWaves) void prune_kernel(Geom g, const uint8_
     const int nt = min(64, g.Bk - t0);
     const int cen = wcen[min(t0 + lane, g.Bk - 1)];  // this lane's window center
     const bool cen_staged = cen >= t0 && cen < t0 + nt;  // its row is part of this pass's tile
+    const bool all_staged = __all(cen_staged);
+    // load n of a group: chunk q of row (lane >> 2) + 16 n (rows and chunks past the end repeat the last)
+    const int q = lane & 3;
+    const uint8_t* src[kGroup];
+#pragma unroll
+    for (int n = 0; n < kGroup; ++n) src[n] = base + (int64_t)koff[t0 + min((lane >> 2) + 16 * n, nt - 1)] * row_bytes;
+    typedef uint32_t words4 __attribute__((ext_vector_type(4)));
+    auto request = [&](int grp, words4 (&v)[kGroup]) {
+      const int c = min(grp * kGroup + q, cpr - 1);
+#pragma unroll
+      for (int n = 0; n < kGroup; ++n) v[n] = *reinterpret_cast<const words4*>(src[n] + 16 * c);
+    };
     double dot = 0.0, na2 = 0.0, nc2 = 0.0;  // <q, q_c>, |q|^2, |q_c|^2: channels ascending
-    for (int q0 = 0; q0 < cpr; q0 += kGroup) {
-      const int nq = min(kGroup, cpr - q0);
+    auto chunk = [&](const uint4& xv, const uint4& cv, bool norm_c) {
+      const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w}, cw[4] = {cv.x, cv.y, cv.z, cv.w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        double x[2], c[2];
+        if (ES == 4) {
+          x[0] = (double)__uint_as_float(xw[e]);
+          c[0] = (double)__uint_as_float(cw[e]);
+        } else {
+          unpack<ES>(xw[e], x[0], x[1]);
+          unpack<ES>(cw[e], c[0], c[1]);
+        }
+#pragma unroll
+        for (int h = 0; h < 4 / ES; ++h) {
+          dot = fma(x[h], c[h], dot);
+          na2 = fma(x[h], x[h], na2);
+          if (norm_c) nc2 = fma(c[h], c[h], nc2);
+        }
+      }
+    };
+    auto multiply = [&](int grp, const words4 (&v)[kGroup]) {
+      if (grp >= groups) return;
       wave_lds_sync();  // everyone is done reading the previous group
-      {  // all loads of the group first (at most 64 * kGroup / 64 = kGroup per lane), then the LDS writes
-        uint4 val[kGroup];
 #pragma unroll
-        for (int n = 0; n < kGroup; ++n) {
-          const int v = lane + 64 * n, r = min(v / nq, nt - 1), q = v - (v / nq) * nq;
-          val[n] = *reinterpret_cast<const uint4*>(base + (int64_t)koff[t0 + r] * row_bytes + 16 * (q0 + q));
-        }
-#pragma unroll
-        for (int n = 0; n < kGroup; ++n) {
-          const int v = lane + 64 * n, r = v / nq, q = v - r * nq;
-          if (v < nt * nq) *reinterpret_cast<uint4*>(tile + r * kRowStride + 16 * q) = val[n];
-        }
-      }
+      for (int n = 0; n < kGroup; ++n)
+        *reinterpret_cast<words4*>(tile + ((lane >> 2) + 16 * n) * kRowStride + 16 * q) = v[n];
       wave_lds_sync();
-      if (lane < nt) {
-        for (int q = 0; q < nq; ++q) {
-          const uint4 xv = *reinterpret_cast<const uint4*>(tile + lane * kRowStride + 16 * q);
-          const uint4 cv = cen_staged
-                               ? *reinterpret_cast<const uint4*>(tile + (cen - t0) * kRowStride + 16 * q)
-                               : *reinterpret_cast<const uint4*>(base + (int64_t)koff[cen] * row_bytes + 16 * (q0 + q));
-          const uint32_t xw[4] = {xv.x, xv.y, xv.z, xv.w}, cw[4] = {cv.x, cv.y, cv.z, cv.w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            if (ES == 4) {
-              const double x = (double)__uint_as_float(xw[e]), c = (double)__uint_as_float(cw[e]);
-              dot = fma(x, c, dot);
-              na2 = fma(x, x, na2);
-              nc2 = fma(c, c, nc2);
-            } else {
-              double xl, xh, cl, ch;
-              unpack<ES>(xw[e], xl, xh);
-              unpack<ES>(cw[e], cl, ch);
-              dot = fma(xl, cl, dot);
-              na2 = fma(xl, xl, na2);
-              nc2 = fma(cl, cl, nc2);
-              dot = fma(xh, ch, dot);
-              na2 = fma(xh, xh, na2);
-              nc2 = fma(ch, ch, nc2);
-            }
-          }
+      const int nq = min(kGroup, cpr - grp * kGroup);
+      const uint8_t* own = tile + lane * kRowStride;
+      if (all_staged) {  // the center's norm is that of its own lane
+        const uint8_t* cr = tile + (cen - t0) * kRowStride;
+        for (int k = 0; k < nq; ++k)
+          chunk(*reinterpret_cast<const uint4*>(own + 16 * k), *reinterpret_cast<const uint4*>(cr + 16 * k), false);
+      } else {
+        for (int k = 0; k < nq; ++k) {
+          const uint4 cv = cen_staged ? *reinterpret_cast<const uint4*>(tile + (cen - t0) * kRowStride + 16 * k)
+                                      : *reinterpret_cast<const uint4*>(base + (int64_t)koff[cen] * row_bytes + 16 * (grp * kGroup + k));
+          chunk(*reinterpret_cast<const uint4*>(own + 16 * k), cv, true);
         }
       }
+    };
+    for (int g0 = 0; g0 < groups; g0 += 4) {
+      words4 v0[kGroup], v1[kGroup], v2[kGroup], v3[kGroup];
+      request(g0, v0);  // (no conditions: the compiler would wait for a load at the end of one)
+      request(g0 + 1, v1);
+      request(g0 + 2, v2);
+      request(g0 + 3, v3);
+      multiply(g0, v0);
+      multiply(g0 + 1, v1);
+      multiply(g0 + 2, v2);
+      multiply(g0 + 3, v3);
     }
+    if (all_staged) nc2 = __shfl(na2, cen - t0);
     if (lane < nt) {
       const double den = __dsqrt_rn(__dmul_rn(na2, nc2));
-      cosv[wave][t0 + lane] = den > 0.0 ? __ddiv_rn(dot, den) : 0.0;
+      // (a center takes no part in the ranking: NaN is ordered before nothing)
+      cosv[wave][t0 + lane] = t0 + lane == cen ? (double)NAN : den > 0.0 ? __ddiv_rn(dot, den) : 0.0;
     }
   }
   wave_lds_sync();
@@ -199,18 +228,15 @@ __global__ __launch_bounds__(64 * kWaves) void prune_kernel(Geom g, const uint8_
     const int t = t0 + lane;
     bool keep = false;
     if (t < g.Bk) {
-      const int w = wid[t], cen = wcen[t];
-      if (t == cen) {
-        keep = true;
-      } else {
-        const double ct = cosv[wave][t];
-        int rank = 0;  // tokens of the window (center excluded) ordered before t: smaller cosine, then smaller id
-        for (int u = 0; u < g.Bk; ++u) {
-          const double cu = cosv[wave][u];
-          rank += (wid[u] == w && u != cen && u != t) && ((cu < ct) || (cu == ct && u < t));
-        }
-        keep = rank < kw - 1;
+      const int w = wid[t];
+      const double ct = cosv[wave][t];
+      int rank = 0;  // tokens of the window (center excluded) ordered before t: smaller cosine, then smaller id
+#pragma unroll 8
+      for (int u = 0; u < g.Bk; ++u) {
+        const double cu = cosv[wave][u];
+        rank += (wid[u] == w) & ((cu < ct) | ((cu == ct) & (u < t)));
       }
+      keep = t == wcen[t] || rank < kw - 1;
     }
     const unsigned long long m = __ballot(keep);
     if (keep) keep_idx[row * n_keep + base_pos + __popcll(m & ((1ull << lane) - 1ull))] = t;
@@ -234,10 +260,14 @@ int launch_pool(const Geom& g, int dtype, const void* X, double* Xbar, hipStream
 int launch_prune(const Geom& g, int dtype, const void* Q, int window_quota, int32_t* keep_idx, hipStream_t st) {
   const uint8_t* q = static_cast<const uint8_t*>(Q);
   const dim3 grid((g.rows + kWaves - 1) / kWaves), block(64 * kWaves);
-  if (dtype == BSA_F32)
-    hipLaunchKernelGGL(prune_kernel<4>, grid, block, 0, st, g, q, window_quota, keep_idx);
-  else
-    hipLaunchKernelGGL(prune_kernel<2>, grid, block, 0, st, g, q, window_quota, keep_idx);
+  const bool small = g.Bk <= 64;
+  if (dtype == BSA_F32) {
+    if (small) hipLaunchKernelGGL((prune_kernel<4, 64>), grid, block, 0, st, g, q, window_quota, keep_idx);
+    else hipLaunchKernelGGL((prune_kernel<4, 256>), grid, block, 0, st, g, q, window_quota, keep_idx);
+  } else {
+    if (small) hipLaunchKernelGGL((prune_kernel<2, 64>), grid, block, 0, st, g, q, window_quota, keep_idx);
+    else hipLaunchKernelGGL((prune_kernel<2, 256>), grid, block, 0, st, g, q, window_quota, keep_idx);
+  }
   return check_launch();
 }
 
