@@ -604,6 +604,87 @@ __global__ __launch_bounds__(256) void transpose_kernel(Geom g, const uint32_t* 
   }
 }
 
+// ---------------------------------------------------------------- 3-7 in one launch
+// Few rows: the five launches are a chain of latencies (3 to 5 us each), so one workgroup does all of it with the
+// masks in LDS.  Expansion: a wavefront per row, a column a lane, ids stored side by side; transpose as above.
+// One CU does the work, so the line lies low.  Microseconds, the launches (each with a gap of a few more ahead of it
+// in a short program) and one: 32 rows of 16 blocks, both directions, 14 and 4.9; 576 of 48, q2k alone, 8 and 9.8;
+// 756 of 126, both, 24 and 40.
+constexpr int kFewRows = 256, kFewBlocks = 64;
+__global__ __launch_bounds__(1024) void lists_kernel(Geom g, const uint32_t* mask, const int32_t* cnt, int32_t* q2k_ptr, int32_t* q2k_idx,
+                                                     int32_t* k2q_ptr, int32_t* k2q_idx, int64_t* total) {
+  __shared__ uint32_t bits[kFewRows * (kFewBlocks / 32)];
+  __shared__ int start[kFewRows], count[kFewRows], part[2][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int W = (g.N + 31) / 32;
+  const unsigned long long lt = (1ull << lane) - 1ull;
+  // exclusive scan of one value a thread; start[], ptr[0 .. rows]; a barrier inside and one at the end
+  auto scan = [&](int own, int (&tot)[16], int32_t* ptr, int64_t* sum) {
+    int incl = own;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if (lane >= o) incl += u;
+    }
+    if (lane == 63) tot[wave] = incl;
+    __syncthreads();
+    int run = incl - own, all = 0;
+#pragma unroll
+    for (int w = 0; w < 16; ++w) {
+      if (w < wave) run += tot[w];
+      all += tot[w];
+    }
+    if (tid < g.rows) start[tid] = ptr[tid] = run;
+    if (tid == 0) {
+      ptr[g.rows] = all;
+      if (sum) *sum = all;
+    }
+    __syncthreads();
+  };
+  for (int k = tid; k < g.rows * W; k += 1024) bits[k] = mask[k];
+  scan(tid < g.rows ? cnt[tid] : 0, part[0], q2k_ptr, total);
+  for (int row = wave; row < g.rows; row += 16) {
+    int pos = start[row];
+    for (int c0 = 0; c0 < g.N; c0 += 64) {
+      const int c = c0 + lane;
+      const bool set = c < g.N && (bits[row * W + min(c >> 5, W - 1)] >> (c & 31) & 1u);
+      const unsigned long long m = __ballot(set);
+      if (set) q2k_idx[pos + __popcll(m & lt)] = c;
+      pos += __popcll(m);
+    }
+  }
+  if (!k2q_ptr) return;
+  const int G = (g.N + kCols - 1) / kCols, units = g.B * g.H * G;
+  for (int fill = 0; fill < 2; ++fill) {
+    for (int unit = wave; unit < units; unit += 16) {
+      const int bh = unit / G, c0 = (unit - bh * G) * kCols;
+      const int head = bh * g.N, shift = c0 % 32;
+      int acc[kCols];
+#pragma unroll
+      for (int b = 0; b < kCols; ++b) acc[b] = fill ? start[head + min(c0 + b, g.N - 1)] : 0;
+      for (int i0 = 0; i0 < g.N; i0 += 64) {
+        const int i = i0 + lane;
+        const uint32_t now = i < g.N ? bits[(head + i) * W + c0 / 32] >> shift : 0u;
+#pragma unroll
+        for (int b = 0; b < kCols; ++b) {
+          const bool set = (now >> b) & 1u;  // (bits past the last column are zero)
+          const unsigned long long m = __ballot(set);
+          if (fill && set) k2q_idx[acc[b] + __popcll(m & lt)] = i;
+          acc[b] += __popcll(m);
+        }
+      }
+      if (!fill && lane == 0) {
+#pragma unroll
+        for (int b = 0; b < kCols; ++b)
+          if (c0 + b < g.N) count[head + c0 + b] = acc[b];
+      }
+    }
+    if (fill) return;
+    __syncthreads();  // counts written, start[] read by everyone
+    scan(tid < g.rows ? count[tid] : 0, part[1], k2q_ptr, nullptr);
+  }
+}
+
 // One wavefront per row up to 1,536 blocks, four (and two barriers a bisection step) above
 template <int NW, int MAXE, int... MORE>
 static void launch_row_select_of(const Geom& g, double p, double zq, const SelectWs& w, hipStream_t st) {
@@ -628,6 +709,10 @@ int launch_select(const Geom& g, const double* Qbar, const double* Kbar, double 
   launch_scores<8>(g, Qbar, Kbar, score_scale, w.scores, 768, st) || launch_scores<4>(g, Qbar, Kbar, score_scale, w.scores, 512, st) ||
       launch_scores<2>(g, Qbar, Kbar, score_scale, w.scores, 0, st);
   launch_row_select(g, threshold, stat_z, w, st);
+  if (g.rows <= kFewRows && g.N <= kFewBlocks) {
+    hipLaunchKernelGGL(lists_kernel, dim3(1), dim3(1024), 0, st, g, w.mask, w.cnt, q2k_ptr, q2k_idx, k2q_ptr, k2q_idx, nnz_dev);
+    return check_launch();
+  }
   hipLaunchKernelGGL(scan_kernel, dim3(1), dim3(1024), 0, st, w.cnt, g.rows, q2k_ptr, nnz_dev);
   hipLaunchKernelGGL(expand_kernel, dim3((g.rows + 3) / 4), dim3(256), 0, st, g, w.mask, q2k_ptr, q2k_idx);
   if (k2q_ptr) {

@@ -92,12 +92,13 @@ def test_block_counts(N, H):
     check(shp, host, Qbar, Kbar, 0.9, allow_marginal=True)
 
 
-@pytest.mark.parametrize("N,H,d", [(64, 2, 8), (72, 25, 24), (128, 1, 40), (136, 3, 32), (256, 40, 16), (264, 1, 72), (384, 12, 200),
+@pytest.mark.parametrize("N,H,d", [(8, 32, 8), (8, 33, 8), (64, 4, 8), (72, 3, 8), (64, 2, 8), (72, 25, 24), (128, 1, 40), (136, 3, 32), (256, 40, 16), (264, 1, 72), (384, 12, 200),
                                    (392, 2, 64), (512, 1, 104), (776, 1, 96), (1280, 2, 8), (1288, 1, 16), (1536, 1, 8), (1544, 1, 8),
                                    (2048, 2, 8), (2056, 2, 8), (3080, 1, 8)])
 def test_edges_of_tiles_and_element_counts(N, H, d):
     """The last block of a compiled element count and the first of the next, channel counts that leave a
-    remainder of a stage, every number of rows a wavefront computes, and more rows than one scan step takes.
+    remainder of a stage, every number of rows a wavefront computes, more rows than one scan step takes, and
+    the largest counts whose lists one workgroup makes.
     Integer vectors: the scores are exact, many of them tie."""
     U.progress(f"select edges N={N} H={H} d={d}")
     rng = np.random.default_rng(N + d)
