@@ -62,8 +62,9 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
   constexpr int NREG = (D / 32) * 16 + 2;  // floats per lane of a partial result: O^T tile, m, l
   const int ngroups = (g.N + PG - 1) / PG;
   Item it;
-  if (COMBINE) it = split_item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n);
-  else if (!item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)) return;
+  if (COMBINE ? !split_item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)
+              : !item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it))
+    return;
   const int unit = it.unit;
   const int64_t bh = unit / ngroups;
   const int i0 = (unit % ngroups) * PG + qb0;  // the wavefront's first query block
@@ -528,8 +529,9 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void bwd_dq_pipe_kernel(Geom
   constexpr int NREG = (D / 32) * 16;  // floats per lane of a partial result: the dQ^T tile
   const int ngroups = (g.N + PG - 1) / PG;
   Item it;
-  if (COMBINE) it = split_item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n);
-  else if (!item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)) return;
+  if (COMBINE ? !split_item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)
+              : !item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it))
+    return;
   const int unit = it.unit;
   const int64_t bh = unit / ngroups;
   const int i0 = (unit % ngroups) * PG + qb0;
@@ -784,7 +786,7 @@ static bool fwd_packs(const Geom& g, int n_keep) { return n_keep <= 16 && !g.den
 static SplitPlan fwd_plan(const Geom& g, int n_keep, bool allow, bool pack = false) {
   const bool splitq = n_keep > 32;
   const int pg = pack ? 2 * PG : PG;
-  return plan_split(((g.N + pg - 1) / pg) * g.B * g.H, kCUs * (splitq ? 1 : 2), allow);
+  return plan_split(((g.N + pg - 1) / pg) * g.B * g.H, kCUs * (splitq ? 1 : 2), g.N, allow);
 }
 
 template <int D, int NQT, bool PACK>

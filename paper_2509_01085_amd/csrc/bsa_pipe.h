@@ -4,6 +4,8 @@
 
 #include <math.h>
 
+#include <algorithm>
+
 #include "bsa_mfma.h"
 
 namespace bsa {
@@ -17,8 +19,8 @@ constexpr int PBK = 64;   // tokens per block on this path
 // [x*q + min(x, r), ...) with q = units / 8, r = units % 8: neighbouring query blocks, whose
 // lists overlap, share that XCD's L2.  When the launch is only a few rounds long (units per
 // workgroup slot), its tail leaves most of the chip idle; then the last split_n units of every
-// XCD's range are walked in split_S segments by separate, shorter workgroups dispatched last,
-// and a combine launch merges their partial results.
+// XCD's range (all of them in the shortest launches) are walked in split_S segments by separate, shorter
+// workgroups dispatched last, and a combine launch merges their partial results.
 constexpr int kCUs = 256;  // compute units of the MI355X
 
 
@@ -28,10 +30,18 @@ struct SplitPlan {
   int units;  // number of split units = workgroups of the combine launch
 };
 
-static SplitPlan plan_split(int units, int slots, bool allow) {
+// tiles: blocks of a head, the longest union a unit can walk
+static SplitPlan plan_split(int units, int slots, int tiles, bool allow) {
   SplitPlan p{1, 0, 0, 0};
   const int q = units / 8, r = units % 8, cmax = q + (r ? 1 : 0);
-  if (allow && q >= 5 && units < 12 * slots) {  // short launch: split the last fifth in four
+  if (allow && 2 * units <= slots && tiles >= 32) {
+    // Less than half a round: a launch lasts as long as one walk (about 10 us and 1.5 per tile) with most slots
+    // empty, so every unit is split, in as many segments as there are slots.  Below 32 tiles the combine launch
+    // costs what the shorter walks save.
+    // 144 units, 48 tiles, a fifth split in four against all in three: walk 74 and 43 us, combine 12 and 15.
+    p.S = std::min(slots / units, std::min(8, tiles / 8));
+    p.n = cmax;
+  } else if (allow && q >= 5 && units < 12 * slots) {  // short launch: split the last fifth in four
     p.S = 4;
     p.n = (q + 4) / 5;
   }
@@ -47,23 +57,25 @@ struct Item {
 
 __device__ inline bool item_of(int b, int units, int S, int n, Item& it) {
   const int q = units >> 3, r = units & 7, x = b & 7, k = b >> 3;
-  const int start = x * q + min(x, r), cnt = q + (x < r ? 1 : 0), whole = cnt - n;
+  const int start = x * q + min(x, r), cnt = q + (x < r ? 1 : 0);
+  const int split = min(n, cnt), whole = cnt - split;
   if (k < whole) {
     it.unit = start + k; it.seg = 0; it.nseg = 1; it.sidx = -1;
     return true;
   }
   const int kk = k - whole, si = kk / S;
-  if (si >= n) return false;
+  if (si >= split) return false;
   it.unit = start + whole + si; it.seg = kk - si * S; it.nseg = S; it.sidx = x * n + si;
   return true;
 }
 
-// the split unit a workgroup of the combine launch finishes
-__device__ inline Item split_item_of(int b, int units, int S, int n) {
+// the split unit a workgroup of the combine launch finishes (none: an XCD with fewer units than n)
+__device__ inline bool split_item_of(int b, int units, int S, int n, Item& it) {
   const int q = units >> 3, r = units & 7, x = b & 7, si = b >> 3;
-  Item it;
-  it.unit = x * q + min(x, r) + (q + (x < r ? 1 : 0) - n) + si; it.seg = 0; it.nseg = S; it.sidx = x * n + si;
-  return it;
+  const int cnt = q + (x < r ? 1 : 0), split = min(n, cnt);
+  if (si >= split) return false;
+  it.unit = x * q + min(x, r) + cnt - split + si; it.seg = 0; it.nseg = S; it.sidx = x * n + si;
+  return true;
 }
 
 // Ascending walk over the union of NL block lists kept as bit masks in LDS.  Every value
