@@ -217,8 +217,10 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4, 
     if (all_staged) nc2 = __shfl(na2, cen - t0);
     if (lane < nt) {
       const double den = __dsqrt_rn(__dmul_rn(na2, nc2));
-      // (a center takes no part in the ranking: NaN is ordered before nothing)
-      cosv[wave][t0 + lane] = t0 + lane == cen ? (double)NAN : den > 0.0 ? __ddiv_rn(dot, den) : 0.0;
+      // A center takes no part in the ranking: NaN is ordered before nothing.  Any other token has to have a
+      // place, or more than the quota would be kept: inf / inf (an infinity in Q) ranks last, by id.
+      const double c = den > 0.0 ? __ddiv_rn(dot, den) : 0.0;
+      cosv[wave][t0 + lane] = t0 + lane == cen ? (double)NAN : c == c ? c : (double)INFINITY;
     }
   }
   wave_lds_sync();
