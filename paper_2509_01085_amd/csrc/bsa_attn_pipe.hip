@@ -159,7 +159,11 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
   for (int dt = 0; dt < DT; ++dt)
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
-  float m = -INFINITY, l = 0.f;
+  // The running maximum starts at a finite value: relative to -inf the exponents of a tile of nothing but -inf
+  // logits would be NaN, and wherever a walk or a segment of one begins with it, it has to weigh nothing.
+  // The sum starts at -0, which the first tile turns into +0 or more.
+  constexpr float kLowest = -3.4e38f;
+  float m = kLowest, l = -0.f;
   const float c2 = a.sm_scale * kLog2e;
   __syncthreads();
 
@@ -174,7 +178,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 #pragma unroll
       for (int k = 0; k < NREG; ++k) v[k] = __builtin_nontemporal_load(ps + k * 64);
       const float ms = v[NREG - 2];
-      const float w = ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - m);
+      const float w = __builtin_amdgcn_exp2f(ms - m);  // (a segment that met no key above -inf has l_s = O~_s = 0)
       l += w * v[NREG - 1];
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -264,9 +268,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
       mx = pair_max(mx);
-      const float mtrue = fmaxf(m, mx * c2);  // c2 > 0: the maximum commutes with the scaling
-      // (packed: a query whose block has seen no tile yet stays at -inf; the arithmetic below then uses 0)
-      const float mnew = (PACK && mtrue == -INFINITY) ? 0.f : mtrue;
+      const float mnew = fmaxf(m, mx * c2);  // c2 > 0: the maximum commutes with the scaling
       const float alpha = __builtin_amdgcn_exp2f(m - mnew);
       float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll
@@ -277,7 +279,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
         sum1 += s[1][r];
       }
       l = l * alpha + (sum0 + sum1);  // per-lane partial; the lane pair is summed at the end
-      m = mtrue;
+      m = mnew;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {  // rescale only when some row's maximum moved
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
@@ -312,7 +314,9 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
   // (in the tile ring, idle now) for the fill
   uint16_t* cen_rows = reinterpret_cast<uint16_t*>(smem);  // [PG][nwin][D]
   const float ltot = pair_sum(l);
-  const float inv = ltot > 0.f ? 1.f / ltot : 0.f;
+  // No mass: an empty list gives zeros, a list of nothing but -inf logits NaN (packed, where a tile of the other
+  // block's list counts as one of them, zeros for both).
+  const float inv = ltot > 0.f ? 1.f / ltot : PACK || __builtin_signbit(ltot) ? 0.f : NAN;
   const float lse = ltot > 0.f ? (m + __builtin_amdgcn_logf(ltot)) * kLn2 : -INFINITY;
   __syncthreads();  // every wavefront is done with the ring
   if (qid >= 0) {
