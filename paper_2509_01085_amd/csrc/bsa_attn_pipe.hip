@@ -160,10 +160,11 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 #pragma unroll
     for (int r = 0; r < 16; ++r) o[dt][r] = 0.f;
   // The running maximum starts at a finite value: relative to -inf the exponents of a tile of nothing but -inf
-  // logits would be NaN, and wherever a walk or a segment of one begins with it, it has to weigh nothing.
-  // The sum starts at -0, which the first tile turns into +0 or more.
-  constexpr float kLowest = -3.4e38f;
-  float m = kLowest, l = -0.f;
+  // logits would be NaN, and wherever a walk or a segment of one begins with it, it has to weigh nothing (packed: a
+  // block that has seen no key yet stays at -inf, and the exponents are relative to 0).  The sum starts at -0, which
+  // the first tile turns into +0 or more.
+  constexpr float kLowest = PACK ? -INFINITY : -3.4e38f;
+  float m = kLowest, l = PACK ? 0.f : -0.f;
   const float c2 = a.sm_scale * kLog2e;
   __syncthreads();
 
@@ -178,7 +179,8 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 #pragma unroll
       for (int k = 0; k < NREG; ++k) v[k] = __builtin_nontemporal_load(ps + k * 64);
       const float ms = v[NREG - 2];
-      const float w = __builtin_amdgcn_exp2f(ms - m);  // (a segment that met no key above -inf has l_s = O~_s = 0)
+      // (a segment that met no key above -inf has l_s = O~_s = 0)
+      const float w = PACK && ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - m);
       l += w * v[NREG - 1];
 #pragma unroll
       for (int dt = 0; dt < DT; ++dt)
@@ -268,7 +270,8 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 #pragma unroll
         for (int r = 0; r < 16; ++r) mx = fmaxf(mx, s[kt][r]);
       mx = pair_max(mx);
-      const float mnew = fmaxf(m, mx * c2);  // c2 > 0: the maximum commutes with the scaling
+      const float mtrue = fmaxf(m, mx * c2);  // c2 > 0: the maximum commutes with the scaling
+      const float mnew = (PACK && mtrue == -INFINITY) ? 0.f : mtrue;
       const float alpha = __builtin_amdgcn_exp2f(m - mnew);
       float sum0 = 0.f, sum1 = 0.f;
 #pragma unroll
@@ -279,7 +282,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
         sum1 += s[1][r];
       }
       l = l * alpha + (sum0 + sum1);  // per-lane partial; the lane pair is summed at the end
-      m = mnew;
+      m = mtrue;
       if (__builtin_amdgcn_ballot_w64(alpha != 1.f)) {  // rescale only when some row's maximum moved
 #pragma unroll
         for (int dt = 0; dt < DT; ++dt)
