@@ -167,6 +167,10 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
   float m = kLowest, l = PACK ? 0.f : -0.f;
   const float c2 = a.sm_scale * kLog2e;
   __syncthreads();
+  if (it.nseg > 1 && a.split_by_lists) {  // (at the top, the prologue would wait for these loads)
+    it.nseg = min(it.nseg, max(2, pairs_of(g, a.q2k_ptr, unit, ngroups, PG) / kSegPairs));
+    if (it.seg >= it.nseg) return;
+  }
 
   // partial results of split unit sidx: [segment][wavefront][NREG][64 lanes] floats
   float* part = it.sidx >= 0 ? a.part + ((int64_t)it.sidx * a.split_S * NW + wave) * (NREG * 64) + lane : nullptr;
@@ -644,6 +648,10 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void bwd_dq_pipe_kernel(Geom
     for (int r = 0; r < 16; ++r) dq[dt][r] = 0.f;
   const float c2 = a.sm_scale * kLog2e;
   __syncthreads();
+  if (it.nseg > 1 && a.split_by_lists) {  // (at the top, the prologue would wait for these loads)
+    it.nseg = min(it.nseg, max(2, pairs_of(g, a.q2k_ptr, unit, ngroups, PG) / kSegPairs));
+    if (it.seg >= it.nseg) return;
+  }
 
   // partial results of split unit sidx: [segment][wavefront][NREG][64 lanes] floats
   float* part = it.sidx >= 0 ? a.part + ((int64_t)it.sidx * a.split_S * NW + wave) * (NREG * 64) + lane : nullptr;
@@ -814,6 +822,7 @@ static int launch_bwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
     const SplitPlan p = fwd_plan(g, a.n_keep, !g.dense, PACK);  // the dQ walk is the forward's walk
     a.split_S = p.S;
     a.split_n = p.n;
+    a.split_by_lists = p.by_lists;
     a.part = reinterpret_cast<float*>(static_cast<uint8_t*>(a.ws) + (size_t)R::BYTES * nrec);  // behind the records
     hipLaunchKernelGGL((bwd_dq_pipe_kernel<D, SPLITQ, false, PACK>), dim3(p.grid), dim3(SPLITQ ? 512 : 256), lds_q, st, g, a);
     if (p.units)
@@ -856,6 +865,7 @@ static int launch_fwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
   const SplitPlan p = fwd_plan(g, a.n_keep, !g.dense && a.fwd_ws != nullptr, PACK);
   a.split_S = p.S;
   a.split_n = p.n;
+  a.split_by_lists = p.by_lists;
   a.part = static_cast<float*>(a.fwd_ws);
   hipLaunchKernelGGL((fwd_pipe_kernel<D, SPLITQ, false, PACK>), dim3(p.grid), dim3(SPLITQ ? 512 : 256), lds, st, g, a);
   if (p.units)  // the combine launch needs LDS only for the parked critical-token rows

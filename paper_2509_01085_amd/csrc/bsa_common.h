@@ -135,6 +135,7 @@ struct AttnArgs {
   // split_S segments by separate workgroups, which leave fp32 partial results in `part` for a
   // combine launch; split_n == 0 turns it off.  fwd_ws: the forward's own workspace.
   int split_S, split_n;
+  int split_by_lists;  // 1: a split unit of short lists has fewer segments than split_S
   float* part;
   void* fwd_ws;
   int pack;  // backward records hold two query blocks of at most 16 retained queries each

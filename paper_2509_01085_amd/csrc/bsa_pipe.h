@@ -19,8 +19,8 @@ constexpr int PBK = 64;   // tokens per block on this path
 // [x*q + min(x, r), ...) with q = units / 8, r = units % 8: neighbouring query blocks, whose
 // lists overlap, share that XCD's L2.  When the launch is only a few rounds long (units per
 // workgroup slot), its tail leaves most of the chip idle; then the last split_n units of every
-// XCD's range (all of them in the shortest launches) are walked in split_S segments by separate, shorter
-// workgroups dispatched last, and a combine launch merges their partial results.
+// XCD's range (all of them in the shortest launches, and there in fewer segments where lists are short) are walked
+// in split_S segments by separate, shorter workgroups dispatched last, and a combine launch merges their partial results.
 constexpr int kCUs = 256;  // compute units of the MI355X
 
 
@@ -28,20 +28,31 @@ struct SplitPlan {
   int S, n;   // segments per split unit; split units per XCD (0: no splitting)
   int grid;   // workgroups of the main launch
   int units;  // number of split units = workgroups of the combine launch
+  int by_lists;  // 1: a unit has a segment per kSegPairs listed pairs, at least two and at most S
 };
+
+constexpr int kSegPairs = 4;
 
 // tiles: blocks of a head, the longest union a unit can walk
 static SplitPlan plan_split(int units, int slots, int tiles, bool allow) {
-  SplitPlan p{1, 0, 0, 0};
+  SplitPlan p{1, 0, 0, 0, 0};
   const int q = units / 8, r = units % 8, cmax = q + (r ? 1 : 0);
-  if (allow && 2 * units <= slots && tiles >= 32) {
+  if (!allow || q < 5) {
+    // Below 40 units a launch stands alone: how long the lists are is known only on the device, and a second launch
+    // costs more than it saves where a row lists one block or two (16 units, 64 tiles, one block a list: 13 us whole,
+    // 21 split in eight; half of the blocks listed: 84 and 31).
+  } else if (2 * units <= slots && tiles >= 32) {
     // Less than half a round: a launch lasts as long as one walk (about 10 us and 1.5 per tile) with most slots
     // empty, so every unit is split, in as many segments as there are slots.  Below 32 tiles the combine launch
     // costs what the shorter walks save.
     // 144 units, 48 tiles, a fifth split in four against all in three: walk 74 and 43 us, combine 12 and 15.
+    // A segment is worth kSegPairs listed pairs of the unit or more, two segments at least: with one block a list the eight
+    // segments of 64 units, 256 tiles, cost 33 us for the forward and 34 for dQ, mostly for empty partial results, two
+    // cost 21 and 21 (a fifth of the units in four: 25 and 22).
     p.S = std::min(slots / units, std::min(8, tiles / 8));
     p.n = cmax;
-  } else if (allow && q >= 5 && units < 12 * slots) {  // short launch: split the last fifth in four
+    p.by_lists = 1;
+  } else if (units < 12 * slots) {  // short launch: split the last fifth in four
     p.S = 4;
     p.n = (q + 4) / 5;
   }
@@ -76,6 +87,14 @@ __device__ inline bool split_item_of(int b, int units, int S, int n, Item& it) {
   if (si >= split) return false;
   it.unit = x * q + min(x, r) + cnt - split + si; it.seg = 0; it.nseg = S; it.sidx = x * n + si;
   return true;
+}
+
+// Listed pairs of a unit, whose rows' lists stand one behind the other: the same value in every segment and in the
+// combine launch, and cheaper than the union that it bounds.
+__device__ inline int pairs_of(const Geom& g, const int32_t* q2k_ptr, int unit, int ngroups, int pg) {
+  const int first = (unit % ngroups) * pg;
+  const int32_t* ptr = q2k_ptr + (int64_t)(unit / ngroups) * g.N;
+  return ptr[min(first + pg, g.N)] - ptr[first];
 }
 
 // Ascending walk over the union of NL block lists kept as bit masks in LDS.  Every value

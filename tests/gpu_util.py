@@ -102,6 +102,28 @@ def check_lists_against_oracle(wl: Workload, shp: B.Shape, host: dict, b: int, h
     return bad
 
 
+def split_plan(N: int, BH: int, n_keep: int):
+    """The host-side plan of the forward and dQ launches, restated: (kind, segments, units of a head, the units whose
+    walk is split).  A unit is a group of 4 query blocks (8 when n_keep <= 16); XCD x owns the contiguous range
+    [x*q + min(x, r), ...) of q or q + 1 units (q, r = divmod(units, 8)).  From 40 units up, "all": no more than half of
+    the chip's slots and at least 32 blocks, every unit is split; else "tail": shorter than 12 rounds of slots, the
+    last n = ceil(q / 5) of every XCD in four."""
+    pg = 8 if n_keep <= 16 else 4
+    groups = -(-N // pg)
+    units = groups * BH
+    q, r = divmod(units, 8)
+    slots = 256 * (1 if n_keep > 32 else 2)
+    if q < 5 or not (2 * units <= slots and N >= 32 or units < 12 * slots):
+        return "none", 1, groups, []
+    if 2 * units <= slots and N >= 32:
+        return "all", min(slots // units, 8, N // 8), groups, list(range(units))
+    n, out = (q + 4) // 5, []
+    for x in range(8):
+        end = x * q + min(x, r) + q + (1 if x < r else 0)
+        out.extend(range(end - n, end))
+    return "tail", 4, groups, out
+
+
 def rel_err(got: np.ndarray, ref: np.ndarray) -> float:
     """max |got - ref| / RMS(ref): the plain tolerance metric."""
     return T.figures(got, ref)["plain"]

@@ -16,9 +16,9 @@ pytestmark = pytest.mark.gpu
 
 # 64, 32 and 16 retained queries a block: two wavefronts a block, one, and two blocks a wavefront
 @pytest.mark.parametrize("keep_ratio", [1.0, 0.5, 0.25])
-@pytest.mark.parametrize("d,H", [(64, 1), (128, 1), (128, 20)])
+@pytest.mark.parametrize("d,H", [(64, 5), (128, 1), (128, 20)])
 def test_blocks_at_minus_infinity(keep_ratio, d, H):
-    """32 blocks, all listed.  One head: every walk is shared by several workgroups; twenty: the last ones of an XCD."""
+    """32 blocks, all listed.  One head: whole walks.  Five and twenty: four segments a walk, or those of the last ones of an XCD."""
     U.progress(f"masked blocks r={keep_ratio} d={d} H={H}")
     wl = Workload(f"masked_{d}_{H}", 1, H, d, "bf16", (8, 16, 16), (4, 4, 4), threshold=1.0, keep_ratio=keep_ratio)
     x = U.device_inputs(wl, ("Q", "K", "V"), heads=(0, H - 1))

@@ -41,30 +41,10 @@ def _sample(rng, n, k, always=()):
     return sorted(picks)
 
 
-# ---- which units the forward and dQ launches split (their host-side launch plan, restated) ----
-# A launch covers `units` units; XCD x owns the contiguous range [x*q + min(x, r), ...) of q or
-# q + 1 units (q, r = divmod(units, 8)) and walks the last n of it in four segments that a
-# combine launch merges.  A unit is a group of 4 query blocks (8 when n_keep <= 16),
-# n = ceil(q / 5) when q >= 5 and the launch is shorter than 12 rounds of the chip's slots.
-def _split_units(units, n):
-    q, r = divmod(units, 8)
-    out = []
-    for x in range(8):
-        start, cnt = x * q + min(x, r), q + (1 if x < r else 0)
-        out.extend(range(start + cnt - n, start + cnt))
-    return out
-
-
 def split_query_blocks(N, BH, n_keep, h):
     """Query blocks of head h (B = 1) whose forward / dQ walk is split, or []."""
-    pg = 8 if n_keep <= 16 else 4
-    groups = -(-N // pg)
-    units = groups * BH
-    q = units // 8
-    slots = 256 * (1 if n_keep > 32 else 2)
-    if not (q >= 5 and units < 12 * slots):
-        return []
-    return [(u % groups) * pg for u in _split_units(units, (q + 4) // 5) if u // groups == h]
+    _, _, groups, units = U.split_plan(N, BH, n_keep)
+    return [(u % groups) * (8 if n_keep <= 16 else 4) for u in units if u // groups == h]
 
 
 @pytest.mark.parametrize("name", list(PLAN))

@@ -38,9 +38,9 @@ CASES = {
     "keep_one": Workload("keep_one", 1, 2, 64, "fp32", (4, 8, 8), (2, 4, 4), threshold=0.6, keep_ratio=1 / 32),
     # maximum block size and head dimension
     "max_block": Workload("max_block", 1, 1, 256, "fp32", (8, 8, 8), (4, 8, 8), threshold=0.9, keep_ratio=0.3),
-    # short launches on the MFMA path: on each XCD the walks of the last units are split over
-    # several workgroups and merged by a combine launch (48 units; 60 units, not a multiple of 8,
-    # last query-block group ragged, two wavefronts per query block)
+    # short launches on the MFMA path: all walks are split over several workgroups and merged by
+    # a combine launch (48 units; 60 units, not a multiple of 8, last query-block group ragged, two
+    # wavefronts per query block)
     "split_tail": Workload("split_tail", 1, 2, 128, "bf16", (16, 16, 24), (4, 4, 4), threshold=0.7),
     "split_ragged": Workload("split_ragged", 1, 5, 64, "bf16", (12, 12, 20), (4, 4, 4), threshold=0.7, keep_ratio=0.75),
     # window-based critical tokens (Sec. 3.2.2): the paper's (2,2,2) windows in 4x4x4 blocks on the
@@ -56,7 +56,7 @@ CASES = {
     "bm_wan": Workload("mini_wan", 1, 2, 128, "bf16", (8, 8, 12), (4, 4, 4), threshold=0.6, block_major=True),
     "bm_win_split": Workload("win_split", 1, 2, 128, "bf16", (16, 16, 24), (4, 4, 4), threshold=0.7, window=(2, 2, 2), seed=3,
                              block_major=True),
-    # 16 or fewer retained queries per block: a wavefront carries two query blocks.  A split tail with
+    # 16 or fewer retained queries per block: a wavefront carries two query blocks.  Split walks with
     # windows; a block count that is not a multiple of eight (a wavefront with one real and one
     # missing block, a group with missing wavefronts); a single retained query per block
     "pack_win_split": Workload("pack_win_split", 1, 4, 128, "bf16", (16, 16, 24), (4, 4, 4), threshold=0.7, keep_ratio=0.25,
