@@ -70,11 +70,13 @@ int static_select_scratch(void** ptr, size_t* bytes) {
 // A wavefront computes R rows x 64 columns, one column a lane: the K operand of a channel is one LDS read
 // (the tile is staged transposed, the next 32 channels are requested while these are multiplied), the R
 // Q operands are the same for all lanes and come through scalar loads, so for R = 8 sixteen fp64 instructions
-// stand against one LDS read and the fp64 rate bounds it.  A workgroup is 4 R rows.
+// stand against one LDS read.  A workgroup is 4 R rows.  The latency of a stage bounds it where workgroups are few;
+// where they are many it reaches 43 % of the fp64 rate (40 heads of 1,100 blocks, d = 128), which is not its bound,
+// and the tile below 51 %.
 // Every output is accumulated over the channels in ascending order, multiply and add rounded
 // separately, whatever the tiling.
-// Before, a 64 x 64 tile a workgroup with both operands in LDS and no request ahead.  Microseconds, d = 128, before
-// and now: 12 heads of 48 blocks 32 and 10, 4 of 546 47 and 32, 12 of 364 44 and 32.
+// Microseconds, d = 128, the 64 x 64 tile below and this: 12 heads of 48 blocks 32 and 10, 4 of 546 47 and 32, 12 of
+// 364 44 and 32.
 constexpr int TJ = 64, KC = 32;
 typedef double double2_a8 __attribute__((ext_vector_type(2), aligned(8)));  // (rows are only 8-byte aligned)
 
@@ -138,6 +140,53 @@ __global__ __launch_bounds__(256) void scores_kernel(Geom g, const double* __res
 #pragma unroll
   for (int u = 0; u < R; ++u)
     if (i0 + u < g.N && j < g.N) S[((int64_t)bh * g.N + i0 + u) * g.N + j] = __dmul_rn(acc[u], scale);
+}
+
+// Many tiles: 64 x 64 scores a workgroup, 4 x 4 a thread (rows i0 + 4 ti .., columns j0 + 4 tj ..), both operands in
+// LDS: 4 + 4 reads for 16 multiply-adds a channel.  Nothing is requested ahead, so it takes enough workgroups on a
+// CU to cover a stage, and channels enough to make stages long.
+constexpr int kTile = 64, kTileKC = 16;
+__global__ __launch_bounds__(256) void scores_tile_kernel(Geom g, const double* Qbar, const double* Kbar, double scale, double* S) {
+  __shared__ __align__(16) double qs[kTileKC][kTile + 2];  // +2: conflict-free staging stores, rows stay 16-byte aligned
+  __shared__ __align__(16) double ks[kTileKC][kTile + 2];
+  const int bh = blockIdx.z;
+  const int i0 = blockIdx.y * kTile, j0 = blockIdx.x * kTile;
+  const int tid = threadIdx.x, ti = tid / 16, tj = tid % 16;
+  const double* Qh = Qbar + (int64_t)bh * g.N * g.d;
+  const double* Kh = Kbar + (int64_t)bh * g.N * g.d;
+  double acc[4][4] = {};
+  for (int c0 = 0; c0 < g.d; c0 += kTileKC) {
+    __syncthreads();
+    for (int e = tid; e < kTile * kTileKC; e += 256) {
+      const int r = e / kTileKC, c = e % kTileKC;
+      qs[c][r] = (i0 + r < g.N && c0 + c < g.d) ? Qh[(int64_t)(i0 + r) * g.d + c0 + c] : 0.0;
+    }
+    for (int e = tid; e < kTile * kTileKC; e += 256) {
+      const int r = e / kTileKC, c = e % kTileKC;
+      ks[c][r] = (j0 + r < g.N && c0 + c < g.d) ? Kh[(int64_t)(j0 + r) * g.d + c0 + c] : 0.0;
+    }
+    __syncthreads();
+    const int kc = min(kTileKC, g.d - c0);
+    for (int c = 0; c < kc; ++c) {
+      double q[4], k[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        q[u] = qs[c][4 * ti + u];
+        k[u] = ks[c][4 * tj + u];
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int u = 0; u < 4; ++u) acc[a][u] = __dadd_rn(acc[a][u], __dmul_rn(q[a], k[u]));
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int i = i0 + 4 * ti + a, j = j0 + 4 * tj + u;
+      if (i < g.N && j < g.N) S[((int64_t)bh * g.N + i) * g.N + j] = __dmul_rn(acc[a][u], scale);
+    }
 }
 
 template <int R>
@@ -697,6 +746,25 @@ static void launch_row_select(const Geom& g, double p, double zq, const SelectWs
   else launch_row_select_of<4, 8, 12, 16, 32>(g, p, zq, w, st);
 }
 
+// Tiles from 4,608 of them (4.5 rounds of four a CU) at 128 channels and from 5,632 at 64, never below.
+// Microseconds of the whole selection, wavefront rows and tiles:
+//   d = 256: 12 heads of 1,100 blocks (3,888 tiles) 492 and 507, 40 of 700 (4,840) 732 and 677, 12 of 2,520 (19,200) 2,810 and 2,573
+//   d = 128: 12 of 1,100 271 and 276, 12 of 1,280 (4,800) 413 and 414, 40 of 700 462 and 444, 40 of 1,100 (12,960) 1,129 and 1,024,
+//            12 of 2,520 1,882 and 1,746
+//   d = 64:  80 of 512 (5,120) 351 and 359, 12 of 1,400 (5,808) 384 and 383, 24 of 1,100 (7,776) 506 and 477, 12 of 2,520 1,456 and 1,384
+//   d = 32:  40 of 1,100 668 and 650, 12 of 2,048 788 and 811
+static void launch_block_logits(const Geom& g, const double* Qbar, const double* Kbar, double scale, double* S, hipStream_t st) {
+  const int n = (g.N + kTile - 1) / kTile;
+  if (g.d >= 64 && (int64_t)n * n * g.B * g.H >= (g.d >= 128 ? 4608 : 5632)) {
+    hipLaunchKernelGGL(scores_tile_kernel, dim3(n, n, g.B * g.H), dim3(256), 0, st, g, Qbar, Kbar, scale, S);
+    return;
+  }
+  // the most rows a wavefront that still leave three workgroups a CU (eight rows) or two (four): four fit, and hide
+  // the scalar loads
+  launch_scores<8>(g, Qbar, Kbar, scale, S, 768, st) || launch_scores<4>(g, Qbar, Kbar, scale, S, 512, st) ||
+      launch_scores<2>(g, Qbar, Kbar, scale, S, 0, st);
+}
+
 int launch_select(const Geom& g, const double* Qbar, const double* Kbar, double threshold, double stat_z,
                   double score_scale, int32_t* q2k_ptr, int32_t* q2k_idx, int32_t* k2q_ptr,
                   int32_t* k2q_idx, int64_t* nnz_dev, void* ws, hipStream_t st) {
@@ -705,9 +773,7 @@ int launch_select(const Geom& g, const double* Qbar, const double* Kbar, double 
   const size_t lds = (size_t)g.N * sizeof(unsigned long long);  // <= 64 KB
   if (g.N > 4096)
     if (int rc = allow_dynamic_lds<row_select_kernel<4, 32>>(lds)) return rc;
-  // the most rows per wavefront that still leave three workgroups a CU (the four that fit hide the scalar loads)
-  launch_scores<8>(g, Qbar, Kbar, score_scale, w.scores, 768, st) || launch_scores<4>(g, Qbar, Kbar, score_scale, w.scores, 512, st) ||
-      launch_scores<2>(g, Qbar, Kbar, score_scale, w.scores, 0, st);
+  launch_block_logits(g, Qbar, Kbar, score_scale, w.scores, st);
   launch_row_select(g, threshold, stat_z, w, st);
   if (g.rows <= kFewRows && g.N <= kFewBlocks) {
     hipLaunchKernelGGL(lists_kernel, dim3(1), dim3(1024), 0, st, g, w.mask, w.cnt, q2k_ptr, q2k_idx, k2q_ptr, k2q_idx, nnz_dev);

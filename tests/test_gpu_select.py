@@ -108,6 +108,28 @@ def test_edges_of_tiles_and_element_counts(N, H, d):
     check(shp, host, Qbar, Kbar, 0.8, allow_marginal=True)
 
 
+@pytest.mark.parametrize("N,H,d,tiles", [(8, 5631, 64, False), (8, 5632, 64, True), (72, 1408, 104, True), (136, 512, 128, True), (136, 511, 136, False),
+                                         (64, 4608, 56, False), (1544, 8, 200, True)])
+def test_block_logits_of_many_tiles(N, H, d, tiles):
+    """Both sides of the line from which tiles compute the block logits, and ragged tiles and stages beyond it.
+    Integer vectors: the scores are exact."""
+    U.progress(f"select tiles N={N} H={H} d={d}")
+    assert (d >= 64 and (-(-N // 64)) ** 2 * H >= (4608 if d >= 128 else 5632)) == tiles  # the rule, restated
+    rng = np.random.default_rng(N + d)
+    heads = [0, H // 2, H - 1]
+    shp, part = select_shape(N, H, d), select_shape(N, len(heads), d)
+    Qbar, Kbar = rng.integers(-2, 3, (len(heads), N, d)) * 1.0, rng.integers(-2, 3, (len(heads), N, d)) * 0.5
+    q, k = (torch.zeros((1, H, N, d), dtype=torch.float64, device="cuda") for _ in range(2))
+    q[0, heads], k[0, heads] = torch.from_numpy(Qbar).cuda(), torch.from_numpy(Kbar).cuda()
+    host = U.lists_to_host(shp, B.select_kv(shp, q, k, 0.8))
+    pick = {w: [U.head_csr(host, shp, 0, h, w) for h in heads] for w in ("q2k", "k2q")}
+    host = {}
+    for w, rows in pick.items():
+        host[w + "_ptr"] = np.concatenate([[0], np.cumsum(np.concatenate([np.diff(p) for p, _ in rows]))])
+        host[w + "_idx"] = np.concatenate([i for _, i in rows])
+    check(part, host, Qbar, Kbar, 0.8, allow_marginal=True)
+
+
 @pytest.mark.parametrize("N", [8, 200, 1600])
 @pytest.mark.parametrize("big", [1e6, 1e150, 1e300])
 def test_scores_of_very_different_size(N, big):
