@@ -219,8 +219,9 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4, 
       const double den = __dsqrt_rn(__dmul_rn(na2, nc2));
       // A center takes no part in the ranking: NaN is ordered before nothing.  Any other token has to have a
       // place, or more than the quota would be kept: inf / inf (an infinity in Q) ranks last, by id.
-      const double c = den > 0.0 ? __ddiv_rn(dot, den) : 0.0;
-      cosv[wave][t0 + lane] = t0 + lane == cen ? (double)NAN : c == c ? c : (double)INFINITY;
+      double c = NAN;
+      if (t0 + lane != cen) c = fmin(den > 0.0 ? __ddiv_rn(dot, den) : 0.0, (double)INFINITY);  // (infinity for NaN)
+      cosv[wave][t0 + lane] = c;
     }
   }
   wave_lds_sync();
