@@ -35,13 +35,16 @@ __device__ inline void unpack(uint32_t w, double& lo, double& hi) {  // ES == 2:
 // ones by the latency of a batch of loads: half a 64-token block at once, none of them behind a condition.
 // Sixteen conditional loads a batch and one word a lane before, and now, microseconds: 3,072 tokens, 12 heads,
 // d = 128, fp32 44 and 7.0, bf16 8.5 and 5.1; 23,296 tokens, bf16, 14.0 and 13.9 (5.1 TB/s).
+// A batch past the end of a block reads its last row again, so it is no longer than short blocks: 8, 16 or 32 rows.
+// 8 heads of 8,192 blocks, d = 128, fp32 and bf16, in batches of 32 and now: one token 81 and 33, 31 and 25; 8 tokens 97
+// and 35, 55 and 32; 16 tokens 110 and 58, 109 and 58.
 template <int WL>
 struct Words {
   typedef uint32_t type __attribute__((ext_vector_type(WL), aligned(4)));
 };
-template <int ES, int WL>
+// TB: token rows loaded ahead of the additions, the smallest that holds a block, or 32
+template <int ES, int WL, int TB>
 __global__ __launch_bounds__(64 * kWaves) void pool_kernel(Geom g, const uint8_t* X, double* Xbar) {
-  constexpr int TB = 32;   // token rows loaded ahead of the additions
   constexpr int CW = 4 / ES;  // channels of a word
   typedef typename Words<WL>::type words_t;
   __shared__ uint32_t off[256];  // row offsets in words
@@ -247,15 +250,22 @@ __global__ __launch_bounds__(64 * kWaves) __attribute__((amdgpu_waves_per_eu(4, 
   }
 }
 
+template <int ES, int WL>
+static void launch_pool_of(const Geom& g, const uint8_t* x, double* Xbar, hipStream_t st) {
+  const dim3 grid((g.rows + kWaves - 1) / kWaves), block(64 * kWaves);
+  if (g.Bk <= 8) hipLaunchKernelGGL((pool_kernel<ES, WL, 8>), grid, block, 0, st, g, x, Xbar);
+  else if (g.Bk <= 16) hipLaunchKernelGGL((pool_kernel<ES, WL, 16>), grid, block, 0, st, g, x, Xbar);
+  else hipLaunchKernelGGL((pool_kernel<ES, WL, 32>), grid, block, 0, st, g, x, Xbar);
+}
+
 int launch_pool(const Geom& g, int dtype, const void* X, double* Xbar, hipStream_t st) {
   const uint8_t* x = static_cast<const uint8_t*>(X);
-  const dim3 grid((g.rows + kWaves - 1) / kWaves), block(64 * kWaves);
   if (dtype == BSA_F32) {
-    if (g.d > 64) hipLaunchKernelGGL((pool_kernel<4, 2>), grid, block, 0, st, g, x, Xbar);
-    else hipLaunchKernelGGL((pool_kernel<4, 1>), grid, block, 0, st, g, x, Xbar);
+    if (g.d > 64) launch_pool_of<4, 2>(g, x, Xbar, st);
+    else launch_pool_of<4, 1>(g, x, Xbar, st);
   } else {
-    if (g.d > 128) hipLaunchKernelGGL((pool_kernel<2, 2>), grid, block, 0, st, g, x, Xbar);
-    else hipLaunchKernelGGL((pool_kernel<2, 1>), grid, block, 0, st, g, x, Xbar);
+    if (g.d > 128) launch_pool_of<2, 2>(g, x, Xbar, st);
+    else launch_pool_of<2, 1>(g, x, Xbar, st);
   }
   return check_launch();
 }
