@@ -36,8 +36,8 @@ __device__ inline void unpack(uint32_t w, double& lo, double& hi) {  // ES == 2:
 // Sixteen conditional loads a batch and one word a lane before, and now, microseconds: 3,072 tokens, 12 heads,
 // d = 128, fp32 44 and 7.0, bf16 8.5 and 5.1; 23,296 tokens, bf16, 14.0 and 13.9 (5.1 TB/s).
 // A batch past the end of a block reads its last row again, so it is no longer than short blocks: 8, 16 or 32 rows.
-// 8 heads of 8,192 blocks, d = 128, fp32 and bf16, in batches of 32 and now: one token 81 and 33, 31 and 25; 8 tokens 97
-// and 35, 55 and 32; 16 tokens 110 and 58, 109 and 58.
+// 8 heads of 8,192 blocks, d = 128, in batches of 32 and now: fp32 1 token 81 and 31, 8 tokens 97 and 55, 16 tokens 110
+// and 109; bf16 33 and 25, 35 and 32, 58 and 58.
 template <int WL>
 struct Words {
   typedef uint32_t type __attribute__((ext_vector_type(WL), aligned(4)));

@@ -5,14 +5,15 @@
 //
 // Pipeline (all on one stream, no host round trip; nnz stays on the device):
 //   1. scores_kernel       s[r][j] = score_scale * <Qbar_r, Kbar_j>, fp64, channel-ascending,
-//                          multiply and add rounded separately (the order another
+//      scores_tile_kernel  multiply and add rounded separately (the order another
 //                          implementation must follow to reproduce every comparison)
 //   2. row_select_kernel   one workgroup per row: e = exp(s - s_max), Z, then a bisection for
 //                          the key of the last block of the minimal prefix (no sort); marks
 //                          the k* selected blocks in a bit mask, writes k*
 //   3. scan_kernel         exclusive scan of the counts -> q2k_ptr, nnz
 //   4. expand_kernel       bit mask -> ascending block ids at q2k_ptr[r]
-//   5-7. transpose         per (head, 32 columns): ballot-count, scan, ballot-fill -> k2q
+//   5-7. transpose         per (head, 8 columns): ballot-count, scan, ballot-fill -> k2q
+//   lists_kernel           3 to 7 in one launch where rows are few
 #include <math.h>
 
 #include "bsa_common.h"
@@ -209,7 +210,8 @@ static bool launch_scores(const Geom& g, const double* Qbar, const double* Kbar,
 // (infinities), the pivot is the middle key, so the search ends whatever the scores are.
 // More than one key left in a bracket of one value means equal scores: those are
 // taken in ascending block id while the mass is short.  Sums run in a fixed order (per lane
-// ascending, butterfly across lanes, wavefronts in order), so the result is reproducible;
+// ascending, butterfly across lanes, wavefronts in order), so the result is reproducible (the number of wavefronts,
+// and with it the order, depends on the number of blocks alone);
 // it equals the sequential-prefix definition whenever no comparison is within rounding of a
 // tie, which the callers' margin check establishes.
 __device__ inline unsigned long long order_key(double s) {
@@ -658,7 +660,8 @@ __global__ __launch_bounds__(256) void transpose_kernel(Geom g, const uint32_t* 
 // masks in LDS.  Expansion: a wavefront per row, a column a lane, ids stored side by side; transpose as above.
 // One CU does the work, so the line lies low.  Microseconds, the launches (each with a gap of a few more ahead of it
 // in a short program) and one: 32 rows of 16 blocks, both directions, 14 and 4.9; 576 of 48, q2k alone, 8 and 9.8;
-// 756 of 126, both, 24 and 40.
+// 756 of 126, both, 24 and 40.  Whole selections of 64 blocks, d = 64: 256 rows 25.0 and 21.7 (q2k alone 16.6 and
+// 16.4), 384 rows 26 and 26, 512 rows 25 and 30.
 constexpr int kFewRows = 256, kFewBlocks = 64;
 __global__ __launch_bounds__(1024) void lists_kernel(Geom g, const uint32_t* mask, const int32_t* cnt, int32_t* q2k_ptr, int32_t* q2k_idx,
                                                      int32_t* k2q_ptr, int32_t* k2q_idx, int64_t* total) {
@@ -734,7 +737,9 @@ __global__ __launch_bounds__(1024) void lists_kernel(Geom g, const uint32_t* mas
   }
 }
 
-// One wavefront per row up to 1,536 blocks, four (and two barriers a bisection step) above
+// One wavefront per row up to 1,536 blocks (24 elements a lane), four (and two barriers a bisection step) above.  Whole
+// selections, d = 64, us, one wavefront a row and four: 1,028 blocks, 1 head 68 and 69, 40 heads 681 and 963; 1,536
+// blocks 95 and 100, 1,417 and 1,781.
 template <int NW, int MAXE, int... MORE>
 static void launch_row_select_of(const Geom& g, double p, double zq, const SelectWs& w, hipStream_t st) {
   if constexpr (sizeof...(MORE) > 0)

@@ -145,6 +145,28 @@ def test_scores_of_very_different_size(N, big):
     check(shp, host, Qbar, Kbar, 0.9, allow_marginal=True)
 
 
+@pytest.mark.parametrize("N,H", [(8, 1), (8, 32), (8, 33), (64, 4), (64, 5), (72, 3), (520, 2)])
+def test_lists_without_the_transpose(N, H):
+    """A call that asks for the query blocks' lists alone, on both sides of the line up to which one workgroup makes
+    the lists (256 rows of at most 64 blocks): the same lists and count as with the transpose."""
+    U.progress(f"select q2k alone N={N} H={H}")
+    d = 16
+    rng = np.random.default_rng(N + H)
+    shp = select_shape(N, H, d)
+    Qbar, Kbar = rng.standard_normal((H, N, d)) * 1.5, rng.standard_normal((H, N, d)) * 1.5
+    host = run(shp, Qbar, Kbar, 0.8)
+    check(shp, host, Qbar, Kbar, 0.8, allow_marginal=True)
+    q, k = (torch.from_numpy(t).cuda().reshape(1, H, N, d) for t in (Qbar, Kbar))
+    lists = B.alloc_kv_lists(shp, q.device, transpose=False)
+    lists.q2k_idx.fill_(-1)
+    B.select_kv(shp, q, k, 0.8, out=lists)
+    assert lists.k2q_ptr is None and lists.k2q_idx is None
+    nnz = int(lists.nnz.item())
+    assert nnz == host["nnz"] and np.array_equal(lists.q2k_ptr.cpu().numpy(), host["q2k_ptr"])
+    idx = lists.q2k_idx.cpu().numpy()
+    assert np.array_equal(idx[:nnz], host["q2k_idx"]) and (idx[nnz:] == -1).all()
+
+
 def test_signed_zero_and_negative_scores():
     """Scores of both signs and exact zeros (+0 and -0 must tie)."""
     U.progress("select signed zeros")
