@@ -33,7 +33,7 @@ def kernel_instances(d: int, n_keep: int) -> dict:
     launches only, as a profiler prints them.  tests/test_bench_host.py holds them to the built library."""
     b = lambda v: "true" if v else "false"
     split, pack = n_keep > 32, n_keep <= 16
-    return {"fwd_pipe_kernel": f"<{d}, {b(split)}, false, {b(pack)}>",
+    return {"fwd_walk_kernel": f"<{d}, {1 if split else 2 if pack else 0}>",
             "bwd_dq_pipe_kernel": f"<{d}, {b(split)}, false, {b(pack)}>",
             "bwd_dkv_pipe_kernel": f"<{d}, {b(pack)}>"}
 
@@ -317,7 +317,7 @@ def measure(wl, steps, warmup, torch, B, traffic=True):
     dense_flops = 14.0 * wl.B * wl.H * wl.L * wl.L * wl.d
     # credited FLOPs per listed (query block, KV block) pair, in units of d*n_keep*Bk:
     # forward 4 (QK^T, PV); dK/dV kernel 8 (S, dP, dV, dK); dQ kernel 2 (its S/dP recompute is not credited)
-    kernels = {"fwd_pipe_kernel": ("attn_fwd", 4), "bwd_dkv_pipe_kernel": ("bwd_dkv", 8), "bwd_dq_pipe_kernel": ("bwd_dq", 2)}
+    kernels = {"fwd_walk_kernel": ("attn_fwd", 4), "bwd_dkv_pipe_kernel": ("bwd_dkv", 8), "bwd_dq_pipe_kernel": ("bwd_dq", 2)}
     dominant = max(kernels, key=lambda k: parts[kernels[k][0]])
     instances = kernel_instances(wl.d, nk)
 

@@ -16,6 +16,7 @@ SOURCES = [
     "bsa_pool_prune.hip",
     "bsa_select.hip",
     "bsa_attn_generic.hip",
+    "bsa_attn_fwd.hip",
     "bsa_attn_pipe.hip",
     "bsa_attn_dkv.hip",
     "bsa_probe.hip",
@@ -27,6 +28,9 @@ FLAGS = [
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-I" + os.path.join(ROOT, "include"), "-I" + CSRC, "-Wall", "-Wno-unused-function", "-Wno-inline-asm",
 ]
+# bsa_attn_fwd: its wavefronts choose between code paths on scalars.  Structured like divergent branches, such paths would keep
+# separate registers for what they have in common, and moves between them.
+EXTRA_FLAGS = {"bsa_attn_fwd.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
 
 
 def hipcc() -> str:
@@ -45,7 +49,7 @@ def build(verbose: bool = True, out: str = LIB, extra_flags=()) -> str:
 
     def comp(src):
         obj = os.path.join(obj_dir, src.replace(".hip", ".o"))
-        cmd = [hipcc(), *FLAGS, *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
+        cmd = [hipcc(), *FLAGS, *EXTRA_FLAGS.get(src, ()), *extra_flags, "-c", os.path.join(CSRC, src), "-o", obj]
         r = subprocess.run(cmd, capture_output=True, text=True)
         noise = "is not a recognized feature for this target"
         err = "\n".join(l for l in r.stderr.splitlines() if noise not in l)

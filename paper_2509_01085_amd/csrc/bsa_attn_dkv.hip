@@ -30,72 +30,16 @@
 // 1,410 on the same card).  The matrix cores are busy 55 % of the launch's cycles, which pass at 2.0 GHz;
 // 3.5 GB come from beyond the L2 (86 % hits).  A wavefront issues an instruction in half of its cycles,
 // a vector instruction in a third: what the MFMAs leave free, the exponentials take.
-#include <type_traits>
-
 #include "bsa_pipe.h"
 
 namespace bsa {
 
-// first product of a tile (C = 0); following ones; one that also orders `done`, the tile finished
-// two slots earlier, in front of its consumers; accumulation registers
-__device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
-}
-__device__ inline void mfma_next(f32x16& d, bf16x8 a, bf16x8 b) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
-}
-__device__ inline void mfma_next(f32x16& d, bf16x8 a, bf16x8 b, f32x16& done) {
-  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0" : "+v"(d), "+v"(done) : "v"(a), "v"(b));
-}
-template <bool FRESH>  // B was written by vector instructions not long ago
-__device__ inline void mfma_acc(f32x16& d, bf16x8 a, bf16x8 b) {
-  if (FRESH) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
-  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
-}
-__device__ inline void order_behind(f32x16& done) { asm volatile("" : "+v"(done)); }
-
-// the fragments of bsa_mfma.h addressed by LDS byte offsets, so that constants fold into the
-// instruction's offset field
-__device__ inline bf16x8 frag_at(int off) {
-  return *(__attribute__((address_space(3))) const bf16x8*)(uintptr_t)(uint32_t)off;
-}
-__device__ inline f32x4 f4_at(int off) { return *(__attribute__((address_space(3))) const f32x4*)(uintptr_t)(uint32_t)off; }
-__device__ inline bf16x8 frag_tr_at(int off0, int off1) {
-  typedef __attribute__((address_space(3))) s16x4* lp;
-  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(uintptr_t)(uint32_t)off0);
-  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(uintptr_t)(uint32_t)off1);
-  typedef short s16x8 __attribute__((ext_vector_type(8)));
-  const s16x8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
-  return __builtin_bit_cast(bf16x8, v);
-}
-
-// 1 KB of a record, global -> LDS (see dma16_raw); the instruction's offset moves both addresses
-template <int OFF>
-__device__ inline void dma_kb(uint64_t sbase, uint32_t lane16, uint32_t lds) {
-  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
-               :
-               : "v"(lane16), "s"(sbase), "s"(lds), "n"(OFF)
-               : "memory", "m0");
-}
 // the record's 256 bytes of row constants: sixteen lanes
 __device__ inline void dma_tail(uint64_t sbase, uint32_t lane16, uint32_t lds) {
   asm volatile("s_mov_b32 m0, %2\n\ts_mov_b64 exec, 0xffff\n\tglobal_load_lds_dwordx4 %0, %1\n\ts_mov_b64 exec, -1"
                :
                : "v"(lane16), "s"(sbase), "s"(lds)
                : "memory", "m0");
-}
-
-template <int N>
-__device__ inline void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
-}
-
-template <int K, int N, typename F>
-__device__ inline void static_for(F f) {
-  if constexpr (K < N) {
-    f(std::integral_constant<int, K>{});
-    static_for<K + 1, N>(f);
-  }
 }
 
 constexpr int kListCap = 8192;  // blocks per head at most

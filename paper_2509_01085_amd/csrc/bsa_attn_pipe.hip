@@ -1,11 +1,12 @@
-// Pipelined bf16 MFMA forward for the flagship tile shape (Bk = 64, d = 128 or 64).
+// bf16 MFMA kernels that walk lists with a barrier a tile (Bk = 64, d = 128 or 64): the forward of launches whose lists are short
+// (bsa_attn_fwd.hip has the other one; the choice is at the end of this file) and the backward's dQ.
 //
 // A workgroup owns four consecutive query blocks of a head and walks the union of their KV
 // lists in ascending order (Eq. 5: each query block multiplies only the tiles on its own
 // list).  K/V tiles stream from the raster layout straight into an LDS ring by global->LDS
 // DMA (no staging registers, no transposition pass: the tile format of bsa_mfma.h serves both
 // the row fragments of K and the transposed fragments of V) while earlier tiles are being
-// multiplied; one barrier per tile.  Per tile and wavefront (32 queries on the MFMA column
+// multiplied; one barrier per tile.  Forward, per tile and wavefront (32 queries on the MFMA column
 // index): S^T = K Q^T, online softmax in the exp2 domain, O^T += V^T P^T.
 //
 //   n_keep <= 32 : four wavefronts (one per query block), two tiles in the ring, two
@@ -65,6 +66,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
   if (COMBINE ? !split_item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)
               : !item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it))
     return;
+  if (lists_are_long(g, a)) return;
   const int unit = it.unit;
   const int64_t bh = unit / ngroups;
   const int i0 = (unit % ngroups) * PG + qb0;  // the wavefront's first query block
@@ -796,9 +798,9 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void bwd_dq_pipe_kernel(Geom
 constexpr int fwd_part_regs(int d) { return (d / 32) * 16 + 2; }
 constexpr int dq_part_regs(int d) { return (d / 32) * 16; }
 
-// pack: the forward's packed variant (two query blocks per wavefront, eight per workgroup)
+// pack: the packed variant (two query blocks per wavefront, eight per workgroup)
 static bool fwd_packs(const Geom& g, int n_keep) { return n_keep <= 16 && !g.dense; }
-static SplitPlan fwd_plan(const Geom& g, int n_keep, bool allow, bool pack = false) {
+static SplitPlan pipe_plan(const Geom& g, int n_keep, bool allow, bool pack = false) {
   const bool splitq = n_keep > 32;
   const int pg = pack ? 2 * PG : PG;
   return plan_split(((g.N + pg - 1) / pg) * g.B * g.H, kCUs * (splitq ? 1 : 2), g.N, allow);
@@ -819,7 +821,7 @@ static int launch_bwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
   if (a.stages & BSA_BWD_PRE)  // LDS: per-row-group partial sums + per-window sums of the fill gradient
     hipLaunchKernelGGL((bwd_pre_pipe_kernel<D, NQT>), dim3(g.rows), dim3(256), (size_t)(256 / (D / 8) + g.nwin) * D * 4, st, g, a);
   if (a.stages & BSA_BWD_DQ) {
-    const SplitPlan p = fwd_plan(g, a.n_keep, !g.dense, PACK);  // the dQ walk is the forward's walk
+    const SplitPlan p = pipe_plan(g, a.n_keep, !g.dense, PACK);
     a.split_S = p.S;
     a.split_n = p.n;
     a.split_by_lists = p.by_lists;
@@ -843,16 +845,24 @@ int launch_bwd_pipe(const Geom& g, const AttnArgs& a, hipStream_t st) {
 size_t bwd_workspace_pipe(const Geom& g, int n_keep) {
   const bool two = n_keep > 32;
   const size_t per_rec = g.d == 128 ? BwdRec<128>::BYTES : BwdRec<64>::BYTES;
-  const SplitPlan p = fwd_plan(g, n_keep, !g.dense, fwd_packs(g, n_keep));
+  const SplitPlan p = pipe_plan(g, n_keep, !g.dense, fwd_packs(g, n_keep));
   const size_t partials = (size_t)p.units * p.S * (two ? 8 : 4) * dq_part_regs(g.d) * 64 * sizeof(float);
   const size_t nrec = fwd_packs(g, n_keep) ? (size_t)g.B * g.H * ((g.N + 1) / 2) : (size_t)g.rows * (two ? 2 : 1);
   return per_rec * nrec + partials;  // records | dQ partials
 }
 
+// The other forward kernel's plan keeps to the same workspace.
 size_t fwd_workspace_pipe(const Geom& g, int n_keep) {
   if (g.dense) return 0;
-  const SplitPlan p = fwd_plan(g, n_keep, true, fwd_packs(g, n_keep));
+  const SplitPlan p = pipe_plan(g, n_keep, true, fwd_packs(g, n_keep));
   return (size_t)p.units * p.S * (n_keep > 32 ? 8 : 4) * fwd_part_regs(g.d) * 64 * sizeof(float);
+}
+
+template <int D, bool SPLITQ, bool PACK>
+static int grant_fwd_pipe(const Geom& g) {
+  constexpr int PGK = PACK ? 2 * PG : PG;
+  if (int rc = allow_dynamic_lds<fwd_pipe_kernel<D, SPLITQ, false, PACK>>((size_t)(SPLITQ ? 4 : 2) * 2 * PBK * D * 2 + (size_t)PGK * ((g.N + 31) / 32) * 4)) return rc;
+  return allow_dynamic_lds<fwd_pipe_kernel<D, SPLITQ, true, PACK>>((size_t)PGK * g.nwin * D * 2);
 }
 
 template <int D, bool SPLITQ, bool PACK>
@@ -860,9 +870,8 @@ static int launch_fwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
   constexpr int PGK = PACK ? 2 * PG : PG;
   const int W = (g.N + 31) / 32;
   const size_t lds = (size_t)(SPLITQ ? 4 : 2) * 2 * PBK * D * 2 + (size_t)PGK * W * 4;
-  if (int rc = allow_dynamic_lds<fwd_pipe_kernel<D, SPLITQ, false, PACK>>(lds)) return rc;
-  if (int rc = allow_dynamic_lds<fwd_pipe_kernel<D, SPLITQ, true, PACK>>((size_t)PGK * g.nwin * D * 2)) return rc;
-  const SplitPlan p = fwd_plan(g, a.n_keep, !g.dense && a.fwd_ws != nullptr, PACK);
+  if (int rc = grant_fwd_pipe<D, SPLITQ, PACK>(g)) return rc;
+  const SplitPlan p = pipe_plan(g, a.n_keep, !g.dense && a.fwd_ws != nullptr, PACK);
   a.split_S = p.S;
   a.split_n = p.n;
   a.split_by_lists = p.by_lists;
@@ -874,9 +883,38 @@ static int launch_fwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
   return check_launch();
 }
 
-int launch_fwd_pipe(const Geom& g, const AttnArgs& a, hipStream_t st) {
-  const bool splitq = a.n_keep > 32;
-  if (fwd_packs(g, a.n_keep)) return g.d == 128 ? launch_fwd_pipe_t<128, false, true>(g, a, st) : launch_fwd_pipe_t<64, false, true>(g, a, st);
+// Two forward kernels.  The one of bsa_attn_fwd.hip costs some 15 us a unit whatever its lists, the one above half of
+// that under another workgroup's walk, but more a tile.  Within one round of the CUs the former is the faster one everywhere (12 heads of
+// 64 blocks, d = 128: 30 and 30 us at 3 blocks a list, 60 and 54 at 28).  Beyond, it is from so many listed blocks a row on
+// (old and new, d = 128, 12 heads: one tile a block, 270 blocks, 40 listed: 266 and 282 us, 121 listed: 563 and 537; two
+// tiles, 40: 476 and 494, 121: 1,018 and 965; half a tile, 13: 138 and 146, 40: 272 and 231; d = 64, two tiles, 40: 344 and 336).
+// With d = 64 and one tile a block or less it never is (520 blocks, 234 listed: 1,049 and 1,155).
+// How long the lists are is known on the device only: where they may be long enough both are launched, and one of them
+// ends at once (2 to 5 us).
+static int long_lists(const Geom& g, int n_keep) {
+  if (n_keep > 32 || g.dense) return g.d == 128 ? 56 : 40;
+  if (g.d == 64) return g.N + 1;
+  return n_keep > 16 ? 48 : 24;
+}
+
+int launch_fwd_pipe(const Geom& g, const AttnArgs& args, hipStream_t st) {
+  AttnArgs a = args;
+  const bool splitq = a.n_keep > 32, pack = fwd_packs(g, a.n_keep);
+  const int from = long_lists(g, a.n_keep), shortest = pack ? 192 : splitq ? 256 : 320;  // (fewer blocks: up to 5 % for the launch, for 1 %)
+  const bool one_round = fwd_walk_units(g, a.n_keep) <= kCUs;
+  const bool walk = one_round || (g.N >= (g.dense ? from : shortest) && g.N >= from), pipe = !one_round && (!walk || !g.dense);
+  a.fwd_long = walk && pipe ? from : 0;
+  if (walk) {
+    const SplitPlan p = pipe_plan(g, a.n_keep, !g.dense, pack);
+    if (int rc = grant_fwd_walk(g, a)) return rc;
+    if (pipe)
+      if (int rc = g.d == 128 ? pack ? grant_fwd_pipe<128, false, true>(g) : splitq ? grant_fwd_pipe<128, true, false>(g) : grant_fwd_pipe<128, false, false>(g)
+                              : pack ? grant_fwd_pipe<64, false, true>(g) : splitq ? grant_fwd_pipe<64, true, false>(g) : grant_fwd_pipe<64, false, false>(g))
+        return rc;
+    if (int rc = launch_fwd_walk(g, a, p.units * p.S * (splitq ? 2 : 1), st)) return rc;
+    if (!pipe) return BSA_OK;
+  }
+  if (pack) return g.d == 128 ? launch_fwd_pipe_t<128, false, true>(g, a, st) : launch_fwd_pipe_t<64, false, true>(g, a, st);
   if (g.d == 128) return splitq ? launch_fwd_pipe_t<128, true, false>(g, a, st) : launch_fwd_pipe_t<128, false, false>(g, a, st);
   return splitq ? launch_fwd_pipe_t<64, true, false>(g, a, st) : launch_fwd_pipe_t<64, false, false>(g, a, st);
 }

@@ -138,6 +138,9 @@ struct AttnArgs {
   int split_by_lists;  // 1: a split unit of short lists has fewer segments than split_S
   float* part;
   void* fwd_ws;
+  int fwd_long;   // forward: listed blocks a row from which on one of its two kernels is the one that works; 0: only that one is launched
+  int fwd_blocks; // forward: query blocks of a unit
+  int fwd_slots;  // forward: workgroups of an XCD that share out its whole units
   int pack;  // backward records hold two query blocks of at most 16 retained queries each
 };
 

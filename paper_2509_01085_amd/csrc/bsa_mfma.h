@@ -14,6 +14,8 @@
 // transposed LDS reads (lds_frag_tr below), so no tile is stored permuted.
 #pragma once
 
+#include <type_traits>
+
 #include "bsa_common.h"
 
 namespace bsa {
@@ -117,6 +119,15 @@ __device__ inline void dma16_raw(uint64_t sbase, uint32_t lane_offset, uint32_t 
                : "memory", "m0");
 }
 
+// The same; the instruction's offset moves both addresses.
+template <int OFF>
+__device__ inline void dma_kb(uint64_t sbase, uint32_t lane_offset, uint32_t lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1 offset:%3"
+               :
+               : "v"(lane_offset), "s"(sbase), "s"(lds_addr), "n"(OFF)
+               : "memory", "m0");
+}
+
 // Barrier without the memory fence of __syncthreads() (see dma16): callers pair it with
 // explicit waits.  The empty asm statements stop the compiler moving LDS accesses across it.
 __device__ inline void raw_barrier() {
@@ -145,6 +156,53 @@ __device__ inline float pair_max(float v) {
 __device__ inline float pair_sum(float v) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
   return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// ---- MFMAs with their operands' register files fixed (inline assembly) -------------------
+// first product of a tile (C = 0); following ones; one that also orders `done`, the tile finished
+// two slots earlier, in front of its consumers; accumulation registers
+__device__ inline void mfma_first(f32x16& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(d) : "v"(a), "v"(b));
+}
+__device__ inline void mfma_next(f32x16& d, bf16x8 a, bf16x8 b) {
+  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(d) : "v"(a), "v"(b));
+}
+__device__ inline void mfma_next(f32x16& d, bf16x8 a, bf16x8 b, f32x16& done) {
+  asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %2, %3, %0" : "+v"(d), "+v"(done) : "v"(a), "v"(b));
+}
+template <bool FRESH>  // B was written by vector instructions not long ago
+__device__ inline void mfma_acc(f32x16& d, bf16x8 a, bf16x8 b) {
+  if (FRESH) asm volatile("s_nop 1\n\tv_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+  else asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(d) : "v"(a), "v"(b));
+}
+__device__ inline void order_behind(f32x16& done) { asm volatile("" : "+v"(done)); }
+
+// the fragments of bsa_mfma.h addressed by LDS byte offsets, so that constants fold into the
+// instruction's offset field
+__device__ inline bf16x8 frag_at(int off) {
+  return *(__attribute__((address_space(3))) const bf16x8*)(uintptr_t)(uint32_t)off;
+}
+__device__ inline f32x4 f4_at(int off) { return *(__attribute__((address_space(3))) const f32x4*)(uintptr_t)(uint32_t)off; }
+__device__ inline bf16x8 frag_tr_at(int off0, int off1) {
+  typedef __attribute__((address_space(3))) s16x4* lp;
+  const s16x4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(uintptr_t)(uint32_t)off0);
+  const s16x4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(uintptr_t)(uint32_t)off1);
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const s16x8 v = {a[0], a[1], a[2], a[3], b[0], b[1], b[2], b[3]};
+  return __builtin_bit_cast(bf16x8, v);
+}
+
+template <int N>
+__device__ inline void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" : : "n"(N) : "memory");
+}
+
+template <int K, int N, typename F>
+__device__ inline void static_for(F f) {
+  if constexpr (K < N) {
+    f(std::integral_constant<int, K>{});
+    static_for<K + 1, N>(f);
+  }
 }
 
 }  // namespace bsa

@@ -66,18 +66,31 @@ struct Item {
   int sidx;  // ordinal of a split unit (addresses its partial results), -1 for a whole unit
 };
 
-__device__ inline bool item_of(int b, int units, int S, int n, Item& it) {
-  const int q = units >> 3, r = units & 7, x = b & 7, k = b >> 3;
-  const int start = x * q + min(x, r), cnt = q + (x < r ? 1 : 0);
-  const int split = min(n, cnt), whole = cnt - split;
-  if (k < whole) {
-    it.unit = start + k; it.seg = 0; it.nseg = 1; it.sidx = -1;
+// One XCD's range of units, walked as items: the whole units, then the segments of the split ones.
+struct Share {
+  int start, cnt, split, S, sbase, items;
+  __device__ inline Share(int x, int units, int S_, int n) : S(S_), sbase(x * n) {
+    const int q = units >> 3, r = units & 7;
+    start = x * q + min(x, r);
+    cnt = q + (x < r ? 1 : 0);
+    split = min(n, cnt);
+    items = cnt - split + S * split;
+  }
+  __device__ inline bool item(int k, Item& it) const {
+    const int whole = cnt - split;
+    if (k < whole) {
+      it.unit = start + k; it.seg = 0; it.nseg = 1; it.sidx = -1;
+      return true;
+    }
+    const int kk = k - whole, si = kk / S;
+    if (si >= split) return false;
+    it.unit = start + whole + si; it.seg = kk - si * S; it.nseg = S; it.sidx = sbase + si;
     return true;
   }
-  const int kk = k - whole, si = kk / S;
-  if (si >= split) return false;
-  it.unit = start + whole + si; it.seg = kk - si * S; it.nseg = S; it.sidx = x * n + si;
-  return true;
+};
+
+__device__ inline bool item_of(int b, int units, int S, int n, Item& it) {
+  return Share(b & 7, units, S, n).item(b >> 3, it);
 }
 
 // the split unit a workgroup of the combine launch finishes (none: an XCD with fewer units than n)
@@ -95,6 +108,12 @@ __device__ inline int pairs_of(const Geom& g, const int32_t* q2k_ptr, int unit, 
   const int first = (unit % ngroups) * pg;
   const int32_t* ptr = q2k_ptr + (int64_t)(unit / ngroups) * g.N;
   return ptr[min(first + pg, g.N)] - ptr[first];
+}
+
+// Where the forward's two kernels are both launched: are there so many listed blocks a row that the one of bsa_attn_fwd.hip is
+// the faster one?
+__device__ inline bool lists_are_long(const Geom& g, const AttnArgs& a) {
+  return a.fwd_long && a.q2k_ptr[g.rows] >= (int64_t)a.fwd_long * g.rows;
 }
 
 // Ascending walk over the union of NL block lists kept as bit masks in LDS.  Every value
@@ -163,6 +182,9 @@ struct BwdRec {
   static constexpr int BYTES = DL + 128;     // multiple of 256
 };
 
+int fwd_walk_units(const Geom& g, int n_keep);  // its units; within one round of the CUs the smallest that are
+int grant_fwd_walk(const Geom& g, const AttnArgs& a);  // before any launch of the call
+int launch_fwd_walk(const Geom& g, const AttnArgs& a, int cap, hipStream_t st);
 int grant_bwd_dkv_pipe(const Geom& g, const AttnArgs& a);  // before any launch of the call
 int launch_bwd_dkv_pipe(const Geom& g, const AttnArgs& a, hipStream_t st);
 
