@@ -886,13 +886,15 @@ static int launch_fwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
 // Two forward kernels.  The one of bsa_attn_fwd.hip costs some 15 us a unit whatever its lists, the one above half of
 // that under another workgroup's walk, but more a tile.  Within one round of the CUs the former is the faster one everywhere (12 heads of
 // 64 blocks, d = 128: 30 and 30 us at 3 blocks a list, 60 and 54 at 28).  Beyond, it is from so many listed blocks a row on
-// (old and new, d = 128, 12 heads: one tile a block, 270 blocks, 40 listed: 266 and 282 us, 121 listed: 563 and 537; two
-// tiles, 40: 476 and 494, 121: 1,018 and 965; half a tile, 13: 138 and 146, 40: 272 and 231; d = 64, two tiles, 40: 344 and 336).
-// With d = 64 and one tile a block or less it never is (520 blocks, 234 listed: 1,049 and 1,155).
+// (old and new, 12 heads, d = 128: one tile a block, 400 blocks, 40 listed: 371 and 375 us, 270 blocks, 54: 322 and 303; two
+// tiles, 270 blocks, 27: 359 and 335, 400 blocks, 40: 697 and 618, 16 heads of 200 blocks, 20: 273 and 286; half a tile, 270 blocks,
+// 27: 209 and 176; d = 64, two tiles, 270 blocks, 27: 259 and 228, 16 heads of 200 blocks, 20: 193 and 196).
+// With d = 64 and one tile a block or less it never is (520 blocks, 208 listed: 935 and 1,028).
 // How long the lists are is known on the device only: where they may be long enough both are launched, and one of them
 // ends at once (2 to 5 us).
 static int long_lists(const Geom& g, int n_keep) {
-  if (n_keep > 32 || g.dense) return g.d == 128 ? 56 : 40;
+  if (g.dense) return g.d == 128 ? 56 : 40;
+  if (n_keep > 32) return 32;
   if (g.d == 64) return g.N + 1;
   return n_keep > 16 ? 48 : 24;
 }
