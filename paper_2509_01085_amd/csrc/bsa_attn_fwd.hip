@@ -17,7 +17,7 @@
 // MFMA of the current job's O a share of the next one's maxima and exponents, and the requests and LDS reads of the
 // halves to come stand one behind an MFMA each.  What does not depend on the lists is compiled for every set of tiles: a jump
 // costs about 40 cycles here (the same loop with a jump for every choice took 2.38 ms on the benchmark layer).  A row maximum is moved
-// only when a logit exceeds it by 2^16: the accumulators are hardly ever scaled after the first tiles.
+// only for a key that weighs (kRise below): the accumulators are seldom scaled after the first tiles.
 //
 // One workgroup stays on a CU and takes unit after unit: the dispatcher hands out workgroups round the shader engines, and a CU
 // that was free waited 14 us for its next one.  Units are handed out by the length of their lists, reckoned by every workgroup
@@ -39,7 +39,14 @@ namespace bsa {
 enum FwdMode { kOne, kTwo, kPack };  // 32-column tiles: one a query block, two a block, one for two blocks
 
 constexpr int kFwdList = 2048;     // union entries in LDS at a time
-constexpr float kRise = 16.f;      // a row maximum is moved when a logit exceeds it by more (exp2 domain): probabilities stay below 2^16
+// A row maximum lags: it is moved when a logit exceeds it by more than kRise (exp2 domain) and the key's probability is
+// more than 1 + kShare l, with l the lane's sum so far, or more than kMost.  The probability of the key at the maximum is 1, which
+// bf16 holds exactly, and it is the keys that weigh most in a row whose rounding shows: a maximum that may lag by 2^16
+// whatever the share has 1.10 times the error of O that P relative to the row's maximum has, this one 0.98 (32 x 4 rows of 64
+// blocks, noise of 1.0 on the fields; at a noise of 0.3 1.006 and 1.000 against a maximum moved at every tile).  A move scales 64 registers, about a job's time: dense, 23,296
+// tokens, 3.01 -> 3.11 ms, 33,280 tokens 1.61 -> 1.66, a layer of 3,072 tokens 49 -> 58 us (12 jobs a tile, 4 moves).  Moved whenever kRise is
+// exceeded 3.18 ms dense; with the sum's share in a register, one comparison a job, 3.06 against 3.03.
+constexpr float kRise = 2.f, kShare = 0.5f, kMost = 64.f;
 constexpr float kLowest = -3.4e38f;
 constexpr int kFwdPlan = 512;       // items of a workgroup at most that are handed out by their length
 constexpr uint32_t kFwdFixed = 256;  // what a unit costs besides its pairs, in pairs (64 to 800: no difference of more than 2 %)
@@ -591,14 +598,16 @@ __global__ __launch_bounds__(256, 1) void fwd_walk_kernel(FwdArgs) {
         BSA_FENCE();
       });
     };
-    // a row maximum of the next job rises: its tile's sums and accumulators follow
+    // a row maximum of the next job rises: its tile's sums and accumulators follow (at the tile's first job they are zeros)
     auto raise = [&](auto S) {
       constexpr int s = decltype(S)::value;
       const float up = fmaxf(m[s], pair_max(mx) * c2), alpha = __builtin_amdgcn_exp2f(m[s] - up);
-      l[s] *= alpha;
+      if (__builtin_amdgcn_ballot_w64(m[s] != kLowest) != 0) {
+        l[s] *= alpha;
+        acc_settled();
+        static_for<0, DT>([&](auto T) { acc_mul16<16 * (DT * s + decltype(T)::value)>(alpha); });
+      }
       m[s] = up;
-      acc_settled();
-      static_for<0, DT>([&](auto T) { acc_mul16<16 * (DT * s + decltype(T)::value)>(alpha); });
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         y[r] = __builtin_fmaf(x[r], c2, -up);
@@ -621,7 +630,10 @@ __global__ __launch_bounds__(256, 1) void fwd_walk_kernel(FwdArgs) {
             logits(S, bool_constant<j == 1>{}, hn);
             values(std::integral_constant<int, nth_bit(set, j - 1)>{}, S, bool_constant<false>{}, bool_constant<last>{});
           }
-          if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx * c2 > m[bn] + kRise) != 0, 0)) raise(S);
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx * c2 > m[bn] + kRise) != 0, 0)) {
+            const float top = __builtin_amdgcn_exp2f(__builtin_fmaf(mx, c2, -m[bn]));
+            if (__builtin_amdgcn_ballot_w64(top > __builtin_amdgcn_fmed3f(0.f, __builtin_fmaf(l[bn], kShare, 1.f), kMost)) != 0) raise(S);
+          }
         });
         bc = nth_bit(set, jobs - 1);
         vfree = jobs == 1;
