@@ -16,8 +16,8 @@
 // a tile.  Behind every MFMA of the next job's S stands a share of the current job's exponentials, sums and conversions, behind every
 // MFMA of the current job's O a share of the next one's maxima and exponents, and the requests and LDS reads of the
 // halves to come stand one behind an MFMA each.  What does not depend on the lists is compiled for every set of tiles: a jump
-// costs about 40 cycles here (the same loop with a jump for every choice took 2.38 ms on the benchmark layer).  A row maximum is moved
-// only for a key that weighs (kRise below): the accumulators are seldom scaled after the first tiles.
+// costs about 40 cycles here (the same loop with a jump for every choice took 2.38 ms on the benchmark layer).  A row maximum lags
+// behind (kRise below): the accumulators are seldom scaled after the first tiles.
 //
 // One workgroup stays on a CU and takes unit after unit: the dispatcher hands out workgroups round the shader engines, and a CU
 // that was free waited 14 us for its next one.  Units are handed out by the length of their lists, reckoned by every workgroup
@@ -39,14 +39,15 @@ namespace bsa {
 enum FwdMode { kOne, kTwo, kPack };  // 32-column tiles: one a query block, two a block, one for two blocks
 
 constexpr int kFwdList = 2048;     // union entries in LDS at a time
-// A row maximum lags: it is moved when a logit exceeds it by more than kRise (exp2 domain) and the key's probability is
-// more than 1 + kShare l, with l the lane's sum so far, or more than kMost.  The probability of the key at the maximum is 1, which
-// bf16 holds exactly, and it is the keys that weigh most in a row whose rounding shows: a maximum that may lag by 2^16
-// whatever the share has 1.10 times the error of O that P relative to the row's maximum has, this one 0.98 (32 x 4 rows of 64
-// blocks, noise of 1.0 on the fields; at a noise of 0.3 1.006 and 1.000 against a maximum moved at every tile).  A move scales 64 registers, about a job's time: dense, 23,296
-// tokens, 3.01 -> 3.11 ms, 33,280 tokens 1.61 -> 1.66, a layer of 3,072 tokens 49 -> 58 us (12 jobs a tile, 4 moves).  Moved whenever kRise is
-// exceeded 3.18 ms dense; with the sum's share in a register, one comparison a job, 3.06 against 3.03.
-constexpr float kRise = 2.f, kShare = 0.5f, kMost = 64.f;
+// A row maximum lags: it is moved when a logit exceeds it by more than kRise (exp2 domain).  The probability of the key at
+// the maximum is 1, which bf16 holds exactly, and it is the keys that weigh most in a row whose rounding shows.  So where a
+// logit exceeds the maximum by more than kLag and its probability 1 + kShare l, l the lane's sum so far, the residual of the job's
+// probabilities is multiplied, too.  Error of O against that of P relative to the row's maximum (4 heads of 64 blocks, noise of 1.0 on
+// the fields): a maximum that lags by up to 2^16 with no residual 1.10, this 0.98; at a noise of 0.3 1.006 and 0.999.
+// A move scales 64 registers, about one and a half jobs' time, a residual costs half of that.  Time with the lag of 2^16, a move instead
+// of the residual, and this: dense, 23,296 tokens, 2.96, 3.07 and 3.05 ms; 33,280 tokens 1.61, 1.66 and 1.66 ms; 3,072 tokens
+// 49, 58 and 55 us.  With the limits of each tile in registers the loop spills (dense 3.28 ms).
+constexpr float kLag = 3.f, kShare = 1.f, kRise = 6.f;
 constexpr float kLowest = -3.4e38f;
 constexpr int kFwdPlan = 512;       // items of a workgroup at most that are handed out by their length
 constexpr uint32_t kFwdFixed = 256;  // what a unit costs besides its pairs, in pairs (64 to 800: no difference of more than 2 %)
@@ -614,6 +615,32 @@ __global__ __launch_bounds__(256, 1) void fwd_walk_kernel(FwdArgs) {
         if (r < E) y[r] = __builtin_amdgcn_exp2f(y[r]);
       }
     };
+    // O^T of tile s += V^T R^T, R what the rounding to bf16 will leave of the next job's probabilities.  First job of its half: V
+    // is not in registers yet, and what is there has served.
+    auto residual = [&](auto S, auto First) {
+      constexpr int s = decltype(S)::value;
+      if constexpr (decltype(First)::value) {
+        wait_vm<0>();
+        const uint32_t at = v_at(hn);
+        static_for<0, 2 * DT>([&](auto VV) { read_v(at, VV); });
+      }
+      BSA_ACC_HERE();
+      static_for<0, 2>([&](auto Q) {
+        constexpr int q = decltype(Q)::value;
+        u32x4 left;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int r = 8 * q + 2 * k;
+          const float a = r < E ? y[r] : __builtin_amdgcn_exp2f(y[r]), b = r < E ? y[r + 1] : __builtin_amdgcn_exp2f(y[r + 1]);
+          const uint32_t p = pack_bf16(a, b);
+          left[k] = pack_bf16(a - __uint_as_float(p << 16), b - __uint_as_float(p & 0xffff0000u));
+        }
+        static_for<q * DT, (q + 1) * DT>([&](auto VV) {
+          constexpr int v = decltype(VV)::value;
+          acc_mfma<16 * (DT * s + v % DT), v % DT == 0>(vf[v], as_frag(left));
+        });
+      });
+    };
     using std::bool_constant;
     auto entry_halves = [&](auto A) {
       constexpr int set = decltype(A)::value, jobs = __builtin_popcount(set);
@@ -630,9 +657,10 @@ __global__ __launch_bounds__(256, 1) void fwd_walk_kernel(FwdArgs) {
             logits(S, bool_constant<j == 1>{}, hn);
             values(std::integral_constant<int, nth_bit(set, j - 1)>{}, S, bool_constant<false>{}, bool_constant<last>{});
           }
-          if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx * c2 > m[bn] + kRise) != 0, 0)) {
-            const float top = __builtin_amdgcn_exp2f(__builtin_fmaf(mx, c2, -m[bn]));
-            if (__builtin_amdgcn_ballot_w64(top > __builtin_amdgcn_fmed3f(0.f, __builtin_fmaf(l[bn], kShare, 1.f), kMost)) != 0) raise(S);
+          if (__builtin_expect(__builtin_amdgcn_ballot_w64(mx * c2 > m[bn] + kLag) != 0, 0)) {
+            const float top = __builtin_fmaf(mx, c2, -m[bn]);
+            if (__builtin_amdgcn_ballot_w64(top > kRise) != 0) raise(S);
+            else if (__builtin_amdgcn_ballot_w64(__builtin_amdgcn_exp2f(top) > __builtin_fmaf(l[bn], kShare, 1.f)) != 0) residual(S, bool_constant<j == 0>{});
           }
         });
         bc = nth_bit(set, jobs - 1);

@@ -28,18 +28,20 @@ def rounded(Q, K, V, part, ptr, idx, keep, scale, blocks):
 
 # the roundings of the stored O are the same nearly everywhere, so the ratio scatters by less than 1 %: what is above
 # 1.03 is an error that the roundings do not explain
+# Heads: units of one tile, where every entry of a list is one job, and of several.
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("keep_ratio", [0.25, 0.5, 1.0])
-def test_error_is_that_of_the_roundings(keep_ratio, d):
-    U.progress(f"precision r={keep_ratio} d={d}")
-    wl = Workload(f"precision_{keep_ratio}_{d}", 1, 4, d, "bf16", (8, 16, 32), (4, 4, 4), threshold=0.95, keep_ratio=keep_ratio, sigma=1.0)
-    x = U.device_inputs(wl, ("Q", "K", "V"), heads=range(wl.H))
+@pytest.mark.parametrize("keep_ratio,H", [(0.25, 2), (0.25, 12), (0.5, 2), (0.5, 8), (1.0, 2), (1.0, 4)])
+def test_error_is_that_of_the_roundings(keep_ratio, H, d):
+    U.progress(f"precision r={keep_ratio} H={H} d={d}")
+    wl = Workload(f"precision_{keep_ratio}_{H}_{d}", 1, H, d, "bf16", (8, 16, 48), (4, 4, 4), threshold=0.95, keep_ratio=keep_ratio, sigma=1.0)
+    heads = sorted({0, H // 3, H // 2, H - 1})
+    x = U.device_inputs(wl, ("Q", "K", "V"), heads=heads)
     shp, _, _, lists, keep = U.run_indices(wl, x)
     O, _ = B.attn_fwd(shp, x["Q"], x["K"], x["V"], lists, keep)
     part, host = U.part_of(wl), U.lists_to_host(shp, lists)
     tok, blocks = part.block_tokens(), range(0, part.N, 4)
     got = model = 0.0
-    for h in range(wl.H):
+    for h in heads:
         ptr, idx = U.head_csr(host, shp, 0, h)
         kp, (Q, K, V) = keep[0, h].cpu().numpy(), (U.host_f64(x[c][0, h]) for c in "QKV")
         ref, _ = o.attn_fwd(Q, K, V, part, ptr, idx, kp, 1 / sqrt(d), q_blocks=list(blocks))
