@@ -784,9 +784,12 @@ __global__ __launch_bounds__(256, 1) void fwd_walk_kernel(FwdArgs) {
   }
 }
 
-// Merges the segments of a split unit, in order; wavefront s has tile s.
+// Merges the segments of a split unit, in order; wavefront s has tile s.  Both forward kernels leave their partial results alike
+// (of the other one, two tiles a block, a unit has eight tiles and two workgroups here), so where both are launched one
+// combine launch serves the one that worked: lists of one block, 259 blocks, 3 heads, d = 128, every query, 43 us with a launch
+// each and 34 so; of 16 blocks, 364 blocks, 12 heads, half of the queries 196 and 193.
 template <int D, int MODE>
-__global__ __launch_bounds__(256) void fwd_combine_kernel(Geom g, AttnArgs a) {
+__global__ __launch_bounds__(256) void fwd_combine_kernel(Geom g, AttnArgs a, FwdSplit walk, FwdSplit pipe) {
   using F = Fwd<D, MODE>;
   constexpr int PGB = F::PGB, DT = F::DT, NREG = F::NREG;
   __shared__ __align__(16) uint8_t rows[128 * F::ROWB];
@@ -795,13 +798,14 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Geom g, AttnArgs a) {
   __shared__ int16_t src[PGB * PBK];
   __shared__ uint32_t dest[PGB * PBK];
   const int tid = threadIdx.x, lane = tid & 63, s = tid >> 6, grp = lane >> 5, col = lane & 31;
-  const int ngroups = (g.N + a.fwd_blocks - 1) / a.fwd_blocks;
+  const FwdSplit p = (a.fwd_long ? lists_are_long(g, a) : walk.n > 0) ? walk : pipe;
+  const int parts = p.blocks > PGB ? p.blocks / PGB : 1, nth = blockIdx.x >> 3, sub = nth % parts;  // workgroups of a unit
+  const int ngroups = (g.N + p.blocks - 1) / p.blocks;
   Item it;
-  if (!split_item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)) return;
-  if (a.fwd_long && !lists_are_long(g, a)) return;
+  if (!split_item_of((nth / parts) << 3 | (blockIdx.x & 7), ngroups * g.B * g.H, p.S, p.n, it)) return;
   const int64_t bh = it.unit / ngroups;
-  const int i0 = (it.unit % ngroups) * a.fwd_blocks, end = min(i0 + a.fwd_blocks, g.N);
-  if (a.split_by_lists) it.nseg = min(it.nseg, max(2, pairs_of(g, a.q2k_ptr, it.unit, ngroups, a.fwd_blocks) / kSegPairs));
+  const int i0 = (it.unit % ngroups) * p.blocks + sub * PGB, end = min(i0 + min(p.blocks, PGB), g.N);
+  if (p.by_lists) it.nseg = min(it.nseg, max(2, pairs_of(g, a.q2k_ptr, it.unit, ngroups, p.blocks) / kSegPairs));
   if (tid < PBK) koff[tid] = intra_offset(g, tid);
   for (int k = tid; k < PGB * PBK; k += 256) src[k] = -1;
   __syncthreads();
@@ -810,8 +814,8 @@ __global__ __launch_bounds__(256) void fwd_combine_kernel(Geom g, AttnArgs a) {
     src[blk * PBK + min(max(a.keep_idx[(bh * g.N + i0 + blk) * a.n_keep + pos], 0), PBK - 1)] = (int16_t)(32 * s + col);
   __syncthreads();
   find_rows<PGB>(g, src, koff, i0, end, dest);
-  constexpr int64_t seg = 4 * NREG * 64;
-  const float* part = a.part + (int64_t)it.sidx * a.split_S * seg + s * (NREG * 64) + lane;
+  const int64_t seg = 4 * NREG * 64 * parts;
+  const float* part = a.part + (int64_t)it.sidx * p.S * seg + (4 * sub + s) * (NREG * 64) + lane;
   // m = max m_s, (l, O~) = sum of (l_s, O~_s) 2^(m_s - m)
   float m = kLowest, l = -0.f;
   for (int sg = 0; sg < it.nseg; ++sg) m = fmaxf(m, part[sg * seg + (NREG - 2) * 64]);
@@ -899,18 +903,25 @@ int grant_fwd_walk(const Geom& g, const AttnArgs& a) {
   return for_instance(g, a.n_keep, [&](auto D, auto M) { return allow_dynamic_lds<fwd_walk_kernel<D, M>>(Fwd<D, M>::lds(g)); });
 }
 
-int launch_fwd_walk(const Geom& g, const AttnArgs& args, int cap, hipStream_t st) {
+int launch_fwd_walk(const Geom& g, const AttnArgs& args, int cap, FwdSplit& split, hipStream_t st) {
   AttnArgs a = args;
   const FwdPlan p = plan_fwd(g, mode_of(g, a.n_keep), a.fwd_ws ? cap : 0);
+  split = FwdSplit{p.S, p.n, p.by_lists, p.blocks};
   a.split_S = p.S;
   a.split_n = p.n;
   a.split_by_lists = p.by_lists;
-  a.part = static_cast<float*>(a.fwd_ws);
   a.fwd_slots = p.slots;
   a.fwd_blocks = p.blocks;
   return for_instance(g, a.n_keep, [&](auto D, auto M) {
     hipLaunchKernelGGL((fwd_walk_kernel<D, M>), dim3(8 * (p.slots + p.S * p.n)), dim3(256), (Fwd<D, M>::lds(g)), st, FwdArgs{g, a});
-    if (p.n) hipLaunchKernelGGL((fwd_combine_kernel<D, M>), dim3(8 * p.n), dim3(256), 0, st, g, a);
+    return check_launch();
+  });
+}
+
+int launch_fwd_combine(const Geom& g, const AttnArgs& a, const FwdSplit& walk, const FwdSplit& pipe, hipStream_t st) {
+  return for_instance(g, a.n_keep, [&](auto D, auto M) {
+    const int grid = 8 * std::max(walk.n, pipe.n * std::max(1, pipe.blocks / Fwd<D, M>::PGB));
+    if (grid) hipLaunchKernelGGL((fwd_combine_kernel<D, M>), dim3(grid), dim3(256), 0, st, g, a, walk, pipe);
     return check_launch();
   });
 }

@@ -25,13 +25,12 @@ bool mfma_supported(const Geom& g, int dtype, int n_keep) {
   return dtype == BSA_BF16 && g.Bk == PBK && (g.d == 128 || g.d == 64) && n_keep <= PBK;
 }
 
-// COMBINE = false: the walk (a whole unit, or one segment of a split unit, whose unnormalised
-// accumulators, running maxima and sums go to a.part).  COMBINE = true: merge the segments of
-// a split unit and finish it.  Both end in the same epilogue.
+// The walk: a whole unit, or one segment of a split unit, whose unnormalised accumulators, running maxima and sums go
+// to a.part (fwd_combine_kernel merges them).
 // PACK (n_keep <= 16): a wavefront carries two query blocks, 16 columns of its 32-column MFMA
 // tile each, so a workgroup covers eight blocks; a tile that only one of the two lists holds
 // is masked (-inf) in the other block's columns.
-template <int D, bool SPLITQ, bool COMBINE, bool PACK>
+template <int D, bool SPLITQ, bool PACK>
 __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g, AttnArgs a) {
   static_assert(!(PACK && SPLITQ), "packing is for short retained sets");
   constexpr int PG = PACK ? 2 * bsa::PG : bsa::PG;  // query blocks per workgroup
@@ -63,9 +62,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
   constexpr int NREG = (D / 32) * 16 + 2;  // floats per lane of a partial result: O^T tile, m, l
   const int ngroups = (g.N + PG - 1) / PG;
   Item it;
-  if (COMBINE ? !split_item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)
-              : !item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it))
-    return;
+  if (!item_of(blockIdx.x, ngroups * g.B * g.H, a.split_S, a.split_n, it)) return;
   if (lists_are_long(g, a)) return;
   const int unit = it.unit;
   const int64_t bh = unit / ngroups;
@@ -81,11 +78,10 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
   float* Lh = a.LSE_out + bh * g.L;
 
   if (tid < PBK) koff[tid] = intra_offset(g, tid);
-  if (!COMBINE)
-    for (int k = tid; k < PG * W; k += NT) masks[k] = 0u;
+  for (int k = tid; k < PG * W; k += NT) masks[k] = 0u;
   if (tid < 2 * PG) keepbits[tid >> 1][tid & 1] = 0u;
   __syncthreads();
-  if (!COMBINE && sub == 0) {
+  if (sub == 0) {
 #pragma unroll
     for (int o2 = 0; o2 < NOWN; ++o2) {  // the wavefront's own list(s)
       const int ib = i0 + o2, ql = qb0 + o2;
@@ -135,7 +131,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 #pragma unroll
   for (int s = 0; s < DS; ++s) {
     u32x4 v = {0u, 0u, 0u, 0u};
-    if (!COMBINE && qid >= 0) v = *reinterpret_cast<const u32x4*>(Qh + (int64_t)qtok * D + 16 * s + 8 * grp);
+    if (qid >= 0) v = *reinterpret_cast<const u32x4*>(Qh + (int64_t)qtok * D + 16 * s + 8 * grp);
     qf[s] = as_frag(v);
   }
 #pragma unroll
@@ -176,38 +172,18 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
 
   // partial results of split unit sidx: [segment][wavefront][NREG][64 lanes] floats
   float* part = it.sidx >= 0 ? a.part + ((int64_t)it.sidx * a.split_S * NW + wave) * (NREG * 64) + lane : nullptr;
-  if (COMBINE) {
-    // merge the segments in order: m = max m_s, (l, O~) = sum of (l_s, O~_s) 2^(m_s - m)
-    for (int sg = 0; sg < it.nseg; ++sg) m = fmaxf(m, part[(int64_t)sg * NW * NREG * 64 + (NREG - 2) * 64]);
-    for (int sg = 0; sg < it.nseg; ++sg) {
-      const float* ps = part + (int64_t)sg * NW * NREG * 64;
-      float v[NREG];  // the segment's values first, all loads in flight together
-#pragma unroll
-      for (int k = 0; k < NREG; ++k) v[k] = __builtin_nontemporal_load(ps + k * 64);
-      const float ms = v[NREG - 2];
-      // (a segment that met no key above -inf has l_s = O~_s = 0)
-      const float w = PACK && ms == -INFINITY ? 0.f : __builtin_amdgcn_exp2f(ms - m);
-      l += w * v[NREG - 1];
-#pragma unroll
-      for (int dt = 0; dt < DT; ++dt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) o[dt][r] += w * v[dt * 16 + r];
-    }
-  }
   WalkN<PG, NOWN> walk(masks, W, qb0);  // runs NB-1 tiles ahead of the multiplication; `pending` remembers
   int issued = 0;                      // for the tiles in flight which of this wavefront's lists have them (2 bits a tile)
   uint32_t pending = 0;
-  if (!COMBINE) {
-    if (it.nseg > 1) walk.restrict_to(it.seg, it.nseg);
+  if (it.nseg > 1) walk.restrict_to(it.seg, it.nseg);
 #pragma unroll
-    for (int k = 0; k < NB - 1; ++k) {
-      uint32_t mk = 0;
-      const int jb = walk.next(mk);
-      if (jb >= 0) {
-        issue(jb, k);
-        pending |= mk << (2 * k);
-        ++issued;
-      }
+  for (int k = 0; k < NB - 1; ++k) {
+    uint32_t mk = 0;
+    const int jb = walk.next(mk);
+    if (jb >= 0) {
+      issue(jb, k);
+      pending |= mk << (2 * k);
+      ++issued;
     }
   }
   for (int t = 0; t < issued; ++t) {
@@ -309,7 +285,7 @@ __global__ __launch_bounds__(SPLITQ ? 512 : 256, 2) void fwd_pipe_kernel(Geom g,
     }
   }
 
-  if (!COMBINE && it.nseg > 1) {  // a segment: leave the partial result, the combine launch finishes the unit
+  if (it.nseg > 1) {  // a segment: leave the partial result, the combine launch finishes the unit
     float* ps = part + (int64_t)it.seg * NW * NREG * 64;
 #pragma unroll
     for (int dt = 0; dt < DT; ++dt)
@@ -859,28 +835,32 @@ size_t fwd_workspace_pipe(const Geom& g, int n_keep) {
 }
 
 template <int D, bool SPLITQ, bool PACK>
-static int grant_fwd_pipe(const Geom& g) {
-  constexpr int PGK = PACK ? 2 * PG : PG;
-  if (int rc = allow_dynamic_lds<fwd_pipe_kernel<D, SPLITQ, false, PACK>>((size_t)(SPLITQ ? 4 : 2) * 2 * PBK * D * 2 + (size_t)PGK * ((g.N + 31) / 32) * 4)) return rc;
-  return allow_dynamic_lds<fwd_pipe_kernel<D, SPLITQ, true, PACK>>((size_t)PGK * g.nwin * D * 2);
+static size_t fwd_pipe_lds(const Geom& g) {
+  return (size_t)(SPLITQ ? 4 : 2) * 2 * PBK * D * 2 + (size_t)(PACK ? 2 * PG : PG) * ((g.N + 31) / 32) * 4;
 }
 
-template <int D, bool SPLITQ, bool PACK>
-static int launch_fwd_pipe_t(const Geom& g, AttnArgs a, hipStream_t st) {
-  constexpr int PGK = PACK ? 2 * PG : PG;
-  const int W = (g.N + 31) / 32;
-  const size_t lds = (size_t)(SPLITQ ? 4 : 2) * 2 * PBK * D * 2 + (size_t)PGK * W * 4;
-  if (int rc = grant_fwd_pipe<D, SPLITQ, PACK>(g)) return rc;
-  const SplitPlan p = pipe_plan(g, a.n_keep, !g.dense && a.fwd_ws != nullptr, PACK);
+// calls f with the constants of the kernel
+template <typename F>
+static int for_fwd_pipe(const Geom& g, int n_keep, F f) {
+  using std::bool_constant;
+  auto go = [&](auto D) {
+    if (fwd_packs(g, n_keep)) return f(D, bool_constant<false>{}, bool_constant<true>{});
+    return n_keep > 32 ? f(D, bool_constant<true>{}, bool_constant<false>{}) : f(D, bool_constant<false>{}, bool_constant<false>{});
+  };
+  return g.d == 128 ? go(std::integral_constant<int, 128>{}) : go(std::integral_constant<int, 64>{});
+}
+
+static int launch_pipe(const Geom& g, AttnArgs a, FwdSplit& split, hipStream_t st) {
+  const bool pack = fwd_packs(g, a.n_keep);
+  const SplitPlan p = pipe_plan(g, a.n_keep, !g.dense && a.fwd_ws != nullptr, pack);
+  split = FwdSplit{p.S, p.n, p.by_lists, pack ? 2 * PG : PG};
   a.split_S = p.S;
   a.split_n = p.n;
   a.split_by_lists = p.by_lists;
-  a.part = static_cast<float*>(a.fwd_ws);
-  hipLaunchKernelGGL((fwd_pipe_kernel<D, SPLITQ, false, PACK>), dim3(p.grid), dim3(SPLITQ ? 512 : 256), lds, st, g, a);
-  if (p.units)  // the combine launch needs LDS only for the parked critical-token rows
-    hipLaunchKernelGGL((fwd_pipe_kernel<D, SPLITQ, true, PACK>), dim3(p.units), dim3(SPLITQ ? 512 : 256),
-                       (size_t)PGK * g.nwin * D * 2, st, g, a);
-  return check_launch();
+  return for_fwd_pipe(g, a.n_keep, [&](auto D, auto SPLITQ, auto PACK) {
+    hipLaunchKernelGGL((fwd_pipe_kernel<D, SPLITQ, PACK>), dim3(p.grid), dim3(SPLITQ ? 512 : 256), (fwd_pipe_lds<D, SPLITQ, PACK>(g)), st, g, a);
+    return check_launch();
+  });
 }
 
 // Two forward kernels.  The one of bsa_attn_fwd.hip costs some 15 us a unit whatever its lists, the one above half of
@@ -906,19 +886,21 @@ int launch_fwd_pipe(const Geom& g, const AttnArgs& args, hipStream_t st) {
   const bool one_round = fwd_walk_units(g, a.n_keep) <= kCUs;
   const bool walk = one_round || (g.N >= (g.dense ? from : shortest) && g.N >= from), pipe = !one_round && (!walk || !g.dense);
   a.fwd_long = walk && pipe ? from : 0;
-  if (walk) {
-    const SplitPlan p = pipe_plan(g, a.n_keep, !g.dense, pack);
+  a.part = static_cast<float*>(a.fwd_ws);
+  if (walk)
     if (int rc = grant_fwd_walk(g, a)) return rc;
-    if (pipe)
-      if (int rc = g.d == 128 ? pack ? grant_fwd_pipe<128, false, true>(g) : splitq ? grant_fwd_pipe<128, true, false>(g) : grant_fwd_pipe<128, false, false>(g)
-                              : pack ? grant_fwd_pipe<64, false, true>(g) : splitq ? grant_fwd_pipe<64, true, false>(g) : grant_fwd_pipe<64, false, false>(g))
-        return rc;
-    if (int rc = launch_fwd_walk(g, a, p.units * p.S * (splitq ? 2 : 1), st)) return rc;
-    if (!pipe) return BSA_OK;
-  }
-  if (pack) return g.d == 128 ? launch_fwd_pipe_t<128, false, true>(g, a, st) : launch_fwd_pipe_t<64, false, true>(g, a, st);
-  if (g.d == 128) return splitq ? launch_fwd_pipe_t<128, true, false>(g, a, st) : launch_fwd_pipe_t<128, false, false>(g, a, st);
-  return splitq ? launch_fwd_pipe_t<64, true, false>(g, a, st) : launch_fwd_pipe_t<64, false, false>(g, a, st);
+  if (pipe)
+    if (int rc = for_fwd_pipe(g, a.n_keep, [&](auto D, auto SPLITQ, auto PACK) {
+          return allow_dynamic_lds<fwd_pipe_kernel<D, SPLITQ, PACK>>(fwd_pipe_lds<D, SPLITQ, PACK>(g));
+        }))
+      return rc;
+  const SplitPlan p = pipe_plan(g, a.n_keep, !g.dense, pack);
+  FwdSplit sw{1, 0, 0, 0}, sp{1, 0, 0, 0};
+  if (walk)
+    if (int rc = launch_fwd_walk(g, a, p.units * p.S * (splitq ? 2 : 1), sw, st)) return rc;
+  if (pipe)
+    if (int rc = launch_pipe(g, a, sp, st)) return rc;
+  return launch_fwd_combine(g, a, sw, sp, st);
 }
 
 }  // namespace bsa

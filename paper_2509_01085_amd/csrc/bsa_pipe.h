@@ -184,7 +184,13 @@ struct BwdRec {
 
 int fwd_walk_units(const Geom& g, int n_keep);  // its units; within one round of the CUs the smallest that are
 int grant_fwd_walk(const Geom& g, const AttnArgs& a);  // before any launch of the call
-int launch_fwd_walk(const Geom& g, const AttnArgs& a, int cap, hipStream_t st);
+struct FwdSplit {
+  int S, n, by_lists;  // segments of a split unit, split units of an XCD, as in SplitPlan
+  int blocks;          // query blocks of a unit
+};
+int launch_fwd_walk(const Geom& g, const AttnArgs& a, int cap, FwdSplit& split, hipStream_t st);
+// finishes the split units of the forward kernels that were launched; n of the others is 0
+int launch_fwd_combine(const Geom& g, const AttnArgs& a, const FwdSplit& walk, const FwdSplit& pipe, hipStream_t st);
 int grant_bwd_dkv_pipe(const Geom& g, const AttnArgs& a);  // before any launch of the call
 int launch_bwd_dkv_pipe(const Geom& g, const AttnArgs& a, hipStream_t st);
 

@@ -124,6 +124,18 @@ def split_plan(N: int, BH: int, n_keep: int):
     return "tail", 4, groups, out
 
 
+def forward_route(N: int, BH: int, n_keep: int, d: int) -> str:
+    """Which of the two bf16 forward kernels a sparse call launches, restated: "walk" (bsa_attn_fwd.hip), "pipe"
+    (bsa_attn_pipe.hip) or "both", where the lists' mean length decides on the device."""
+    most, least = (8, 2) if n_keep <= 16 else (2, 1) if n_keep > 32 else (4, 1)
+    while most > least and -(-N // (most - least)) * BH <= 256:
+        most -= least
+    if -(-N // most) * BH <= 256:
+        return "walk"
+    start, shortest = (32, 256) if n_keep > 32 else (N + 1, 0) if d == 64 else (48, 320) if n_keep > 16 else (24, 192)
+    return "both" if N >= max(start, shortest) else "pipe"
+
+
 def rel_err(got: np.ndarray, ref: np.ndarray) -> float:
     """max |got - ref| / RMS(ref): the plain tolerance metric."""
     return T.figures(got, ref)["plain"]
