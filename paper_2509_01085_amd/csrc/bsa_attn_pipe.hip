@@ -863,28 +863,51 @@ static int launch_pipe(const Geom& g, AttnArgs a, FwdSplit& split, hipStream_t s
   });
 }
 
-// Two forward kernels.  The one of bsa_attn_fwd.hip costs some 15 us a unit whatever its lists, the one above half of
-// that under another workgroup's walk, but more a tile.  Within one round of the CUs the former is the faster one everywhere (12 heads of
-// 64 blocks, d = 128: 30 and 30 us at 3 blocks a list, 60 and 54 at 28).  Beyond, it is from so many listed blocks a row on
-// (old and new, 12 heads, d = 128: one tile a block, 400 blocks, 40 listed: 371 and 375 us, 270 blocks, 54: 322 and 303; two
-// tiles, 270 blocks, 27: 359 and 335, 400 blocks, 40: 697 and 618, 16 heads of 200 blocks, 20: 273 and 286; half a tile, 270 blocks,
-// 27: 209 and 176; d = 64, two tiles, 270 blocks, 27: 259 and 228, 16 heads of 200 blocks, 20: 193 and 196).
-// With d = 64 and one tile a block or less it never is (520 blocks, 208 listed: 935 and 1,028).
-// How long the lists are is known on the device only: where they may be long enough both are launched, and one of them
-// ends at once (2 to 5 us).
-static int long_lists(const Geom& g, int n_keep) {
-  if (g.dense) return g.d == 128 ? 56 : 40;
-  if (n_keep > 32) return 32;
-  if (g.d == 64) return g.N + 1;
-  return n_keep > 16 ? 48 : 24;
+// Two forward kernels.  The one of bsa_attn_fwd.hip (walk) costs some 15 us a unit whatever its lists, the one above (pipe) half of
+// that under another workgroup's walk, but more a tile.  What walk does for the keys that weigh most in a row costs the more, the sharper
+// the logits.  Figures: us, pipe / walk, 12 heads, selected lists of so many blocks on fields with noise of 0.3 (with noise of 1.0).
+struct FwdChoice {
+  bool walk, pipe;
+  int from;  // both are launched, and one ends at once (2 us): walk works from so many listed blocks a row on
+};
+
+static FwdChoice choose_forward(const Geom& g, int n_keep) {
+  const bool half = fwd_packs(g, n_keep), two = g.dense || n_keep > 32, one = !half && !two;  // tiles a block
+  const int units = fwd_walk_units(g, n_keep);
+  if (units <= kCUs) {
+    // Within one round walk takes a workgroup a unit and no combine launch.  d = 128, 4 heads of 128 blocks, 23 and 72 listed: two
+    // tiles a block 66 / 56, 113 / 101 (67 / 63, 114 / 113), one 46 / 41, 72 / 69 (47 / 45, 73 / 74), half 49 / 40, 60 / 57
+    // (49 / 41, 61 / 60); half a tile, 12 heads, 72 listed: 134 / 116 (136 / 131).  But pipe, with less than two tiles a block,
+    // - where the chip is full of short walks: 48 blocks, 18 and 36 listed, one tile: 46 / 44, 52 / 54 (47 / 50, 53 / 62), half
+    //   46 / 46, 47 / 50 (45 / 48, 47 / 55); d = 64, 4 heads of 128 blocks, 71 and 92 listed: one 49 / 49, 54 / 56 (49 / 55, 54 / 62), half
+    //   43 / 42, 44 / 46 (44 / 47, 44 / 48);
+    // - where units shrink to a block or four and pipe has several segments for each: 1 head, 520 blocks, half a tile, 48, 200 and 520
+    //   listed (independent logits with a deviation of 2): 80 / 78, 146 / 176, 196 / 280; 256 blocks, one tile, 200 listed: 88 / 95;
+    // and below 16 blocks, where lists are short whatever the threshold (2 heads of 12 blocks, 3 and 12 listed: 16 / 18, 23 / 23).
+    const bool full = !two && g.rows >= 512 && g.N <= (g.d == 128 ? 64 : 128);
+    const bool lone = !two && g.N >= 256 && g.rows <= 640, few = g.N < 16 && !g.dense;
+    const bool walk = !full && !lone && !few;
+    return {walk, !walk, 0};
+  }
+  // Beyond, the lists decide, and how long they are is known on the device only.  d = 128:
+  // two tiles, 364 blocks, 26, 57 and 179 listed: 500 / 455, 886 / 720, 1944 / 1720 (507 / 534, 889 / 816, 2023 / 1873);
+  // one, 26, 57 and 179: 283 / 292, 484 / 444, 1052 / 956 (285 / 328, 489 / 504, 1097 / 1035), 1,100 blocks, 52: 1392 / 1392 (1432 / 1446);
+  // half, 26, 57 and 179: 252 / 238, 400 / 370, 664 / 645 (256 / 259, 399 / 395, 671 / 699), 520 blocks, 28: 434 / 344 (434 / 381).
+  // d = 64: two tiles, 364 blocks, 27 and 59: 366 / 339, 647 / 526 (363 / 386, 644 / 591); one tile or less hardly ever (520 blocks, one, 29,
+  // 67 and 346: 235 / 301, 435 / 494, 1435 / 1594).
+  // Fewer blocks: two tiles, 192 blocks, 26, 51 and 161: 233 / 256, 374 / 367, 822 / 814; one, 252 blocks, 27, 56: 206 / 212, 336 / 311 (206 / 242,
+  // 346 / 353), 192 blocks, 92: 300 / 337; half, 192 blocks, 26: 175 / 126, but with little more than two rounds of units (24 heads,
+  // independent logits, 64 listed) 352 / 424.  Dense, from where the block count is a list's length.
+  const int from = g.dense ? (g.d == 128 ? 56 : 40) : two ? 32 : g.d == 64 ? g.N + 1 : one ? 48 : 24;
+  const int shortest = g.dense ? 0 : two ? 256 : one ? 320 : units < 2 * kCUs ? 192 : 320;
+  const bool walk = g.N >= from && g.N >= shortest;
+  return {walk, !walk || !g.dense, from};
 }
 
 int launch_fwd_pipe(const Geom& g, const AttnArgs& args, hipStream_t st) {
   AttnArgs a = args;
   const bool splitq = a.n_keep > 32, pack = fwd_packs(g, a.n_keep);
-  const int from = long_lists(g, a.n_keep), shortest = pack ? 192 : splitq ? 256 : 320;  // (fewer blocks: up to 5 % for the launch, for 1 %)
-  const bool one_round = fwd_walk_units(g, a.n_keep) <= kCUs;
-  const bool walk = one_round || (g.N >= (g.dense ? from : shortest) && g.N >= from), pipe = !one_round && (!walk || !g.dense);
+  const auto [walk, pipe, from] = choose_forward(g, a.n_keep);
   a.fwd_long = walk && pipe ? from : 0;
   a.part = static_cast<float*>(a.fwd_ws);
   if (walk)

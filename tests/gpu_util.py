@@ -127,13 +127,39 @@ def split_plan(N: int, BH: int, n_keep: int):
 def forward_route(N: int, BH: int, n_keep: int, d: int) -> str:
     """Which of the two bf16 forward kernels a sparse call launches, restated: "walk" (bsa_attn_fwd.hip), "pipe"
     (bsa_attn_pipe.hip) or "both", where the lists' mean length decides on the device."""
+    half, two = n_keep <= 16, n_keep > 32
+    _, walk_units = unit_blocks(N, BH, n_keep)
+    if walk_units <= 256:
+        full = not two and N * BH >= 512 and N <= (64 if d == 128 else 128)
+        lone = not two and N >= 256 and N * BH <= 640
+        return "pipe" if full or lone or N < 16 else "walk"
+    start = 32 if two else N + 1 if d == 64 else 24 if half else 48
+    shortest = 256 if two else 192 if half and walk_units < 512 else 320
+    return "both" if N >= max(start, shortest) else "pipe"
+
+
+def unit_blocks(N: int, BH: int, n_keep: int):
+    """Query blocks of a unit of "walk", and its units: 4, 2 with more than 32 retained queries, 8 with at most 16; fewer
+    while all units still are one round of the 256 compute units."""
     most, least = (8, 2) if n_keep <= 16 else (2, 1) if n_keep > 32 else (4, 1)
     while most > least and -(-N // (most - least)) * BH <= 256:
         most -= least
-    if -(-N // most) * BH <= 256:
-        return "walk"
-    start, shortest = (32, 256) if n_keep > 32 else (N + 1, 0) if d == 64 else (48, 320) if n_keep > 16 else (24, 192)
-    return "both" if N >= max(start, shortest) else "pipe"
+    return most, -(-N // most) * BH
+
+
+def walk_split(N: int, BH: int, n_keep: int):
+    """Segments of the split units of "walk", and these: the last ones of every XCD, where there is more than a round of
+    units and the workspace of "pipe" has room: what is more than a round in four, or every twelfth in two."""
+    _, units = unit_blocks(N, BH, n_keep)
+    kind, S, groups, _ = split_plan(N, BH, n_keep)
+    q, r = divmod(groups * BH, 8)
+    room = 8 * {"none": 0, "tail": (q + 4) // 5, "all": q + (r > 0)}[kind] * S * (2 if n_keep > 32 else 1)
+    q, r = divmod(units, 8)
+    over = q + (r > 0) - 32
+    n, S = (over, 4) if 0 < over < 32 and 32 * over <= room else (-(-q // 12), 2)
+    if units <= 256 or 8 * n * S > room:
+        return 1, []
+    return S, [u for x in range(8) for end in [x * q + min(x, r) + q + (x < r)] for u in range(end - min(n, q + (x < r)), end)]
 
 
 def rel_err(got: np.ndarray, ref: np.ndarray) -> float:

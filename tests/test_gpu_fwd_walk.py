@@ -15,15 +15,6 @@ import gpu_util as U
 pytestmark = pytest.mark.gpu
 
 
-def unit_blocks(N, H, n_keep):
-    """Query blocks of a unit: 4, 2 with more than 32 retained queries, 8 with at most 16; fewer while all units still
-    are one round of the 256 compute units."""
-    most, least = (8, 2) if n_keep <= 16 else (2, 1) if n_keep > 32 else (4, 1)
-    while most > least and -(-N // (most - least)) * H <= 256:
-        most -= least
-    return most, -(-N // most) * H
-
-
 def check(wl, x, shp, lists, keep, heads, blocks, K=None):
     K = x["K"] if K is None else K
     O, LSE = B.attn_fwd(shp, x["Q"], K, x["V"], lists, keep)
@@ -36,26 +27,39 @@ def check(wl, x, shp, lists, keep, heads, blocks, K=None):
         U.check_tensors(wl.name, f"h{h}", "bf16", [("O", U.host_f64(O[0, h])[sel], rO[sel])], lse=(U.host_f64(LSE[0, h])[sel], rL[sel]))
 
 
-# heads, blocks of a head, share of queries kept -> query blocks of a unit; 0: more units than workgroups, handed out by length
-# (d = 128; with d = 64 one tile a block is the other kernel's there)
-SIZES = [(3, 64, 0.5, 1), (7, 64, 0.5, 2), (12, 48, 0.5, 3), (15, 63, 0.5, 4), (8, 320, 0.5, 0),
-         (3, 64, 1.0, 1), (5, 63, 1.0, 2), (5, 256, 1.0, 0),
-         (5, 63, 0.25, 2), (12, 64, 0.25, 4), (20, 64, 0.25, 6), (28, 61, 0.25, 8), (27, 192, 0.25, 0)]
+# heads, blocks of a head, share of queries kept -> query blocks of a unit.  0: more units than workgroups, handed out by length,
+# and the last ones of every XCD split in two; -1: little more units than workgroups, what is more split in four (d = 128 there
+# where a block has one tile or less: with d = 64 that is the other kernel's)
+SIZES = [(3, 64, 0.5, 1), (7, 64, 0.5, 2), (4, 129, 0.5, 3), (5, 170, 0.5, 4), (8, 320, 0.5, 0), (4, 320, 0.5, -1),
+         (3, 64, 1.0, 1), (5, 63, 1.0, 2), (5, 263, 1.0, 0), (2, 257, 1.0, -1),
+         (5, 63, 0.25, 2), (5, 130, 0.25, 4), (10, 130, 0.25, 6), (14, 133, 0.25, 8), (14, 320, 0.25, 0), (11, 197, 0.25, -1)]
 
 
-@pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("H,N,keep_ratio,blocks", SIZES)
+@pytest.mark.parametrize("H,N,keep_ratio,blocks,d", [(*s, d) for s in SIZES for d in (64, 128) if d == 128 or s[3] > 0 or s[2] == 1.0])
 def test_units(H, N, keep_ratio, blocks, d):
+    part = U.part_of(Workload("", 1, H, d, "bf16", (4, 4, 4 * N), (4, 4, 4)))
+    nk = part.n_keep(keep_ratio)
+    got, units = U.unit_blocks(N, H, nk)
+    groups = -(-N // got)
+    S, split = U.walk_split(N, H, nk)
+    route = U.forward_route(N, H, nk, d)
+    if blocks > 0:
+        assert got == blocks and units <= 256 and route == "walk"
+    else:
+        assert units > 256 and route == "both" and S == (2 if blocks == 0 else 4) and split
     U.progress(f"units H={H} N={N} r={keep_ratio} d={d}")
-    wl = Workload(f"units_{H}_{N}_{keep_ratio}_{d}", 1, H, d, "bf16", (4, 4, 4 * N), (4, 4, 4), threshold=0.7 if blocks else 0.9, keep_ratio=keep_ratio)
-    got, units = unit_blocks(N, H, U.part_of(wl).n_keep(keep_ratio))
-    assert got == blocks if blocks else units > 2 * 256
-    heads = sorted({0, H // 2, H - 1})
+    wl = Workload(f"units_{H}_{N}_{keep_ratio}_{d}", 1, H, d, "bf16", (4, 4, 4 * N), (4, 4, 4), threshold=0.7 if blocks > 0 else 0.9, keep_ratio=keep_ratio)
+    heads = sorted({0, H // 2, H - 1} | {u // groups for u in split[:1]})
     x = U.device_inputs(wl, ("Q", "K", "V"), heads=heads)
     shp, _, _, lists, keep = U.run_indices(wl, x)
-    if not blocks:
+    sample = {0, 1, N // 2, N - 2, N - 1} | {b for u in split[:2] for b in range(u % groups * got, min(N, u % groups * got + got))}
+    check(wl, x, shp, lists, keep, heads, sorted(sample))
+    if blocks <= 0:
         assert lists.nnz.item() >= {0.25: 24, 0.5: 48, 1.0: 32}[keep_ratio] * H * N  # from here on the lists are long
-    check(wl, x, shp, lists, keep, heads, [0, 1, N // 2, N - 2, N - 1])
+        # segments of a split unit that hold nothing but logits of -inf
+        x["Q"][..., 0] = x["Q"][..., 0].abs() + 0.5
+        x["K"][:, :, torch.from_numpy(part.block_tokens()[:int(0.6 * N)].reshape(-1)).cuda(), 0] = float("-inf")
+        check(wl, x, shp, lists, keep, heads, sorted(sample))
 
 
 @pytest.mark.parametrize("N", [2048, 2049, 4100])

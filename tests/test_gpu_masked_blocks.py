@@ -18,7 +18,9 @@ pytestmark = pytest.mark.gpu
 @pytest.mark.parametrize("keep_ratio", [1.0, 0.5, 0.25])
 @pytest.mark.parametrize("d,H", [(64, 5), (128, 1), (128, 20)])
 def test_blocks_at_minus_infinity(keep_ratio, d, H):
-    """32 blocks, all listed.  One head: whole walks.  Five and twenty: four segments a walk, or those of the last ones of an XCD."""
+    """32 blocks, all listed.  One head and five: whole walks of the kernel without a barrier.  Twenty: segments of all walks, or
+    of the last ones of an XCD, of the one with a barrier a tile."""
+    assert U.forward_route(32, H, 64 * keep_ratio, d) == ("pipe" if H == 20 else "walk")
     U.progress(f"masked blocks r={keep_ratio} d={d} H={H}")
     wl = Workload(f"masked_{d}_{H}", 1, H, d, "bf16", (8, 16, 16), (4, 4, 4), threshold=1.0, keep_ratio=keep_ratio)
     x = U.device_inputs(wl, ("Q", "K", "V"), heads=(0, H - 1))
@@ -49,7 +51,8 @@ def test_blocks_at_minus_infinity(keep_ratio, d, H):
 @pytest.mark.parametrize("keep_ratio", [1.0, 0.5, 0.25])
 @pytest.mark.parametrize("N", [12, 32])
 def test_empty_list(keep_ratio, N):
-    """Rows that list nothing, in the same workgroup as rows that do: O is zero and LSE -inf, the others are finite."""
+    """Rows that list nothing, in the same workgroup as rows that do: O is zero and LSE -inf, the others are finite.  12 blocks: the
+    kernel with a barrier a tile, 32: the other one."""
     U.progress(f"empty lists r={keep_ratio} N={N}")
     wl = Workload("empty", 1, 1, 64, "bf16", (4, 4, 4 * N), (4, 4, 4), threshold=0.7, keep_ratio=keep_ratio)
     x = U.device_inputs(wl, ("Q", "K", "V"))
