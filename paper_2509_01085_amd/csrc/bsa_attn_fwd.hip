@@ -284,10 +284,6 @@ __global__ __launch_bounds__(256, 1) void fwd_walk_kernel(FwdArgs) {
   if (!share.item(k, it) || (nth && it.nseg > 1)) return;  // (past the whole units)
   const int64_t bh = it.unit / ngroups;
   const int i0 = (it.unit % ngroups) * a.fwd_blocks, end = min(i0 + a.fwd_blocks, g.N);
-  if (it.nseg > 1 && a.split_by_lists) {
-    it.nseg = min(it.nseg, max(2, pairs_of(g, a.q2k_ptr, it.unit, ngroups, a.fwd_blocks) / kSegPairs));
-    if (it.seg >= it.nseg) return;  // (such items are one a workgroup)
-  }
   const uint16_t* Qh = static_cast<const uint16_t*>(a.Q) + bh * g.L * D;
   kbase = uniform64(static_cast<const uint16_t*>(a.K) + bh * g.L * D);
   vbase = uniform64(static_cast<const uint16_t*>(a.V) + bh * g.L * D);
@@ -850,7 +846,6 @@ struct FwdPlan {
   int units;
   int slots;         // workgroups of an XCD that walk whole units
   int S, n;          // segments of a split unit, split units of an XCD
-  int by_lists;      // 1: fewer segments where lists are short (SplitPlan)
 };
 
 static int mode_of(const Geom& g, int n_keep) { return g.dense || n_keep > 32 ? kTwo : n_keep > 16 ? kOne : kPack; }
@@ -858,20 +853,17 @@ static int mode_of(const Geom& g, int n_keep) { return g.dense || n_keep > 32 ? 
 // One workgroup a CU.  cap: partial results (of a unit's segment) that the workspace holds.
 static FwdPlan plan_fwd(const Geom& g, int mode, int cap) {
   const int most = mode == kPack ? 8 : mode == kTwo ? 2 : 4, least = mode == kPack ? 2 : 1;
-  FwdPlan p{most, 0, 0, 1, 0, 0};
+  FwdPlan p{most, 0, 0, 1, 0};
   auto units_of = [&](int n) { return (g.N + n - 1) / n * g.B * g.H; };
-  // Within one round, the smallest units that still are one: 12 heads of 48 blocks, 32 of 64 queries kept, units of four
-  // blocks 62 us, of three 55.
+  // Within one round, the smallest units that still are one: 4 heads of 128 blocks, 32 of 64 queries kept, 72 listed, units of
+  // four blocks 97 us, of two 71.
   while (p.blocks > least && units_of(p.blocks - least) <= kCUs) p.blocks -= least;
   p.units = units_of(p.blocks);
   const int q = p.units / 8, cmax = q + (p.units % 8 ? 1 : 0);
-  if (2 * p.units <= kCUs && g.N >= 32) {  // less than half a round: every unit in segments
-    p.S = std::min(kCUs / p.units, std::min(8, g.N / 8));
-    p.n = cmax;
-    p.by_lists = 1;
-  } else if (p.units > kCUs) {
+  if (p.units > kCUs) {
     // The last units of an XCD in halves, handed out at the end: enough to even out what the reckoning of lengths misses, no
-    // more, because a segment costs what a unit costs besides its walk and the combine launch its partial results.
+    // more, because a segment costs what a unit costs besides its walk and the combine launch its partial results.  Only while the
+    // workspace has room, which is sized by the other kernel's plan: below twelve rounds of its workgroups.
     // Every twelfth unit in two, against every fifth in four and none: 33,280 tokens 1.77, 1.87 and 1.83 ms, 23,296 tokens
     // with short lists 0.485, 0.548 and 0.486, with a quarter of the queries 0.58, 0.61 and 0.63.
     p.S = 2;
@@ -882,7 +874,7 @@ static FwdPlan plan_fwd(const Geom& g, int mode, int cap) {
       p.n = over;
     }
   }
-  if (8 * p.n * p.S > cap) p.n = p.by_lists = 0, p.S = 1;
+  if (8 * p.n * p.S > cap) p.n = 0, p.S = 1;
   p.slots = std::min(cmax - p.n, kCUs / 8);
   return p;
 }
@@ -906,10 +898,9 @@ int grant_fwd_walk(const Geom& g, const AttnArgs& a) {
 int launch_fwd_walk(const Geom& g, const AttnArgs& args, int cap, FwdSplit& split, hipStream_t st) {
   AttnArgs a = args;
   const FwdPlan p = plan_fwd(g, mode_of(g, a.n_keep), a.fwd_ws ? cap : 0);
-  split = FwdSplit{p.S, p.n, p.by_lists, p.blocks};
+  split = FwdSplit{p.S, p.n, 0, p.blocks};
   a.split_S = p.S;
   a.split_n = p.n;
-  a.split_by_lists = p.by_lists;
   a.fwd_slots = p.slots;
   a.fwd_blocks = p.blocks;
   return for_instance(g, a.n_keep, [&](auto D, auto M) {

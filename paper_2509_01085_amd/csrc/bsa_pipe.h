@@ -68,13 +68,12 @@ struct Item {
 
 // One XCD's range of units, walked as items: the whole units, then the segments of the split ones.
 struct Share {
-  int start, cnt, split, S, sbase, items;
+  int start, cnt, split, S, sbase;
   __device__ inline Share(int x, int units, int S_, int n) : S(S_), sbase(x * n) {
     const int q = units >> 3, r = units & 7;
     start = x * q + min(x, r);
     cnt = q + (x < r ? 1 : 0);
     split = min(n, cnt);
-    items = cnt - split + S * split;
   }
   __device__ inline bool item(int k, Item& it) const {
     const int whole = cnt - split;
