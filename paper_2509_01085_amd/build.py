@@ -2,6 +2,7 @@
 from __future__ import annotations
 
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -32,6 +33,27 @@ FLAGS = [
 # separate registers for what they have in common, and moves between them.
 EXTRA_FLAGS = {"bsa_attn_fwd.hip": ["-mllvm", "-structurizecfg-skip-uniform-regions"]}
 
+# Kernels that keep values in accumulation registers which inline assembly names: the compiler does not know of them, so it may
+# have none of its own there.
+NAMED_ACCUMULATORS = {"bsa_attn_fwd.hip": "fwd_walk_kernel"}
+
+
+def foreign_accumulators(assembly: str, kernel: str):
+    """Instructions of the kernel's instances that name an accumulation register and are not inline assembly, and the number
+    of instances."""
+    found, instances, inside, inline = [], 0, False, False
+    for line in assembly.splitlines():
+        if re.match(r"_Z\w*:", line):
+            inside, inline = kernel in line.split(":")[0], False
+            instances += inside
+        elif line.startswith(".Lfunc_end"):
+            inside = False
+        elif "#ASMSTART" in line or "#ASMEND" in line:
+            inline = "#ASMSTART" in line
+        elif inside and not inline and re.search(r"(?<![\w.@$])a(\d+\b|\[)", line.split(";")[0]):
+            found.append(line.strip())
+    return found, instances
+
 
 def hipcc() -> str:
     for cand in (os.environ.get("HIPCC"), "/opt/rocm/bin/hipcc", "hipcc"):
@@ -59,8 +81,19 @@ def build(verbose: bool = True, out: str = LIB, extra_flags=()) -> str:
             print(err, file=sys.stderr)
         return obj
 
-    with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+    def check(src):
+        cmd = [hipcc(), *FLAGS, *EXTRA_FLAGS.get(src, ()), *extra_flags, "-S", "--cuda-device-only", os.path.join(CSRC, src), "-o", "-"]
+        r = subprocess.run(cmd, capture_output=True, text=True)
+        found, instances = foreign_accumulators(r.stdout, NAMED_ACCUMULATORS[src])
+        if r.returncode or found or not instances:
+            raise RuntimeError(f"{src}: the compiler uses accumulation registers that the source names: {found[:5]}" if found else
+                               f"{src}: no assembly of {NAMED_ACCUMULATORS[src]}:\n{r.stderr[-2000:]}")
+
+    with ThreadPoolExecutor(max_workers=8) as ex:
+        checks = [ex.submit(check, src) for src in NAMED_ACCUMULATORS]
         objs = list(ex.map(comp, SOURCES))
+        for c in checks:
+            c.result()
     LIB_OUT = out
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB_OUT, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
