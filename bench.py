@@ -28,12 +28,37 @@ PEAK_BF16_TFLOPS = 2500.0  # MI355X dense bf16 MFMA peak
 PEAK_HBM_GBS = 8000.0
 
 
-def kernel_instances(d: int, n_keep: int) -> dict:
+def unit_blocks(N: int, BH: int, n_keep: int):
+    """Query blocks of a unit of fwd_walk_kernel, and its units: 4, 2 with more than 32 retained queries, 8 with at most 16; fewer
+    while all units still are one round of the 256 compute units."""
+    most, least = (8, 2) if n_keep <= 16 else (2, 1) if n_keep > 32 else (4, 1)
+    while most > least and -(-N // (most - least)) * BH <= 256:
+        most -= least
+    return most, -(-N // most) * BH
+
+
+def forward_route(N: int, BH: int, n_keep: int, d: int):
+    """Which of the two bf16 forward kernels a sparse call launches (the rule of choose_forward in csrc/bsa_attn_pipe.hip,
+    restated): "walk", "pipe", or "both", where walk works from so many listed blocks a row on; and that number."""
+    half, two = n_keep <= 16, n_keep > 32
+    units = unit_blocks(N, BH, n_keep)[1]
+    if units <= 256:
+        full = not two and N * BH >= 512 and N <= (64 if d == 128 else 128)
+        lone = not two and N >= 256 and N * BH <= 640
+        return "pipe" if full or lone or N < 16 else "walk", 0
+    start = 32 if two else N + 1 if d == 64 else 24 if half else 48
+    shortest = 256 if two else 192 if half and units < 512 else 320
+    return "both" if N >= max(start, shortest) else "pipe", start
+
+
+def kernel_instances(d: int, n_keep: int, walk: bool = True) -> dict:
     """The template instances that the sparse attention calls of a bf16 layer launch, by kernel: main
-    launches only, as a profiler prints them.  tests/test_bench_host.py holds them to the built library."""
+    launches that work, as a profiler prints them (walk: which forward kernel does).  tests/test_bench_host.py holds them
+    to the built library."""
     b = lambda v: "true" if v else "false"
     split, pack = n_keep > 32, n_keep <= 16
-    return {"fwd_walk_kernel": f"<{d}, {1 if split else 2 if pack else 0}>",
+    fwd = {"fwd_walk_kernel": f"<{d}, {1 if split else 2 if pack else 0}>"} if walk else {"fwd_pipe_kernel": f"<{d}, {b(split)}, {b(pack)}>"}
+    return {**fwd,
             "bwd_dq_pipe_kernel": f"<{d}, {b(split)}, false, {b(pack)}>",
             "bwd_dkv_pipe_kernel": f"<{d}, {b(pack)}>"}
 
@@ -317,9 +342,11 @@ def measure(wl, steps, warmup, torch, B, traffic=True):
     dense_flops = 14.0 * wl.B * wl.H * wl.L * wl.L * wl.d
     # credited FLOPs per listed (query block, KV block) pair, in units of d*n_keep*Bk:
     # forward 4 (QK^T, PV); dK/dV kernel 8 (S, dP, dV, dK); dQ kernel 2 (its S/dP recompute is not credited)
-    kernels = {"fwd_walk_kernel": ("attn_fwd", 4), "bwd_dkv_pipe_kernel": ("bwd_dkv", 8), "bwd_dq_pipe_kernel": ("bwd_dq", 2)}
+    route, start = forward_route(shp.N, wl.B * wl.H, nk, wl.d)
+    walk = route == "walk" or (route == "both" and nnz >= start * shp.rows)
+    kernels = {"fwd_walk_kernel" if walk else "fwd_pipe_kernel": ("attn_fwd", 4), "bwd_dkv_pipe_kernel": ("bwd_dkv", 8), "bwd_dq_pipe_kernel": ("bwd_dq", 2)}
     dominant = max(kernels, key=lambda k: parts[kernels[k][0]])
-    instances = kernel_instances(wl.d, nk)
+    instances = kernel_instances(wl.d, nk, walk)
 
     # second denominator: what a register-resident MFMA loop sustains on this GPU (two workgroups per CU)
     sink = torch.empty(512 * 256, dtype=torch.float32, device=dev)

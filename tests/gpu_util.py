@@ -12,6 +12,7 @@ from bsa_workloads import Workload, bf16_round, head_inputs, head_tensor
 from oracle import bsa_oracle as o
 from paper_2509_01085_amd import binding as B
 
+import bench
 import tolerance as T
 
 # Deciding comparisons closer to equality than this (relative to the row's total mass) are
@@ -125,26 +126,12 @@ def split_plan(N: int, BH: int, n_keep: int):
 
 
 def forward_route(N: int, BH: int, n_keep: int, d: int) -> str:
-    """Which of the two bf16 forward kernels a sparse call launches, restated: "walk" (bsa_attn_fwd.hip), "pipe"
-    (bsa_attn_pipe.hip) or "both", where the lists' mean length decides on the device."""
-    half, two = n_keep <= 16, n_keep > 32
-    _, walk_units = unit_blocks(N, BH, n_keep)
-    if walk_units <= 256:
-        full = not two and N * BH >= 512 and N <= (64 if d == 128 else 128)
-        lone = not two and N >= 256 and N * BH <= 640
-        return "pipe" if full or lone or N < 16 else "walk"
-    start = 32 if two else N + 1 if d == 64 else 24 if half else 48
-    shortest = 256 if two else 192 if half and walk_units < 512 else 320
-    return "both" if N >= max(start, shortest) else "pipe"
+    """Which of the two bf16 forward kernels a sparse call launches: "walk" (bsa_attn_fwd.hip), "pipe" (bsa_attn_pipe.hip) or
+    "both", where the lists' mean length decides on the device."""
+    return bench.forward_route(N, BH, n_keep, d)[0]
 
 
-def unit_blocks(N: int, BH: int, n_keep: int):
-    """Query blocks of a unit of "walk", and its units: 4, 2 with more than 32 retained queries, 8 with at most 16; fewer
-    while all units still are one round of the 256 compute units."""
-    most, least = (8, 2) if n_keep <= 16 else (2, 1) if n_keep > 32 else (4, 1)
-    while most > least and -(-N // (most - least)) * BH <= 256:
-        most -= least
-    return most, -(-N // most) * BH
+unit_blocks = bench.unit_blocks
 
 
 def walk_split(N: int, BH: int, n_keep: int):

@@ -10,9 +10,10 @@ from paper_2509_01085_amd import binding as B
 
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("n_keep", [16, 32, 64])
-def test_named_kernels_are_in_the_library(d, n_keep):
+@pytest.mark.parametrize("walk", [True, False])
+def test_named_kernels_are_in_the_library(d, n_keep, walk):
     code = open(B._LIB_PATH, "rb").read()
-    for name, args in bench.kernel_instances(d, n_keep).items():
+    for name, args in bench.kernel_instances(d, n_keep, walk).items():
         vals = [{"true": "Lb1E", "false": "Lb0E"}.get(a, f"Li{a}E") for a in args.strip("<>").split(", ")]
         assert f"{len(name)}{name}I{''.join(vals)}E".encode() in code, name + args
 
