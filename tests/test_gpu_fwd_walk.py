@@ -113,3 +113,20 @@ def test_both_kernels_at_the_limit(keep_ratio, limit):
         ptr, idx = i32(np.cumsum([0] + [len(r) for r in rows])), i32(np.concatenate(rows))
         lists = B.KvLists(ptr, idx, ptr, idx, torch.tensor([len(idx)], device="cuda"), torch.empty(1, dtype=torch.uint8, device="cuda"))
         check(wl, x, shp, lists, keep, [0, H // 2, H - 1], [0, 1, N // 2, N - 1])
+
+
+# heads, blocks of a head, d: more than a round of units, the kernel without a barrier, then, with fewer blocks, the other one
+@pytest.mark.parametrize("H,N,d", [(5, 257, 128), (9, 65, 64), (12, 50, 128), (14, 38, 64)])
+def test_dense_beyond_a_round(H, N, d):
+    U.progress(f"dense H={H} N={N} d={d}")
+    wl = Workload(f"dense_{H}_{N}_{d}", 1, H, d, "bf16", (4, 4, 4 * N), (4, 4, 4), keep_ratio=1.0)
+    assert U.unit_blocks(N, H, 64)[1] > 256
+    heads, blocks = [0, H // 2, H - 1], [0, 1, N // 2, N - 2, N - 1]
+    x = U.device_inputs(wl, ("Q", "K", "V"), heads=heads)
+    O, LSE = B.dense_attn_fwd(U.shape_of(wl), x["Q"], x["K"], x["V"])
+    part = U.part_of(wl)
+    sel = part.block_tokens()[blocks].reshape(-1)
+    for h in heads:
+        rO, rL = o.attn_fwd(*[U.host_f64(x[k][0, h]) for k in "QKV"], part, np.arange(N + 1) * N, np.tile(np.arange(N), N),
+                            np.tile(np.arange(64), (N, 1)), 1 / sqrt(d), q_blocks=blocks)
+        U.check_tensors(wl.name, f"h{h}", "bf16", [("O", U.host_f64(O[0, h])[sel], rO[sel])], lse=(U.host_f64(LSE[0, h])[sel], rL[sel]))

@@ -41,10 +41,15 @@ def _sample(rng, n, k, always=()):
     return sorted(picks)
 
 
-def split_query_blocks(N, BH, n_keep, h):
-    """Query blocks of head h (B = 1) whose forward / dQ walk is split, or []."""
+def split_query_blocks(N, BH, n_keep, h, d):
+    """A query block of head h (B = 1) whose dQ walk is split, and one whose forward walk is, where there are any."""
     _, _, groups, units = U.split_plan(N, BH, n_keep)
-    return [(u % groups) * (8 if n_keep <= 16 else 4) for u in units if u // groups == h]
+    picks = [(u % groups) * (8 if n_keep <= 16 else 4) for u in units if u // groups == h][:1]
+    if U.forward_route(N, BH, n_keep, d) != "pipe":  # (otherwise it is dQ's plan)
+        blocks, _ = U.unit_blocks(N, BH, n_keep)
+        groups = -(-N // blocks)
+        picks += [(u % groups) * blocks for u in U.walk_split(N, BH, n_keep)[1] if u // groups == h][:1]
+    return picks
 
 
 @pytest.mark.parametrize("name", list(PLAN))
@@ -80,7 +85,7 @@ def test_full_size_parity(name):
         # and, where the launch splits walks, a query block of a split unit
         lens = np.diff(ix.q2k_ptr)
         nk = keep.shape[-1]
-        always = [int(np.argmax(lens)), int(np.argmin(lens))] + split_query_blocks(part.N, wl.H, nk, h)[:1]
+        always = [int(np.argmax(lens)), int(np.argmin(lens))] + split_query_blocks(part.N, wl.H, nk, h, wl.d)
         qb = _sample(rng, part.N, n_qb, always=always)
         rO, rL = o.attn_fwd(xi["Q"], xi["K"], xi["V"], part, ix.q2k_ptr, ix.q2k_idx, ix.keep_idx, scale, q_blocks=qb)
         O_in = U.o_storage_of(wl)(rO)

@@ -1,6 +1,7 @@
-"""Forward and dQ launches whose walks are split over several workgroups, all of them or the last ones of every XCD,
-against the oracle: both plans with every variant of the kernels, unit counts that leave a remainder of eight, ragged
-last groups, and lists so short that a walk has fewer segments than the plan or segments without a tile."""
+"""dQ launches, and those of the forward with a barrier a tile, whose walks are split over several workgroups, all of them
+or the last ones of every XCD, against the oracle: both plans with every variant of the kernels (the forward's of two tiles a block
+only where the last ones are split), unit counts that leave a remainder of eight, ragged last groups, and lists so short that a walk has
+fewer segments than the plan or segments without a tile.  (Walks that the other forward splits: test_gpu_fwd_walk.py.)"""
 from math import sqrt
 
 import numpy as np
@@ -23,6 +24,8 @@ def case(H, N, d, keep_ratio, window=(0, 0, 0)):
 
 CASES = {  # heads, blocks of a head, d, share of queries kept -> the plan and its segments
     "all_one": (case(5, 38, 128, 0.5), "all", 4),               # 50 units
+    "all_one_fwd": (case(12, 44, 128, 0.5), "all", 3),          # 132 units, the forward's, too
+    "all_pack_fwd": (case(12, 46, 64, 0.25), "all", 5),         # 72 units of eight blocks, the forward's, too
     "all_two": (case(5, 32, 64, 1.0), "all", 4),                # 40 units
     "all_pack": (case(9, 38, 64, 0.25, (2, 2, 2)), "all", 4),   # 45 units of eight blocks
     "all_long": (case(4, 64, 128, 0.5, (2, 2, 2)), "all", 8),   # 64 units
@@ -52,6 +55,7 @@ def test_split_walks(name, lists):
     N, H, nk = shp.N, wl.H, part.n_keep(wl.keep_ratio)
     got_kind, S, groups, units = U.split_plan(N, H, nk)
     assert (got_kind, S) == (kind, segments)
+    assert U.forward_route(N, H, nk, wl.d) == ("pipe" if kind == "tail" or name.endswith("fwd") else "walk")
     split_heads = sorted({u // groups for u in units})
     heads = sorted({0, H - 1} | ({split_heads[0], split_heads[len(split_heads) // 2]} if kind == "tail" else set()))
     assert kind != "tail" or any(u // groups in heads for u in units)

@@ -32,9 +32,9 @@ shim = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)  # ahead of the runtime in the lo
 from paper_2509_01085_amd import binding as B
 L, p, big = B.lib(), 4096, 1 << 60
 refused = 0
-for d in (64, 128):
-    for n_keep in (16, 32, 64):
-        s = C.byref(B.Shape(1, 2, 8, 8, 16, 4, 4, 4, d, B.BF16).c())
+# 16 blocks of 2 heads; 12 blocks; 330 of 14: both forward kernels and their combine launch, but with d = 64 and one tile a block
+for H, N, d, n_keep in [(2, 16, d, k) for d in (64, 128) for k in (16, 32, 64)] + [(2, 12, d, 32) for d in (64, 128)] + [(14, 330, d, k) for d in (64, 128) for k in (16, 32, 64)]:
+        s = C.byref(B.Shape(1, H, 4, 4, 4 * N, 4, 4, 4, d, B.BF16).c())
         calls = {
             "fwd": lambda: L.bsa_attn_fwd(s, p, p, p, p, p, p, n_keep, 0.1, p, p, p, big, None),
             "bwd": lambda: L.bsa_attn_bwd(s, *[p] * 11, n_keep, 0.1, p, p, p, p, big, None),
@@ -51,6 +51,7 @@ for d in (64, 128):
                     assert shim.shim_grants() == allow + 1 and shim.shim_launches() == 0, (name, d, n_keep, allow, shim.shim_launches())
                     refused += 1
                 allow = 1
+            assert shim.shim_launches() == 3 or not (name == "fwd" and N == 330 and (d, n_keep) in [(128, 16), (128, 32), (128, 64), (64, 64)])
             assert shim.shim_launches() > 0
 print("refused", refused)
 """
@@ -65,4 +66,4 @@ def test_a_refused_lds_request_comes_before_any_launch(tmp_path):
     root = os.path.dirname(os.path.dirname(os.path.abspath(B.__file__)))
     r = subprocess.run([sys.executable, "-c", CHILD, str(so)], cwd=root, capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr[-2000:]
-    assert int(r.stdout.split()[-1]) >= 12  # forward, dQ and dK/dV of the variants each had a request refused
+    assert int(r.stdout.split()[-1]) >= 18  # both forwards, dQ and dK/dV of the variants each had a request refused
