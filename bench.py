@@ -43,7 +43,7 @@ def forward_route(N: int, BH: int, n_keep: int, d: int):
     half, two = n_keep <= 16, n_keep > 32
     units = unit_blocks(N, BH, n_keep)[1]
     if units <= 256:
-        full = not two and N * BH >= 512 and N <= (64 if d == 128 else 128)
+        full = not two and N * BH >= 512 and N <= (128 if d == 64 and not half else 64)
         lone = not two and N >= 256 and N * BH <= 640
         return "pipe" if full or lone or N < 16 else "walk", 0
     start = 32 if two else N + 1 if d == 64 else 24 if half else 48

@@ -879,12 +879,12 @@ static FwdChoice choose_forward(const Geom& g, int n_keep) {
     // tiles a block 66 / 56, 113 / 101 (67 / 63, 114 / 113), one 46 / 41, 72 / 69 (47 / 45, 73 / 74), half 49 / 40, 60 / 57
     // (49 / 41, 61 / 60); half a tile, 12 heads, 72 listed: 134 / 116 (136 / 131).  But pipe, with less than two tiles a block,
     // - where the chip is full of short walks: 48 blocks, 18 and 36 listed, one tile: 46 / 44, 52 / 54 (47 / 50, 53 / 62), half
-    //   46 / 46, 47 / 50 (45 / 48, 47 / 55); d = 64, 4 heads of 128 blocks, 71 and 92 listed: one 49 / 49, 54 / 56 (49 / 55, 54 / 62), half
-    //   43 / 42, 44 / 46 (44 / 47, 44 / 48);
+    //   46 / 46, 47 / 50 (45 / 48, 47 / 55); d = 64, 4 heads of 128 blocks, 71 and 92 listed, one tile: 49 / 49, 54 / 56 (49 / 55, 54 / 62), but
+    //   half, 43, 71 and 92: 39 / 35, 43 / 42, 44 / 46 (40 / 39, 44 / 47, 44 / 48);
     // - where units shrink to a block or four and pipe has several segments for each: 1 head, 520 blocks, half a tile, 48, 200 and 520
     //   listed (independent logits with a deviation of 2): 80 / 78, 146 / 176, 196 / 280; 256 blocks, one tile, 200 listed: 88 / 95;
     // and below 16 blocks, where lists are short whatever the threshold (2 heads of 12 blocks, 3 and 12 listed: 16 / 18, 23 / 23).
-    const bool full = !two && g.rows >= 512 && g.N <= (g.d == 128 ? 64 : 128);
+    const bool full = !two && g.rows >= 512 && g.N <= (one && g.d == 64 ? 128 : 64);
     const bool lone = !two && g.N >= 256 && g.rows <= 640, few = g.N < 16 && !g.dense;
     const bool walk = !full && !lone && !few;
     return {walk, !walk, 0};
