@@ -26,10 +26,10 @@
 //
 // What bounds it: a wavefront's issue (33,280 tokens: something in 60 % of its cycles, a vector instruction in 41 %) next to the
 // matrix cores (busy 38 %), at 2.0 GHz.  At 161,280 tokens the fabric (287 GB in 39 ms).
-// Measured (MI355X, against the walk of four lists with a barrier a tile, bsa_attn_pipe.hip, which stays the faster one
-// where lists are short, one box): 33,280 tokens, 12 heads,
-// d = 128, half of the queries, p = 0.9: 1.97 -> 1.71 ms; 70,400 tokens, 40 heads: 27.8 -> 23.7; dense, 23,296 tokens:
-// 3.40 -> 3.09; 23,296 tokens, d = 64, every query: 1.42 -> 1.18; a quarter of the queries: 0.57 -> 0.54.
+// Measured (MI355X, in turn with the walk of four lists with a barrier a tile, bsa_attn_pipe.hip, which stays the faster one
+// where lists are short): 33,280 tokens, 12 heads, d = 128, half of the queries, p = 0.9: 1.97 -> 1.71 ms; 70,400 tokens, 40
+// heads: 27.8 -> 23.7; dense, 23,296 tokens: 3.40 -> 3.09; 23,296 tokens, d = 64, every query: 1.42 -> 1.18; a quarter of the
+// queries: 0.57 -> 0.54.
 #include <type_traits>
 
 #include "bsa_pipe.h"
